@@ -13,6 +13,7 @@
 //   x6 = log1p(s max_j d_j)
 //   x7 = 2 t_i / (d_i (d_i - 1))   local clustering (0 if d_i < 2)
 // Parameter vector layout: W1 (64x8 row-major), b1 (64), W2 (64x64), b2 (64), W3 (1x64), b3.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -63,32 +64,101 @@ __global__ void k_rowof(int64_t n, const int32_t* __restrict__ rowptr, int32_t* 
     for (int32_t k = rowptr[i]; k < rowptr[i + 1]; ++k) rowof[k] = (int32_t)i;
 }
 
-__global__ void k_features(int64_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                           const unsigned long long* __restrict__ tri2, double s, float* __restrict__ feat) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t a = rowptr[i], b = rowptr[i + 1];
-    const double d = b - a;
-    double s1 = 0.0, s2 = 0.0, mx = 0.0;
-    for (int32_t k = a; k < b; ++k) {
-      const int32_t j = colidx[k];
-      const double dj = rowptr[j + 1] - rowptr[j];
-      s1 += dj;
-      s2 += dj * dj;
-      mx = dj > mx ? dj : mx;
-    }
-    const double t = tri2 ? 0.5 * (double)tri2[i] : 0.0;
-    const double mean = d > 0 ? s1 / d : 0.0;
-    const double rms = d > 0 ? sqrt(s2 / d) : 0.0;
-    float* f = feat + i * NIN;
-    f[0] = (float)log1p(s * d);
-    f[1] = (float)log1p(s * s * d);
-    f[2] = (float)log1p(s * s * s * 2.0 * t);
-    f[3] = (float)log1p(s * s * s1);
-    f[4] = (float)log1p(s * mean);
-    f[5] = (float)log1p(s * rms);
-    f[6] = (float)log1p(s * mx);
-    f[7] = d >= 2 ? (float)(2.0 * t / (d * (d - 1.0))) : 0.f;
+__device__ __forceinline__ double wave_add(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Sums over the neighbours of row i: s1 = sum d_j, s2 = sum d_j^2, mx = max d_j, by a group
+// of G lanes (every lane gets the result) or by a workgroup (G = 256, result in all threads).
+// The sums are integers below 2^53, so their order does not matter.  Rows of up to
+// ROWSUM_LONG neighbours take 16 lanes, the others (first in the decreasing-degree list) a
+// workgroup each: with one thread per row a hub row's chain of dependent loads set the time
+// (R-MAT of 2^19 nodes, features 6408 us and surrogate 6325 us; now 127 and 132 us).
+constexpr int ROWSUM_LONG = 512;
+struct RowSums {
+  double s1, s2, mx;
+};
+
+template <int G>
+__device__ __forceinline__ RowSums row_sums(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                            int32_t a, int32_t b, int sub) {
+  RowSums r{0.0, 0.0, 0.0};
+  for (int64_t k = a + sub; k < b; k += G) {
+    const int32_t j = colidx[k];
+    const double dj = rowptr[j + 1] - rowptr[j];
+    r.s1 += dj;
+    r.s2 += dj * dj;
+    r.mx = fmax(r.mx, dj);
   }
+#pragma unroll
+  for (int off = (G < 64 ? G : 64) / 2; off > 0; off >>= 1) {
+    r.s1 += __shfl_xor(r.s1, off, 64);
+    r.s2 += __shfl_xor(r.s2, off, 64);
+    r.mx = fmax(r.mx, __shfl_xor(r.mx, off, 64));
+  }
+  if constexpr (G == 256) {
+    __shared__ double red[4][3];
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+      red[wave][0] = r.s1;
+      red[wave][1] = r.s2;
+      red[wave][2] = r.mx;
+    }
+    __syncthreads();
+    r.s1 = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+    r.s2 = (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]);
+    r.mx = fmax(fmax(red[0][2], red[1][2]), fmax(red[2][2], red[3][2]));
+  }
+  return r;
+}
+
+// Row of this thread's group and its neighbour sums: the first n_long workgroups take one
+// long row each, the others 16 short rows.  False: nothing to do for this thread; sub is
+// the thread's place in its group.
+__device__ __forceinline__ bool row_task(int64_t n, const int32_t* __restrict__ rowptr,
+                                         const int32_t* __restrict__ colidx, const int32_t* __restrict__ long_rows,
+                                         int n_long, int64_t* row, int* sub, RowSums* rs) {
+  if ((int)blockIdx.x < n_long) {
+    *row = long_rows[blockIdx.x];
+    *sub = threadIdx.x;
+    *rs = row_sums<256>(rowptr, colidx, rowptr[*row], rowptr[*row + 1], threadIdx.x);
+    return true;
+  }
+  *row = ((int64_t)blockIdx.x - n_long) * 16 + (threadIdx.x >> 4);
+  *sub = threadIdx.x & 15;
+  if (*row >= n) return false;  // the 16 lanes of a group leave together
+  const int32_t a = rowptr[*row], b = rowptr[*row + 1];
+  if (b - a > ROWSUM_LONG) return false;
+  *rs = row_sums<16>(rowptr, colidx, a, b, *sub);
+  return true;
+}
+
+__global__ __launch_bounds__(256) void k_features(int64_t n, const int32_t* __restrict__ rowptr,
+                                                  const int32_t* __restrict__ colidx,
+                                                  const unsigned long long* __restrict__ tri2, double s,
+                                                  float* __restrict__ feat, const int32_t* __restrict__ long_rows,
+                                                  int n_long) {
+  int64_t i;
+  int f;
+  RowSums rs;
+  if (!row_task(n, rowptr, colidx, long_rows, n_long, &i, &f, &rs) || f >= NIN) return;
+  const double d = rowptr[i + 1] - rowptr[i];
+  const double t = tri2 ? 0.5 * (double)tri2[i] : 0.0;
+  // lane f of the group writes feature f
+  double x;
+  switch (f) {
+    case 0: x = s * d; break;
+    case 1: x = s * s * d; break;
+    case 2: x = s * s * s * 2.0 * t; break;
+    case 3: x = s * s * rs.s1; break;
+    case 4: x = s * (d > 0 ? rs.s1 / d : 0.0); break;
+    case 5: x = s * (d > 0 ? sqrt(rs.s2 / d) : 0.0); break;
+    case 6: x = s * rs.mx; break;
+    default: x = d >= 2 ? 2.0 * t / (d * (d - 1.0)) : 0.0; break;
+  }
+  feat[i * NIN + f] = (float)(f < 7 ? log1p(x) : x);
 }
 
 // out[j] = Y[nodes[j0 + j], j] for the unit-vector block e_{nodes[j0 .. j0+b)}
@@ -112,189 +182,303 @@ __global__ void k_extract_diag(int b, const int32_t* __restrict__ nodes, int64_t
 }
 
 // ------------------------------------------------------------------ MLP
+// The network is three small contractions and runs on the FP32 matrix cores
+// (v_mfma_f32_16x16x4f32: A 16x4, B 4x16; lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16] and holds D[4 (l / 16) + v][l % 16], v = 0..3).  A wave takes tiles of
+// 16 samples with units as rows and samples as columns: with g = l / 16, c = l % 16 lane l
+// holds units 16 t + 4 g + v (t, v = 0..3) of sample c, in every layer.  That is already the
+// B operand of the next layer's step (t, v), which sums over the units {16 t + 4 g + v : g};
+// the matching A operands W2[16 T + c][16 t + 4 g + v] (and W2^T for the backward pass) sit
+// lane-ordered in LDS as 16-byte vectors, so a layer costs no data movement.  Bound: FP32
+// matrix-core rate (27 kflop per sample forward and backward, 157 TFLOP/s) beside 128 tanhf
+// per sample on the vector units.
+// Measured on 204 800 samples, loss and gradient: one sample per thread with LDS sums
+// 6620 us; this form 200 us.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int MLP_TILE = 16;  // samples per tile
+// No instruction moves across: without these marks the compiler interleaves all the tanhf
+// and operand loads of a tile and spills 133 registers at two waves per SIMD.
+#define MLP_STEP() __builtin_amdgcn_sched_barrier(0)
+
+// Lane-ordered operands: sW2[(4 T + t) 64 + l] = W2[16 T + c][16 t + 4 g ..+3],
+// sW2t[(4 T + t) 64 + l] = W2[16 t + 4 g ..+3][16 T + c] (optional); sb = b1, b2, W3, b3.
+__device__ __forceinline__ void mlp_stage(const float* __restrict__ P, float4* sW2, float4* sW2t, float* sb) {
+  for (int e = threadIdx.x; e < 16 * 64; e += 256) {
+    const int l = e & 63, tt = e >> 6, T = tt >> 2, t = tt & 3, g = l >> 4, c = l & 15;
+    const float* r = P + OW2 + (16 * T + c) * NH + 16 * t + 4 * g;
+    sW2[e] = make_float4(r[0], r[1], r[2], r[3]);
+    if (sW2t) {
+      const float* q = P + OW2 + (16 * t + 4 * g) * NH + 16 * T + c;
+      sW2t[e] = make_float4(q[0], q[NH], q[2 * NH], q[3 * NH]);
+    }
+  }
+  for (int e = threadIdx.x; e < NH; e += 256) {
+    sb[e] = P[OB1 + e];
+    sb[NH + e] = P[OB2 + e];
+    sb[2 * NH + e] = P[OW3 + e];
+  }
+  if (threadIdx.x == 0) sb[3 * NH] = P[OB3];
+}
+
+// W1 operands of lane l: W1[16 T + c][2 g], W1[16 T + c][2 g + 1] (step s sums over the
+// features {2 g + s}).
+__device__ __forceinline__ void mlp_w1(const float* __restrict__ P, int lane, float (&w1)[4][2]) {
+#pragma unroll
+  for (int T = 0; T < 4; ++T)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) w1[T][s] = P[OW1 + (16 * T + (lane & 15)) * NIN + 2 * (lane >> 4) + s];
+}
+
+__device__ __forceinline__ v4f mlp_row4(const float* p) {
+  const float4 b = *reinterpret_cast<const float4*>(p);
+  return v4f{b.x, b.y, b.z, b.w};
+}
+
+// D_T = init_T + sum over units of (lane-ordered matrix) x act, for the four row tiles T.
+__device__ __forceinline__ void mlp_contract(const float4* sM, int lane, const v4f (&act)[4], v4f (&d)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    float4 a[4];
+#pragma unroll
+    for (int T = 0; T < 4; ++T) a[T] = sM[(4 * T + t) * 64 + lane];
+#pragma unroll
+    for (int T = 0; T < 4; ++T) d[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[T].x, act[t][0], d[T], 0, 0, 0);
+#pragma unroll
+    for (int T = 0; T < 4; ++T) d[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[T].y, act[t][1], d[T], 0, 0, 0);
+#pragma unroll
+    for (int T = 0; T < 4; ++T) d[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[T].z, act[t][2], d[T], 0, 0, 0);
+#pragma unroll
+    for (int T = 0; T < 4; ++T) d[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[T].w, act[t][3], d[T], 0, 0, 0);
+    MLP_STEP();
+  }
+}
+
+// Forward pass of one tile: hidden layers h1, h2 and the output of sample l % 16 (in every
+// lane).  x0, x1: features 2 g, 2 g + 1 of that sample.
+__device__ __forceinline__ float mlp_tile(const float (&w1)[4][2], const float4* sW2, const float* sb, int lane,
+                                          float x0, float x1, v4f (&h1)[4], v4f (&h2)[4]) {
+  const int g = lane >> 4;
+#pragma unroll
+  for (int T = 0; T < 4; ++T) {
+    v4f z = mlp_row4(sb + 16 * T + 4 * g);
+    z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[T][0], x0, z, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[T][1], x1, z, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) h1[T][v] = tanhf(z[v]);
+    h2[T] = mlp_row4(sb + NH + 16 * T + 4 * g);
+    MLP_STEP();
+  }
+  mlp_contract(sW2, lane, h1, h2);
+  float y = 0.f;
+#pragma unroll
+  for (int T = 0; T < 4; ++T) {
+    const v4f w3 = mlp_row4(sb + 2 * NH + 16 * T + 4 * g);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      h2[T][v] = tanhf(h2[T][v]);
+      y += w3[v] * h2[T][v];
+    }
+    MLP_STEP();
+  }
+  y += __shfl_xor(y, 16, 64);
+  y += __shfl_xor(y, 32, 64);
+  return y + sb[3 * NH];
+}
+
 __global__ __launch_bounds__(256) void k_mlp_forward(int64_t n, const float* __restrict__ P,
                                                      const float* __restrict__ X, float* __restrict__ out) {
-  __shared__ float sp[NPARAM];
-  for (int e = threadIdx.x; e < NPARAM; e += blockDim.x) sp[e] = P[e];
+  __shared__ float4 sW2[16 * 64];
+  __shared__ __align__(16) float sb[3 * NH + 4];
+  mlp_stage(P, sW2, nullptr, sb);
   __syncthreads();
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    float x[NIN], h1[NH];
-#pragma unroll
-    for (int c = 0; c < NIN; ++c) x[c] = X[i * NIN + c];
-#pragma unroll
-    for (int k = 0; k < NH; ++k) {
-      float z = sp[OB1 + k];
-#pragma unroll
-      for (int c = 0; c < NIN; ++c) z += sp[OW1 + k * NIN + c] * x[c];
-      h1[k] = tanhf(z);
-    }
-    float y = sp[OB3];
-    for (int m = 0; m < NH; ++m) {
-      float z = sp[OB2 + m];
-#pragma unroll
-      for (int k = 0; k < NH; ++k) z += sp[OW2 + m * NH + k] * h1[k];
-      y += sp[OW3 + m] * tanhf(z);
-    }
-    out[i] = y;
-  }
-}
-
-// Forward + backward for chunks of TB samples (one per thread); activations are staged
-// in LDS (row = sample) so the cross-sample gradient sums read them back.  Per-workgroup
-// partial gradients (double, fixed layout, the sum of squared residuals last) are
-// reduced afterwards in a fixed order.
-constexpr int TB = 128;
-__global__ __launch_bounds__(TB) void k_mlp_grad(int64_t n, const float* __restrict__ P, const float* __restrict__ X,
-                                                 const float* __restrict__ tgt, double inv_n,
-                                                 double* __restrict__ partials) {
-  __shared__ float sp[NPARAM];
-  __shared__ float sA[TB][NH + 1];  // h1, later dz1
-  __shared__ float sB[TB][NH + 1];  // h2, later dz2
-  __shared__ float sx[TB][NIN];
-  __shared__ float sdy[TB];
-  __shared__ double sl[TB];
-  const int t = threadIdx.x;
-  for (int e = t; e < NPARAM; e += TB) sp[e] = P[e];
-  double gW2[NH * NH / TB];
-  double gW1[NH * NIN / TB];
-  double gb1 = 0.0, gb2 = 0.0, gW3 = 0.0, gb3 = 0.0, loss = 0.0;
-#pragma unroll
-  for (int q = 0; q < NH * NH / TB; ++q) gW2[q] = 0.0;
-#pragma unroll
-  for (int q = 0; q < NH * NIN / TB; ++q) gW1[q] = 0.0;
-  __syncthreads();
-  const int64_t nchunks = (n + TB - 1) / TB;
-  for (int64_t chk = blockIdx.x; chk < nchunks; chk += gridDim.x) {
-    const int64_t i = chk * TB + t;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  float w1[4][2];
+  mlp_w1(P, lane, w1);
+  const int64_t ntiles = (n + MLP_TILE - 1) / MLP_TILE;
+  for (int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); tile < ntiles; tile += (int64_t)gridDim.x * 4) {
+    const int64_t i = tile * MLP_TILE + c;
     const bool ok = i < n;
-    // forward
-    {
-      float x[NIN], h1[NH];
-#pragma unroll
-      for (int c = 0; c < NIN; ++c) {
-        x[c] = ok ? X[i * NIN + c] : 0.f;
-        sx[t][c] = x[c];
-      }
-#pragma unroll
-      for (int k = 0; k < NH; ++k) {
-        float z = sp[OB1 + k];
-#pragma unroll
-        for (int c = 0; c < NIN; ++c) z += sp[OW1 + k * NIN + c] * x[c];
-        h1[k] = tanhf(z);
-        sA[t][k] = h1[k];
-      }
-      float y = sp[OB3];
-      for (int m = 0; m < NH; ++m) {
-        float z = sp[OB2 + m];
-#pragma unroll
-        for (int k = 0; k < NH; ++k) z += sp[OW2 + m * NH + k] * h1[k];
-        const float h2 = tanhf(z);
-        sB[t][m] = h2;
-        y += sp[OW3 + m] * h2;
-      }
-      const float r = ok ? y - tgt[i] : 0.f;
-      sdy[t] = (float)(2.0 * inv_n) * r;
-      sl[t] = (double)r * (double)r;
-    }
-    __syncthreads();
-    // output layer: dL/dW3[m] = sum_s dy_s h2_s[m]; dL/db3 = sum_s dy_s
-    if (t < NH) {
-      float a = 0.f;
-      for (int s = 0; s < TB; ++s) a += sdy[s] * sB[s][t];
-      gW3 += a;
-    }
-    if (t == 0) {
-      double l = 0.0, d = 0.0;
-      for (int s = 0; s < TB; ++s) {
-        l += sl[s];
-        d += sdy[s];
-      }
-      loss += l;
-      gb3 += d;
-    }
-    __syncthreads();
-    // dz2 = dy W3 (1 - h2^2), in place on the thread's own row
-    {
-      const float dy = sdy[t];
-#pragma unroll
-      for (int m = 0; m < NH; ++m) {
-        const float h2 = sB[t][m];
-        sB[t][m] = dy * sp[OW3 + m] * (1.f - h2 * h2);
-      }
-    }
-    __syncthreads();
-    // dL/dW2[m][k] = sum_s dz2_s[m] h1_s[k];  dL/db2[m] = sum_s dz2_s[m]
-#pragma unroll
-    for (int q = 0; q < NH * NH / TB; ++q) {
-      const int e = t + TB * q;
-      const int m = e / NH, k = e % NH;
-      float acc = 0.f;
-      for (int s = 0; s < TB; ++s) acc += sB[s][m] * sA[s][k];
-      gW2[q] += acc;
-    }
-    if (t < NH) {
-      float a = 0.f;
-      for (int s = 0; s < TB; ++s) a += sB[s][t];
-      gb2 += a;
-    }
-    // dh1 = W2^T dz2 for the thread's own sample
-    float dz1[NH];
-    {
-#pragma unroll
-      for (int k = 0; k < NH; ++k) dz1[k] = 0.f;
-      for (int m = 0; m < NH; ++m) {
-        const float d = sB[t][m];
-#pragma unroll
-        for (int k = 0; k < NH; ++k) dz1[k] += d * sp[OW2 + m * NH + k];
-      }
-#pragma unroll
-      for (int k = 0; k < NH; ++k) {
-        const float h1 = sA[t][k];
-        dz1[k] *= 1.f - h1 * h1;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NH; ++k) sA[t][k] = dz1[k];
-    __syncthreads();
-    // dL/dW1[k][c] = sum_s dz1_s[k] x_s[c];  dL/db1[k] = sum_s dz1_s[k]
-#pragma unroll
-    for (int q = 0; q < NH * NIN / TB; ++q) {
-      const int e = t + TB * q;
-      const int k = e / NIN, c = e % NIN;
-      float acc = 0.f;
-      for (int s = 0; s < TB; ++s) acc += sA[s][k] * sx[s][c];
-      gW1[q] += acc;
-    }
-    if (t < NH) {
-      float a = 0.f;
-      for (int s = 0; s < TB; ++s) a += sA[s][t];
-      gb1 += a;
-    }
-    __syncthreads();
-  }
-  double* out = partials + (int64_t)blockIdx.x * (NPARAM + 1);
-#pragma unroll
-  for (int q = 0; q < NH * NH / TB; ++q) out[OW2 + t + TB * q] = gW2[q];
-#pragma unroll
-  for (int q = 0; q < NH * NIN / TB; ++q) out[OW1 + t + TB * q] = gW1[q];
-  if (t < NH) {
-    out[OB1 + t] = gb1;
-    out[OB2 + t] = gb2;
-    out[OW3 + t] = gW3;
-  }
-  if (t == 0) {
-    out[OB3] = gb3;
-    out[NPARAM] = loss;
+    const float x0 = ok ? X[i * NIN + 2 * g] : 0.f, x1 = ok ? X[i * NIN + 2 * g + 1] : 0.f;
+    v4f h1[4], h2[4];
+    const float y = mlp_tile(w1, sW2, sb, lane, x0, x1, h1, h2);
+    if (ok && g == 0) out[i] = y;
   }
 }
 
-__global__ void k_mlp_grad_finalize(int nparts, const double* __restrict__ partials, double* __restrict__ g) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p <= NPARAM; p += gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int q = 0; q < nparts; ++q) s += partials[(int64_t)q * (NPARAM + 1) + p];
-    g[p] = s;
+// Forward and backward.  dh1 = W2^T dz2 has the layout of the forward layers.  The weight
+// gradients sum over samples (dW2[m][k] = sum_s dz2[m][s] h1[k][s]), so both factors are
+// turned through the wave's own LDS slice: lane l reads samples 4 g .. 4 g + 3 of unit
+// 16 T + c (16 bytes) and step v sums over the samples {4 g + v}.  dW1 takes the features as
+// B operand, with a column of ones behind them that gives db1.  A wave sums at most
+// MLP_MAXT tiles (128 samples) in FP32; the four waves and the rounds are then added in FP64
+// and every workgroup writes one partial (fixed order, the sum of squared residuals last).
+constexpr int MLP_MAXT = 8;
+constexpr int MLP_TS = 20;       // floats per unit row of a turned tile (16 samples, padded)
+constexpr int MLP_WGS = 512;     // two workgroups on each of the 256 CUs
+__global__ __launch_bounds__(256, 2) void k_mlp_grad(int64_t n, const float* __restrict__ P,
+                                                     const float* __restrict__ X, const float* __restrict__ tgt,
+                                                     double inv_n, int tiles_per_wave,
+                                                     double* __restrict__ partials) {
+  constexpr size_t W_BYTES = 2 * 16 * 64 * sizeof(float4);                 // W2 and its transpose
+  constexpr size_t T_BYTES = (size_t)4 * 2 * NH * MLP_TS * sizeof(float);  // two turned tiles per wave
+  static_assert(W_BYTES + T_BYTES >= (NPARAM + 1) * sizeof(double), "the reduction reuses the space");
+  __shared__ __align__(16) unsigned char smem[W_BYTES + T_BYTES];
+  __shared__ __align__(16) float sb[3 * NH + 4];
+  float4* sW2 = reinterpret_cast<float4*>(smem);
+  float4* sW2t = sW2 + 16 * 64;
+  double* red = reinterpret_cast<double*>(smem);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
+  float* tA = reinterpret_cast<float*>(smem + W_BYTES) + (size_t)wave * 2 * NH * MLP_TS;
+  float* tB = tA + NH * MLP_TS;
+  float w1[4][2];
+  mlp_w1(P, lane, w1);
+  const int64_t ntiles = (n + MLP_TILE - 1) / MLP_TILE;
+  const int64_t per = (int64_t)4 * tiles_per_wave;
+  double* out = partials + (int64_t)blockIdx.x * (NPARAM + 1);
+  const float dys = (float)(2.0 * inv_n);
+  for (int64_t base = (int64_t)blockIdx.x * per; base < ntiles; base += (int64_t)gridDim.x * per) {
+    mlp_stage(P, sW2, sW2t, sb);
+    __syncthreads();
+    v4f gW2[4][4], gW1[4], gb2[4], gW3[4];
+#pragma unroll
+    for (int T = 0; T < 4; ++T) {
+      gW1[T] = gb2[T] = gW3[T] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int J = 0; J < 4; ++J) gW2[T][J] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    double gb3 = 0.0, loss = 0.0;
+    for (int q = 0; q < tiles_per_wave; ++q) {
+      const int64_t tile = base + (int64_t)q * 4 + wave;
+      if (tile >= ntiles) break;  // whole wave
+      const int64_t i = tile * MLP_TILE + c;
+      const bool ok = i < n;
+      const float x0 = ok ? X[i * NIN + 2 * g] : 0.f, x1 = ok ? X[i * NIN + 2 * g + 1] : 0.f;
+      float xs[4];  // B operand of dW1: feature c (column 8: ones) of sample 4 g + v
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t s = tile * MLP_TILE + 4 * g + v;
+        xs[v] = (s < n && c < NIN) ? X[s * NIN + c] : (c == NIN ? 1.f : 0.f);
+      }
+      v4f h1[4], h2[4];
+      const float y = mlp_tile(w1, sW2, sb, lane, x0, x1, h1, h2);
+      const float r = ok ? y - tgt[i] : 0.f;
+      const float dy = dys * r;
+      if (g == 0) {
+        loss += (double)r * (double)r;
+        gb3 += (double)dy;
+      }
+      // output layer and dz2 = dy W3 (1 - h2^2), in place
+#pragma unroll
+      for (int T = 0; T < 4; ++T) {
+        const v4f w3 = mlp_row4(sb + 2 * NH + 16 * T + 4 * g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float h = h2[T][v];
+          gW3[T][v] += dy * h;
+          const float dz = dy * w3[v] * (1.f - h * h);
+          gb2[T][v] += dz;
+          h2[T][v] = dz;
+          tA[(16 * T + 4 * g + v) * MLP_TS + c] = dz;
+          tB[(16 * T + 4 * g + v) * MLP_TS + c] = h1[T][v];
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      {
+        v4f b[4];
+#pragma unroll
+        for (int J = 0; J < 4; ++J) b[J] = mlp_row4(tB + (16 * J + c) * MLP_TS + 4 * g);
+#pragma unroll
+        for (int T = 0; T < 4; ++T) {
+          const v4f a = mlp_row4(tA + (16 * T + c) * MLP_TS + 4 * g);
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int J = 0; J < 4; ++J)
+              gW2[T][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v], b[J][v], gW2[T][J], 0, 0, 0);
+          MLP_STEP();
+        }
+      }
+      v4f d[4];
+#pragma unroll
+      for (int T = 0; T < 4; ++T) d[T] = v4f{0.f, 0.f, 0.f, 0.f};
+      mlp_contract(sW2t, lane, h2, d);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int T = 0; T < 4; ++T)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          tA[(16 * T + 4 * g + v) * MLP_TS + c] = d[T][v] * (1.f - h1[T][v] * h1[T][v]);  // dz1
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int T = 0; T < 4; ++T) {
+        const v4f a = mlp_row4(tA + (16 * T + c) * MLP_TS + 4 * g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gW1[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v], xs[v], gW1[T], 0, 0, 0);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    gb3 = wave_add(gb3);
+    loss = wave_add(loss);
+    __syncthreads();
+#pragma unroll 1
+    for (int w = 0; w < 4; ++w) {
+      if (wave == w) {
+        auto put = [&](int at, double v) { red[at] = (w == 0 ? 0.0 : red[at]) + v; };
+#pragma unroll
+        for (int T = 0; T < 4; ++T)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int unit = 16 * T + 4 * g + v;
+#pragma unroll
+            for (int J = 0; J < 4; ++J) put(OW2 + unit * NH + 16 * J + c, (double)gW2[T][J][v]);
+            if (c < NIN) put(OW1 + unit * NIN + c, (double)gW1[T][v]);
+            if (c == NIN) put(OB1 + unit, (double)gW1[T][v]);
+            double s2 = (double)gb2[T][v], s3 = (double)gW3[T][v];
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+              s2 += __shfl_xor(s2, off, 64);
+              s3 += __shfl_xor(s3, off, 64);
+            }
+            if (c == 0) {
+              put(OB2 + unit, s2);
+              put(OW3 + unit, s3);
+            }
+            MLP_STEP();
+          }
+        if (lane == 0) {
+          put(OB3, gb3);
+          put(NPARAM, loss);
+        }
+      }
+      __syncthreads();
+    }
+    const bool first = base == (int64_t)blockIdx.x * per;
+    for (int p = threadIdx.x; p <= NPARAM; p += 256) out[p] = (first ? 0.0 : out[p]) + red[p];
+    __syncthreads();
   }
+}
+
+// g[p] = sum of the partials of p, in a fixed order: 16 parameters per workgroup, 16 phases
+// of partials each (one thread per parameter walking all of them took 170 us for 512).
+__global__ __launch_bounds__(256) void k_mlp_grad_finalize(int nparts, const double* __restrict__ partials,
+                                                           double* __restrict__ g) {
+  __shared__ double s[256];
+  const int el = threadIdx.x & 15, ph = threadIdx.x >> 4;
+  const int p = blockIdx.x * 16 + el;
+  double v = 0.0;
+  if (p <= NPARAM)
+    for (int q = ph; q < nparts; q += 16) v += partials[(int64_t)q * (NPARAM + 1) + p];
+  s[threadIdx.x] = v;
+  __syncthreads();
+  for (int h = 8; h > 0; h >>= 1) {
+    if (ph < h) s[threadIdx.x] += s[threadIdx.x + 16 * h];
+    __syncthreads();
+  }
+  if (ph == 0 && p <= NPARAM) g[p] = s[el];
 }
 
 __global__ void k_adam(float* __restrict__ P, const double* __restrict__ g, double* __restrict__ m,
@@ -320,14 +504,16 @@ struct wl_mlp {
 namespace {
 wl_status mlp_grad(wl_mlp* net, const float* feat, const float* tgt, int64_t n, double* loss) {
   wl_ctx* ctx = net->ctx;
-  const int64_t nchunks = (n + TB - 1) / TB;
-  const int grid = (int)(nchunks < 512 ? nchunks : 512);
+  // one tile per wave while that fills the chip's MLP_WGS workgroups, then up to MLP_MAXT
+  const int64_t ntiles = (n + MLP_TILE - 1) / MLP_TILE;
+  const int tpw = (int)std::min<int64_t>(MLP_MAXT, (ntiles + 4 * MLP_WGS - 1) / (4 * MLP_WGS));
+  const int grid = (int)std::min<int64_t>(MLP_WGS, (ntiles + 4 * tpw - 1) / (4 * tpw));
   WL_TRY(net->partials.ensure((size_t)grid * (NPARAM + 1) * sizeof(double)));
   WL_TRY(net->grad.ensure((size_t)(NPARAM + 1) * sizeof(double)));
-  hipLaunchKernelGGL(k_mlp_grad, dim3(grid), dim3(TB), 0, ctx->stream, n, net->params.as<float>(), feat, tgt,
-                     1.0 / (double)n, net->partials.as<double>());
+  hipLaunchKernelGGL(k_mlp_grad, dim3(grid), dim3(256), 0, ctx->stream, n, net->params.as<float>(), feat, tgt,
+                     1.0 / (double)n, tpw, net->partials.as<double>());
   WL_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_mlp_grad_finalize, dim3((NPARAM + 256) / 256), dim3(256), 0, ctx->stream, grid,
+  hipLaunchKernelGGL(k_mlp_grad_finalize, dim3((NPARAM + 16) / 16), dim3(256), 0, ctx->stream, grid,
                      net->partials.as<double>(), net->grad.as<double>());
   WL_HIP(hipGetLastError());
   if (loss) {
@@ -342,41 +528,45 @@ wl_status mlp_grad(wl_mlp* net, const float* feat, const float* tgt, int64_t n, 
 // part of diag phi and the size of what is left, which the network learns):
 //   base  = 1 + c2m d + c3 tri2           (diag q_2 = (1 - mu) d, diag q_3 = (A^3)_rr)
 //   scale = c4 max(1, d^2 + S2),  S2 = sum_{j in N(r)} d_j   (bounds the 4-walk count)
-__device__ inline void surrogate_terms(int64_t r, const int32_t* __restrict__ rowptr,
-                                       const int32_t* __restrict__ colidx, const unsigned long long* __restrict__ tri2,
-                                       double c2m, double c3, double c4, double* base, double* scale) {
-  const int32_t a = rowptr[r], e = rowptr[r + 1];
-  const double d = e - a;
-  double s2 = 0.0;
-  for (int32_t k = a; k < e; ++k) {
-    const int32_t j = colidx[k];
-    s2 += (double)(rowptr[j + 1] - rowptr[j]);
-  }
-  *base = 1.0 + c2m * d + c3 * (double)tri2[r];
+__device__ inline void surrogate_terms(double d, double s2, double tri2, double c2m, double c3, double c4,
+                                       double* base, double* scale) {
+  *base = 1.0 + c2m * d + c3 * tri2;
   *scale = c4 * fmax(1.0, d * d + s2);
 }
 
 template <typename T>
-__global__ void k_surrogate_diag(int64_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                                 const unsigned long long* __restrict__ tri2, double c2m, double c3, double c4,
-                                 T* __restrict__ base, T* __restrict__ scale) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-    double bs, sc;
-    surrogate_terms(r, rowptr, colidx, tri2, c2m, c3, c4, &bs, &sc);
-    if (base) base[r] = (T)bs;
-    if (scale) scale[r] = (T)sc;
-  }
+__global__ __launch_bounds__(256) void k_surrogate_diag(int64_t n, const int32_t* __restrict__ rowptr,
+                                                        const int32_t* __restrict__ colidx,
+                                                        const unsigned long long* __restrict__ tri2, double c2m,
+                                                        double c3, double c4, T* __restrict__ base,
+                                                        T* __restrict__ scale,
+                                                        const int32_t* __restrict__ long_rows, int n_long) {
+  int64_t r;
+  int sub;
+  RowSums rs;
+  if (!row_task(n, rowptr, colidx, long_rows, n_long, &r, &sub, &rs) || sub != 0) return;
+  double bs, sc;
+  surrogate_terms(rowptr[r + 1] - rowptr[r], rs.s1, (double)tri2[r], c2m, c3, c4, &bs, &sc);
+  if (base) base[r] = (T)bs;
+  if (scale) scale[r] = (T)sc;
 }
 
 // out[j] = (d[j] - base(nodes[j])) / scale(nodes[j]) in place (d: diag phi at the nodes)
+// (one wave per node: the nodes are a caller's sample, hubs among them)
 template <typename T>
-__global__ void k_surrogate_target(int64_t count, const int32_t* __restrict__ nodes,
-                                   const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                                   const unsigned long long* __restrict__ tri2, double c2m, double c3, double c4,
-                                   T* __restrict__ d) {
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < count; j += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void k_surrogate_target(int64_t count, const int32_t* __restrict__ nodes,
+                                                          const int32_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ colidx,
+                                                          const unsigned long long* __restrict__ tri2, double c2m,
+                                                          double c3, double c4, T* __restrict__ d) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < count; j += (int64_t)gridDim.x * 4) {
+    const int64_t r = nodes[j];
+    const int32_t a = rowptr[r], b = rowptr[r + 1];
+    const RowSums rs = row_sums<64>(rowptr, colidx, a, b, lane);
+    if (lane != 0) continue;
     double bs, sc;
-    surrogate_terms(nodes[j], rowptr, colidx, tri2, c2m, c3, c4, &bs, &sc);
+    surrogate_terms(b - a, rs.s1, (double)tri2[r], c2m, c3, c4, &bs, &sc);
     d[j] = (T)(((double)d[j] - bs) / sc);
   }
 }
@@ -385,6 +575,13 @@ __global__ void k_affine(int64_t n, const float* __restrict__ base, const float*
                          float* __restrict__ y) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (base ? base[i] : 0.f) + (scale ? scale[i] : 1.f) * y[i];
+}
+
+// rows that take a whole workgroup in the neighbour-sum kernels
+int rowsum_long(const wl_graph* g) {
+  const auto& dd = g->h_long_deg;  // decreasing
+  return (int)(std::lower_bound(dd.begin(), dd.end(), ROWSUM_LONG, [](int32_t d, int t) { return d > t; }) -
+               dd.begin());
 }
 
 // c_2 (1 - mu), c_3, c_4 of the operator's weights
@@ -436,9 +633,9 @@ wl_status wl_features(wl_graph* g, double scale, void* d_feat) {
   hipStream_t st = g->ctx->stream;
   const unsigned long long* tri = nullptr;
   WL_TRY(graph_tri2(g, &tri));
-  const int gb = (int)std::min<int64_t>(8192, (g->n + 255) / 256);
-  hipLaunchKernelGGL(k_features, dim3(gb), dim3(256), 0, st, g->n, g->rowptr, g->colidx,
-                     tri, scale, (float*)d_feat);
+  const int nl = rowsum_long(g);
+  hipLaunchKernelGGL(k_features, dim3((unsigned)(nl + (g->n + 15) / 16)), dim3(256), 0, st, g->n, g->rowptr,
+                     g->colidx, tri, scale, (float*)d_feat, g->long_rows.as<int32_t>(), nl);
   WL_HIP(hipGetLastError());
   WL_HIP(hipStreamSynchronize(st));
   return WL_OK;
@@ -490,13 +687,14 @@ wl_status wl_surrogate_diag(wl_op* op, void* d_base, void* d_scale) {
   WL_TRY(graph_tri2(g, &tri));
   double c2m, c3, c4;
   surrogate_coeffs(op, &c2m, &c3, &c4);
-  const int gb = (int)std::min<int64_t>(8192, (g->n + 255) / 256);
+  const int nl = rowsum_long(g);
+  const dim3 grid((unsigned)(nl + (g->n + 15) / 16));
   if (op->d.prec == WL_FP32)
-    hipLaunchKernelGGL(k_surrogate_diag<float>, dim3(gb), dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx,
-                       tri, c2m, c3, c4, (float*)d_base, (float*)d_scale);
+    hipLaunchKernelGGL(k_surrogate_diag<float>, grid, dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri,
+                       c2m, c3, c4, (float*)d_base, (float*)d_scale, g->long_rows.as<int32_t>(), nl);
   else
-    hipLaunchKernelGGL(k_surrogate_diag<double>, dim3(gb), dim3(256), 0, g->ctx->stream, g->n, g->rowptr,
-                       g->colidx, tri, c2m, c3, c4, (double*)d_base, (double*)d_scale);
+    hipLaunchKernelGGL(k_surrogate_diag<double>, grid, dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri,
+                       c2m, c3, c4, (double*)d_base, (double*)d_scale, g->long_rows.as<int32_t>(), nl);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }
@@ -584,7 +782,7 @@ wl_status wl_mlp_forward(wl_mlp* net, const void* d_feat, int64_t n, void* d_out
   WL_CHECK(n >= 0 && (n == 0 || (d_feat && d_out)), WL_EINVAL, "wl_mlp_forward: bad arguments");
   if (n == 0) return WL_OK;
   (void)hipSetDevice(net->ctx->device);
-  const int grid = (int)std::min<int64_t>(4096, (n + 255) / 256);
+  const int grid = (int)std::min<int64_t>(1024, (n + 4 * MLP_TILE - 1) / (4 * MLP_TILE));
   hipLaunchKernelGGL(k_mlp_forward, dim3(grid), dim3(256), 0, net->ctx->stream, n, net->params.as<float>(),
                      (const float*)d_feat, (float*)d_out);
   WL_HIP(hipGetLastError());
