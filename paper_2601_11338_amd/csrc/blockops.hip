@@ -12,8 +12,7 @@
 //             widths hold rows in registers with C_k (B x B) broadcast from LDS;
 //             single columns are 16-byte vector updates.
 //  * chol:    Cholesky with deflation of a B x B Gram and the inverse of its
-//             factor, one single-wave workgroup per matrix (batched over graphs or
-//             operator groups).
+//             factor, one workgroup per matrix (batched over graphs or operator groups).
 //  * probes:  Philox4x32-10 (Salmon et al., SC'11) Rademacher / Gaussian blocks.
 //  * small helpers: fills, scaled row sums, degree vector, CSR validation.
 #include "wl_internal.h"
@@ -849,77 +848,6 @@ __global__ __launch_bounds__(256) void k_update(int64_t n, const T* X, int ldx, 
   }
 }
 
-// Right-looking Cholesky with deflation of the b x b matrix in sG (LDS, row stride 65),
-// 64 threads: a pivot <= thr zeroes its row of R and marks the column deflated.  Then
-// the inverse of R on the non-deflated columns (zero elsewhere) overwrites sG and, if
-// Rinv is given, is copied to global memory.
-__device__ void chol_deflate(int b, double* sG, double* sR, int* defl, double thr, double* __restrict__ Rinv) {
-  // Right-looking Cholesky of the upper triangle of sG (stride 65) with deflation: a
-  // pivot at or below thr gives a zero row of R.  Every lane derives the pivot's root
-  // and reciprocals itself, and the trailing update is spread over all 64 lanes with
-  // the operands of four entries loaded before any is written (the workgroup is one
-  // wave, so LDS accesses stay in program order).
-  __shared__ double sdi[64];  // 1 / R_kk (0 for a deflated k)
-  const int t = threadIdx.x;
-  const int bb = b * b;
-  for (int e = t; e < bb; e += 64) sR[(e / b) * 65 + e % b] = 0.0;
-  __syncthreads();
-  for (int k = 0; k < b; ++k) {
-    const double p = sG[k * 65 + k];
-    const bool dk = !(p > thr) || !(p > 0.0);
-    const double rkk = dk ? 0.0 : sqrt(p);
-    const double irkk = dk ? 0.0 : 1.0 / rkk;
-    const double ip = irkk * irkk;
-    if (t == 0) {
-      defl[k] = dk ? 1 : 0;
-      sdi[k] = irkk;
-    }
-    if (t >= k && t < b) sR[k * 65 + t] = (t == k) ? rkk : sG[k * 65 + t] * irkk;
-    for (int e0 = 0; e0 < bb; e0 += 256) {
-      double gi[4], gj[4], gij[4];
-      int at[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = e0 + q * 64 + t;
-        const int i = e / b, j = e - (e / b) * b;
-        at[q] = (e < bb && i > k && j >= i) ? i * 65 + j : -1;
-        if (at[q] >= 0) {
-          gi[q] = sG[k * 65 + i];
-          gj[q] = sG[k * 65 + j];
-          gij[q] = sG[at[q]];
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (at[q] >= 0) sG[at[q]] = gij[q] - gi[q] * gj[q] * ip;
-    }
-    __syncthreads();
-  }
-  // the factorisation has consumed sG: column t of the inverse is built in place there
-  // by back substitution (R_ii^{-1} from sdi; deflated rows and columns stay zero)
-  if (t < b) {
-    for (int i = b - 1; i >= 0; --i) {
-      if (defl[i] || defl[t]) {
-        sG[i * 65 + t] = 0.0;
-        continue;
-      }
-      double v0 = (i == t) ? 1.0 : 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
-      int j = i + 1;
-      for (; j + 3 < b; j += 4) {
-        v0 -= sR[i * 65 + j] * sG[j * 65 + t];
-        v1 -= sR[i * 65 + j + 1] * sG[(j + 1) * 65 + t];
-        v2 -= sR[i * 65 + j + 2] * sG[(j + 2) * 65 + t];
-        v3 -= sR[i * 65 + j + 3] * sG[(j + 3) * 65 + t];
-      }
-      for (; j < b; ++j) v0 -= sR[i * 65 + j] * sG[j * 65 + t];
-      sG[i * 65 + t] = ((v0 + v1) + (v2 + v3)) * sdi[i];
-    }
-  }
-  __syncthreads();
-  if (Rinv)
-    for (int e = t; e < bb; e += 64) Rinv[e] = sG[(e / b) * 65 + e % b];
-}
-
 // One projection step of block Lanczos (classical Gram-Schmidt against V_{j-1} and
 // V_j).  P stacks nbv + 1 b x b blocks: [V_{j-1}^T W'; V_j^T W'; W'^T W'] (nbv = 2) or
 // [V_j^T W'; W'^T W'] (nbv = 1).  Outputs: Aout = sym(V_j^T W') (the diagonal block of
@@ -927,7 +855,7 @@ __device__ void chol_deflate(int b, double* sG, double* sR, int* defl, double th
 // max_i (W'^T W')_ii, the block's scale before projection.  The projected block's
 // Gram is then taken from W itself: forming it by Pythagoras from these inner
 // products fails as soon as the basis loses orthogonality (converged Ritz vectors).
-__global__ __launch_bounds__(64) void k_lanczos_proj(int b, int nbv, const double* __restrict__ P,
+__global__ __launch_bounds__(256) void k_lanczos_proj(int b, int nbv, const double* __restrict__ P,
                                                      double* __restrict__ Aout, double* __restrict__ Cc, int64_t gs,
                                                      double* __restrict__ ref_out) {
   // one workgroup per graph of a batch: every matrix of graph g sits gs doubles further
@@ -940,7 +868,7 @@ __global__ __launch_bounds__(64) void k_lanczos_proj(int b, int nbv, const doubl
   const bool hasP1 = nbv == 2;
   const double* Aj = P + (size_t)(nbv - 1) * bb;
   const double* Gp = P + (size_t)nbv * bb;
-  for (int e = t; e < bb; e += 64) {
+  for (int e = t; e < bb; e += 256) {
     const int i = e / b, j = e % b;
     const double a = 0.5 * (Aj[i * b + j] + Aj[j * b + i]);
     Aout[e] = a;
@@ -948,15 +876,36 @@ __global__ __launch_bounds__(64) void k_lanczos_proj(int b, int nbv, const doubl
     Cc[(size_t)(nbv - 1) * bb + e] = -a;
     Cc[(size_t)nbv * bb + e] = i == j ? 1.0 : 0.0;
   }
-  if (t == 0 && ref_out) {
-    double m = 0.0;
-    for (int i = 0; i < b; ++i) m = fmax(m, Gp[i * b + i]);
-    ref_out[go] = m;
+  if (t < 64 && ref_out) {  // (one thread walking the diagonal waits b times for memory)
+    double m = t < b ? fmax(0.0, Gp[t * b + t]) : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (t == 0) ref_out[go] = m;
   }
 }
 
-// Cholesky with deflation, one workgroup of 64 threads, b <= 64.
-__global__ __launch_bounds__(64) void k_chol(int b, const double* __restrict__ G, double tol,
+// Cholesky with deflation of the b x b matrix G (b <= B), one workgroup of NT threads:
+// G = R^T R, a pivot at or below tol * ref gives a zero row of R and a zero column of Rinv.
+// Bound: latency, one serial step per column.  The matrix stays in registers: thread
+// (g, c) = (t / B, t % B) holds the entries (GR u + g, c), u < EPL, of G and of the unit
+// lower factor's inverse E, which the same row operations build (Rinv = E^T / diag), so a
+// step is one exchange of row k through LDS, the pivot's root, and EPL independent updates;
+// there is no back substitution and no serial product for Bout = R Rprev.
+// Measured (with the launch): 16 columns 14.1 us -> 7.3 us, 30 columns 47.7 -> 10.2, 32 columns
+// 108 -> 20.0 (average over both CholQR passes of a step), against the form that kept G in LDS and walked R^{-1} and Bout one
+// row per lane.
+template <int NT>
+__device__ __forceinline__ void chol_sync() {
+  if constexpr (NT == 64) {  // one wave: LDS accesses stay in program order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+template <int B, int NT>
+__global__ __launch_bounds__(NT) void k_chol(int b, const double* __restrict__ G, double tol,
                                              const double* __restrict__ Aref, const double* __restrict__ Bref,
                                              double* __restrict__ R, double* __restrict__ Rinv,
                                              const double* __restrict__ Rprev, double* __restrict__ Bout,
@@ -969,21 +918,6 @@ __global__ __launch_bounds__(64) void k_chol(int b, const double* __restrict__ G
   if (skip_out) skip_out += go;
   if (skip_in) skip_in += go;
   const int t = threadIdx.x;
-  if (skip_in && *skip_in != 0.0) {
-    // second pass not needed: identity factors, Bout = Rprev (the first pass's factor)
-    G += go;
-    if (R) R += go;
-    Rinv += go;
-    if (Rprev) Rprev += go;
-    if (Bout) Bout += go;
-    for (int e = t; e < b * b; e += 64) {
-      const double id = (e / b == e % b) ? 1.0 : 0.0;
-      if (R) R[e] = id;
-      Rinv[e] = id;
-      if (Bout) Bout[e] = Rprev ? Rprev[e] : id;
-    }
-    return;
-  }
   G += go;
   if (Aref) Aref += go;
   if (Bref) Bref += go;
@@ -991,19 +925,29 @@ __global__ __launch_bounds__(64) void k_chol(int b, const double* __restrict__ G
   Rinv += go;
   if (Rprev) Rprev += go;
   if (Bout) Bout += go;
+  if (skip_in && *skip_in != 0.0) {
+    // second pass not needed: identity factors, Bout = Rprev (the first pass's factor)
+    for (int e = t; e < b * b; e += NT) {
+      const double id = (e / b == e % b) ? 1.0 : 0.0;
+      if (R) R[e] = id;
+      Rinv[e] = id;
+      if (Bout) Bout[e] = Rprev ? Rprev[e] : id;
+    }
+    return;
+  }
   if ((int)blockIdx.x == dg) {
     // A group of independent single-column processes (different operators side by
     // side): only the diagonal of G is meaningful.  Each column is factorised alone and
     // judged against its own scale (G_ii, A_ii^2 + B_ii^2, and for the later check the
     // diagonal of dref when given); one pass is exact, so no second pass is asked for.
-    for (int e = t; e < b * b; e += 64) {
+    for (int e = t; e < b * b; e += NT) {
       if (R) R[e] = 0.0;
       Rinv[e] = 0.0;
       if (Bout) Bout[e] = 0.0;
     }
     __syncthreads();
     const double* dr = dref ? dref + go : nullptr;
-    for (int i = t; i < b; i += 64) {
+    for (int i = t; i < b; i += NT) {
       const int d = i * b + i;
       const double g = G[d];
       double sref = g;
@@ -1034,63 +978,119 @@ __global__ __launch_bounds__(64) void k_chol(int b, const double* __restrict__ G
     }
     return;
   }
-  __shared__ double sG[64 * 65];
-  __shared__ double sR[64 * 65];
-  __shared__ int defl[64];
-  __shared__ double sref;
-  // (t defined above)
-  for (int e = t; e < b * b; e += 64) {
-    const int i = e / b, j = e % b;
-    sG[i * 65 + j] = 0.5 * (G[i * b + j] + G[j * b + i]);
-    sR[i * 65 + j] = 0.0;
+  constexpr int GR = NT / B, EPL = B / GR;
+  static_assert(GR * EPL == B, "entries per thread");
+  __shared__ double sR[B * B], sP[B * B];
+  __shared__ double rowG[2][B], rowE[2][B];
+  __shared__ double sRd[B], sBd[B];
+  __shared__ double sref[NT / 64][2];
+  const int c = t % B, g = t / B;
+  double a[EPL], e[EPL];
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int i = GR * u + g;
+    a[u] = (i < b && c < b) ? 0.5 * (G[i * b + c] + G[c * b + i]) : 0.0;
+    e[u] = i == c ? 1.0 : 0.0;
   }
-  __syncthreads();
+  if (Bout && Rprev) {
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) {
+      const int i = GR * u + g;
+      sP[i * B + c] = (i < b && c < b) ? Rprev[i * b + c] : 0.0;
+    }
+  }
+  // reference scale: max diagonal of G and ||Aref||_F^2 + ||Bref||_F^2 over b
   {
-    // reference scale: max diagonal of G and ||Aref||_F^2 + ||Bref||_F^2 over b, the
-    // sums spread over the 64 lanes of the (single-wave) workgroup
     double m = 0.0, fa = 0.0;
-    for (int i = t; i < b; i += 64) m = fmax(m, sG[i * 65 + i]);
+#pragma unroll
+    for (int u = 0; u < EPL; ++u)
+      if (GR * u + g == c) m = fmax(m, a[u]);
     if (Aref)
-      for (int e = t; e < b * b; e += 64) fa += Aref[e] * Aref[e];
+      for (int k = t; k < b * b; k += NT) fa += Aref[k] * Aref[k];
     if (Bref)
-      for (int e = t; e < b * b; e += 64) fa += Bref[e] * Bref[e];
+      for (int k = t; k < b * b; k += NT) fa += Bref[k] * Bref[k];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
       m = fmax(m, __shfl_xor(m, off, 64));
       fa += __shfl_xor(fa, off, 64);
     }
-    if (t == 0) {
-      sref = fmax(m, fa / b);
-      if (ref_out) ref_out[0] = sref;  // reference scale for a later check
+    if ((t & 63) == 0) {
+      sref[t >> 6][0] = m;
+      sref[t >> 6][1] = fa;
     }
   }
   __syncthreads();
-  chol_deflate(b, sG, sR, defl, tol * sref, Rinv);
-  for (int e = t; e < b * b; e += 64) {
-    const int i = e / b, j = e % b;
-    if (R) R[e] = sR[i * 65 + j];
-  }
-  // diagonal of Bout, kept on chip for the checks below (0 for a dropped component)
-  __shared__ double sBd[64];
-  if (Bout) {
-    __syncthreads();
-    if (Rprev) {  // the first pass's factor, staged (sG is free once Rinv is written)
-      for (int e = t; e < b * b; e += 64) sG[(e / b) * 65 + e % b] = Rprev[e];
-      __syncthreads();
+  double ref, thr;
+  {
+    double m = 0.0, fa = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      m = fmax(m, sref[w][0]);
+      fa += sref[w][1];
     }
-    if (t < b) {
-      for (int j = 0; j < b; ++j) {
-        double s;
-        if (Rprev) {
-          s = 0.0;
-          for (int k = t; k <= j; ++k) s += sR[t * 65 + k] * sG[k * 65 + j];  // both upper triangular
-        } else {
-          s = sR[t * 65 + j];
+    ref = fmax(m, fa / b);
+    thr = tol * ref;
+    if (t == 0 && ref_out) ref_out[0] = ref;  // reference scale for a later check
+  }
+#pragma unroll
+  for (int u0 = 0; u0 < EPL; ++u0) {
+#pragma unroll 1
+    for (int g0 = 0; g0 < GR; ++g0) {
+      const int k = GR * u0 + g0, buf = k & 1;
+      if (k >= b) break;
+      if (g == g0) {
+        rowG[buf][c] = a[u0];
+        rowE[buf][c] = e[u0];
+      }
+      chol_sync<NT>();
+      const double p = rowG[buf][k];
+      const double gj = rowG[buf][c], ej = rowE[buf][c];
+      const bool dk = !(p > thr) || !(p > 0.0);
+      const double rkk = dk ? 0.0 : sqrt(p);
+      const double irkk = dk ? 0.0 : 1.0 / rkk;
+      const double ip = irkk * irkk;
+#pragma unroll
+      for (int u = u0; u < EPL; ++u) {
+        const int i = GR * u + g;
+        if (i > k) {
+          const double m = rowG[buf][i] * ip;
+          a[u] -= m * gj;
+          e[u] -= m * ej;
         }
-        Bout[t * b + j] = s;
-        if (j == t) sBd[t] = s;
+      }
+      if (g == g0) {  // row k of R, and of R^{-T}
+        a[u0] = c == k ? rkk : (c > k ? gj * irkk : 0.0);
+        e[u0] = ej * irkk;
+        sR[k * B + c] = a[u0];
+        if (c == k) sRd[k] = rkk;
       }
     }
+  }
+  __syncthreads();
+  if (R) {
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) {
+      const int i = GR * u + g;
+      if (i < b && c < b) R[i * b + c] = a[u];
+    }
+  }
+  if (Bout) {
+    if (Rprev) {
+#pragma unroll
+      for (int u = 0; u < EPL; ++u) a[u] = 0.0;
+      for (int k = 0; k < b; ++k) {
+        const double q = sP[k * B + c];
+#pragma unroll
+        for (int u = 0; u < EPL; ++u) {
+          const int i = GR * u + g;
+          if (i <= k && k <= c) a[u] += sR[i * B + k] * q;  // both upper triangular
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < EPL; ++u)
+      if (GR * u + g == c) sBd[c] = a[u];
+    __syncthreads();
     // Bout is the R factor of the block as stored (R of its true Gram, or R2 R1 after a
     // second pass), so Bout_kk is the true norm of its k-th orthogonal component.
     // Components at the rounding level of the reference scale are dropped: column k of
@@ -1098,33 +1098,43 @@ __global__ __launch_bounds__(64) void k_chol(int b, const double* __restrict__ G
     // instead of carrying normalised noise.
     if (ref_in && post_tol > 0.0) {
       const double lim = post_tol * sqrt(fmax(ref_in[0], 0.0));
-      if (t < b && fabs(sBd[t]) <= lim) {
-        for (int j = 0; j < b; ++j) Bout[t * b + j] = 0.0;
-        for (int i = 0; i < b; ++i) Rinv[i * b + t] = 0.0;
-        sBd[t] = 0.0;
+#pragma unroll
+      for (int u = 0; u < EPL; ++u) {
+        const int i = GR * u + g;
+        if (i < b && fabs(sBd[i]) <= lim) a[u] = e[u] = 0.0;
       }
+      __syncthreads();
+      if (t < b && fabs(sBd[t]) <= lim) sBd[t] = 0.0;
     }
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) {
+      const int i = GR * u + g;
+      if (i < b && c < b) Bout[i * b + c] = c >= i ? a[u] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int i = GR * u + g;
+    if (i < b && c < b) Rinv[c * b + i] = c <= i ? e[u] : 0.0;
   }
   // Is a second CholQR pass needed?  One pass with the Gram accumulated in FP64 leaves
   // the new block orthonormal to about u_64 kappa^2; kappa^2 is the ratio of the largest
   // to the smallest kept pivot.  skip_out = 1 when min / max >= skip_ratio.
   if (skip_out) {
     __syncthreads();
-    double pmax = 0.0, pmin = INFINITY;
-    for (int k = t; k < b; k += 64) {
-      const double r = sR[k * 65 + k];
-      const bool kept = r > 0.0 && !(Bout && sBd[k] == 0.0);
-      if (kept) {
-        pmax = fmax(pmax, r * r);
-        pmin = fmin(pmin, r * r);
+    if (t < 64) {
+      double pmax = 0.0, pmin = INFINITY;
+      if (t < b) {
+        const double r = sRd[t];
+        if (r > 0.0 && !(Bout && sBd[t] == 0.0)) pmax = pmin = r * r;
       }
-    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
-      pmin = fmin(pmin, __shfl_xor(pmin, off, 64));
+      for (int off = 32; off > 0; off >>= 1) {
+        pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
+        pmin = fmin(pmin, __shfl_xor(pmin, off, 64));
+      }
+      if (t == 0) *skip_out = (pmax == 0.0 || pmin >= skip_ratio * pmax) ? 1.0 : 0.0;
     }
-    if (t == 0) *skip_out = (pmax == 0.0 || pmin >= skip_ratio * pmax) ? 1.0 : 0.0;
   }
 }
 
@@ -1644,7 +1654,7 @@ wl_status launch_lanczos_proj(wl_ctx* ctx, int b, int nbv, const double* P, doub
                               double* ref_out, int ngraphs, int64_t gs) {
   WL_CHECK(b >= 1 && b <= 64 && (nbv == 1 || nbv == 2) && ngraphs >= 1, WL_EINVAL,
            "lanczos projection: bad sizes");
-  hipLaunchKernelGGL(k_lanczos_proj, dim3(ngraphs), dim3(64), 0, ctx->stream, b, nbv, P, Aout, Cc, gs, ref_out);
+  hipLaunchKernelGGL(k_lanczos_proj, dim3(ngraphs), dim3(256), 0, ctx->stream, b, nbv, P, Aout, Cc, gs, ref_out);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }
@@ -1654,8 +1664,19 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
                       double* ref_out, const double* ref_in, double post_tol, double* skip_out, double skip_ratio,
                       const double* skip_in, int dg, const double* dref) {
   WL_CHECK(b >= 1 && b <= 64 && ngraphs >= 1, WL_EINVAL, "chol: b out of range");
-  hipLaunchKernelGGL(k_chol, dim3(ngraphs), dim3(64), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv, Rprev, Bout,
-                     gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+  // the smallest size that holds the matrix, 16 entries per thread at most
+  if (b <= 8)
+    hipLaunchKernelGGL((k_chol<8, 64>), dim3(ngraphs), dim3(64), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv, Rprev,
+                       Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+  else if (b <= 16)
+    hipLaunchKernelGGL((k_chol<16, 64>), dim3(ngraphs), dim3(64), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
+                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+  else if (b <= 32)
+    hipLaunchKernelGGL((k_chol<32, 256>), dim3(ngraphs), dim3(256), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
+                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+  else
+    hipLaunchKernelGGL((k_chol<64, 256>), dim3(ngraphs), dim3(256), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
+                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }

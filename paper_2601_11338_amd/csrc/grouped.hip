@@ -661,11 +661,12 @@ __global__ __launch_bounds__(256) void k_lanczos_proj_deferred(int nbv, const do
   if (nbv == 2) Cc[t] = -c1;
   Cc[(nbv - 1) * 256 + t] = -c2;
   Cc[nbv * 256 + t] = i == j ? 1.0 : 0.0;
-  if (t == 0 && ref_out) {
+  if (t < 64 && ref_out) {
     const double* Gp = P + nbv * 256;
-    double m = 0.0;
-    for (int d = 0; d < 16; ++d) m = fmax(m, Gp[d * 16 + d]);
-    ref_out[go] = m;
+    double m = t < 16 ? fmax(0.0, Gp[t * 17]) : 0.0;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (t == 0) ref_out[go] = m;
   }
 }
 
