@@ -134,18 +134,45 @@ T* tptr(const DevBuf& b, size_t off_elems = 0) {
 
 }  // namespace
 
-// The autotuned shape of (prec, b) if there is one, else a heuristic from the mean
-// degree: enough neighbour slots per row to cover about half the mean degree.
+// Lanes one row segment takes in launch_spmm when G allows it.
+static int segment_lanes(int prec, int b) {
+  const int vw = prec == WL_FP32 ? 4 : 2;
+  const int w = b % vw == 0 ? vw : (prec == WL_FP32 && b % 2 == 0 ? 2 : 1);
+  const int l = b / w;
+  if (l < 32) return next_pow2(l);
+  return w == vw ? (l % 16 == 0 ? 16 : lanes_for(prec, b)) : 32;
+}
+
+// The autotuned shape of (prec, b) if there is one, else a rule from the mean degree.
+// A neighbour slot has eight gathers in flight, so a row gets about one slot per eight
+// neighbours: more slots leave most lanes idle (and the row's epilogue runs on one slot
+// only), fewer make serial rounds.  Measured (product alone, us, slots 1 / 2 / 4 / 8):
+// Barabasi-Albert n = 10^6, mean degree 10, FP32 16 wide 177 / 172 / 172 / 196, 32 wide
+// 196 / 197 / 215 / 338, FP64 8 wide 171 / 169 / 180 / 259; lattice, degree 2.8, FP64 16 wide
+// 38 / 57 / 106 / 213; R-MAT 2^18, degree 29, 32 wide 117 / 113 / 111 / 112.  (One slot per two
+// neighbours, the earlier rule, took the last column or beyond.)  Four-lane segments
+// take two slots from degree 6 on (172 against 177 above).
+// A graph too small to fill the chip (below 2^19 lanes, eight waves per CU) is bound by its
+// longest chain instead and takes up to one slot per two neighbours (5000 nodes, 5 columns: L X
+// 1.78 ms with one slot, 1.56 with eight).
+// Rows over the threshold go to whole workgroups: 16 rounds of a row's slots (R-MAT 2^19, 64
+// wide: 415 us at 512 to 2048, 447 at 256; flat for the graphs without heavy tails), 4 rounds
+// in a small graph.
 SpmmShape shape_for(wl_graph* g, int prec, int b) {
   auto it = g->tuned.find(prec * 1000 + std::min(b, 999));
   if (it != g->tuned.end()) return it->second;
   SpmmShape s;
-  const int lpn = lanes_for(prec, b);
-  int ns = next_pow2(std::max(1, (int)std::ceil(g->mean_deg))) / 2;
-  if (ns < 1) ns = 1;
-  int G = std::max(4, std::min(64, lpn * ns));
-  s.G = G;
-  s.long_thr = std::max(g->long_min_thr, 32 * (G / lpn));
+  const int lpn = segment_lanes(prec, b);
+  int ns = 1;
+  while (ns < 64 && 8.0 * ns * std::sqrt(2.0) < g->mean_deg) ns <<= 1;  // nearest power of two
+  if (lpn == 4 && g->mean_deg >= 6.0) ns = std::max(ns, 2);
+  int thr = 128 * ns;
+  if (g->n * lpn * ns < (1 << 19)) {
+    while (g->n * lpn * ns < (1 << 19) && 2.0 * ns < g->mean_deg) ns <<= 1;
+    thr = 32 * ns;
+  }
+  s.G = std::max(4, std::min(64, lpn * ns));
+  s.long_thr = std::max(g->long_min_thr, thr);
   return s;
 }
 
