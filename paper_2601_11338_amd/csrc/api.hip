@@ -834,16 +834,61 @@ int coeffs_by_eig(int K, int b, const std::vector<double>& hA, const std::vector
   return 0;
 }
 
+// phi X = V F (or its Laplacian finish) from coefficients on the device
+template <typename T>
+wl_status recombine_device(wl_graph* g, const T* basis, int b, int K, const double* F, const T* wv, const T* Xw,
+                           T* Y) {
+  if (wv) return launch_update<T>(g->ctx, g->n, basis, b, g->n * b, K, F, Xw, 0.0, wv, -1.0, Y, b, nullptr);
+  return launch_update<T>(g->ctx, g->n, basis, b, g->n * b, K, F, nullptr, 0.0, nullptr, 1.0, Y, b, nullptr);
+}
+
 template <typename T>
 wl_status recombine(wl_graph* g, const T* basis, int b, int K, const std::vector<double>& F, DevBuf& coef,
                     const T* wv, const T* Xw, T* Y) {
   WL_TRY(coef.ensure(F.size() * sizeof(double)));
   WL_HIP(hipMemcpyAsync(coef.p, F.data(), F.size() * 8, hipMemcpyHostToDevice, g->ctx->stream));
   WL_HIP(hipStreamSynchronize(g->ctx->stream));
-  if (wv)
-    return launch_update<T>(g->ctx, g->n, basis, b, g->n * b, K, coef.as<double>(), Xw, 0.0, wv, -1.0, Y, b, nullptr);
-  return launch_update<T>(g->ctx, g->n, basis, b, g->n * b, K, coef.as<double>(), nullptr, 0.0, nullptr, 1.0, Y, b,
-                          nullptr);
+  return recombine_device<T>(g, basis, b, K, coef.as<double>(), wv, Xw, Y);
+}
+
+// Coefficients of exp(-t x) on [lo, hi] in Chebyshev polynomials of the interval,
+// e^{-t lo} e^{-z} (2 - [k = 0]) (-1)^k I_k(z) with z = t (hi - lo) / 2: ratios I_k / I_{k-1} by
+// the backward recurrence, scaled by e^{-z} (I_0 + 2 sum I_k) = 1.  Degree about 9 sqrt(z) (the
+// coefficients fall like exp(-k^2 / 2z) and end below 1e-19).
+std::vector<double> cheb_exp_coeffs(double t, double lo, double hi) {
+  const double z = 0.5 * t * (hi - lo);
+  const int deg = (int)std::ceil(9.1 * std::sqrt(z)) + 24;
+  std::vector<double> c(deg + 1, 0.0);
+  double r = 0.0;
+  for (int k = deg + 32; k > deg; --k) r = 1.0 / (2.0 * k / z + r);
+  for (int k = deg; k > 0; --k) c[k] = r = 1.0 / (2.0 * k / z + r);
+  double p = 1.0, sum = 1.0;
+  for (int k = 1; k <= deg; ++k) {
+    p *= c[k];
+    sum += 2.0 * p;
+    c[k] = k & 1 ? -2.0 * p : 2.0 * p;
+  }
+  const double scale = std::exp(-t * lo) / sum;
+  c[0] = scale;
+  for (int k = 1; k <= deg; ++k) c[k] *= scale;
+  while (c.size() > 2 && std::fabs(c.back()) < 1e-19) c.pop_back();
+  return c;
+}
+
+// ||T||_inf of the block tridiagonal T.
+double block_tridiag_norm(int K, int b, const std::vector<double>& hA, const std::vector<double>& hB) {
+  double mx = 0.0;
+  for (int j = 0; j < K; ++j)
+    for (int r = 0; r < b; ++r) {
+      double s = 0.0;
+      for (int c = 0; c < b; ++c) {
+        s += std::fabs(hA[((size_t)j * b + r) * b + c]);
+        if (j > 0) s += std::fabs(hB[((size_t)(j - 1) * b + r) * b + c]);
+        if (j + 1 < K) s += std::fabs(hB[((size_t)j * b + c) * b + r]);
+      }
+      mx = std::max(mx, s);
+    }
+  return mx;
 }
 
 // phi X through the fused recurrence.
@@ -1042,6 +1087,9 @@ wl_status phi_apply_impl(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
 template wl_status phi_apply_impl<float>(wl_op*, const float*, float*, int, const float*, const float*);
 template wl_status phi_apply_impl<double>(wl_op*, const double*, double*, int, const double*, const double*);
 
+constexpr int EXPV_CHEB_M = 100;       // rows of T from which the series runs on the device
+constexpr double EXPV_CHEB_Z = 4e4;    // t ||T|| / 2 up to which its degree (9 sqrt z) stays below 2000
+
 template <typename T>
 wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* const* Y, int outer_dim,
                     double* err_est) {
@@ -1063,6 +1111,48 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
   WL_TRY(block_lanczos<T>(g, L, U0, b, K, std::max(op->d.reorth, 2), op->outer_basis.as<T>(), op->outer_w.as<T>(),
                           op->outer_small, hA, hB, hR0, &Ke));
   const int m = Ke * b;
+  // || B_{K-1} F_last ||_F with F_last the last block row of F (no error left: 0)
+  auto residual = [&](const double* Fl) {
+    double e2 = 0.0;
+    const double* Bl = &hB[(size_t)(K - 1) * b * b];
+    for (int r = 0; r < b; ++r)
+      for (int c = 0; c < b; ++c) {
+        double s = 0.0;
+        for (int k = 0; k < b; ++k) s += Bl[(size_t)r * b + k] * Fl[(size_t)k * b + c];
+        e2 += s * s;
+      }
+    return std::sqrt(e2);
+  };
+  // exp(-t T) E_1 R0 as a Chebyshev series on the device where T is large (the host's
+  // eigendecomposition takes 9 m^3 operations: 105 ms at m = 1280, against 2.4 ms for the
+  // three times 0.1, 1, 10) and the degree moderate.  The interval ends just below 0: L is
+  // positive semidefinite, and a Ritz value pushed below 0 by rounding stays next to it.  The
+  // work blocks lie in memory that the basis no longer needs, so no call needs more of it.
+  const double tmax = *std::max_element(t, t + nt), hi = block_tridiag_norm(Ke, b, hA, hB);
+  if (m >= EXPV_CHEB_M && hi > 0.0 && is_finite(hi) && 0.5 * tmax * hi <= EXPV_CHEB_Z &&
+      (size_t)n * sizeof(T) >= (size_t)m * sizeof(double)) {
+    SmallLayout Ly{b, K, (size_t)b * b};
+    double* S = op->outer_small.as<double>();
+    double *X0 = S + Ly.P(), *X1 = op->outer_w.as<double>();  // m b doubles each
+    WL_TRY(op->outer_coef.ensure((size_t)m * b * sizeof(double)));
+    std::vector<double> last((size_t)nt * b * b);
+    for (int it = 0; it < nt; ++it) {
+      const double lo = t[it] > 0.0 ? -std::min(0.01 * hi, 1.0 / t[it]) : -0.01 * hi;
+      std::vector<double> c = t[it] > 0.0 ? cheb_exp_coeffs(t[it], lo, hi) : std::vector<double>{1.0, 0.0};
+      WL_TRY(launch_cheb(g->ctx, b, Ke, S + Ly.A(0), S + Ly.B(0), S + Ly.R0(), 2.0 / (hi - lo), (hi + lo) / (hi - lo),
+                         c, X0, X1, op->outer_coef.as<double>()));
+      if (err_est && Ke == K)
+        WL_HIP(hipMemcpyAsync(&last[(size_t)it * b * b], op->outer_coef.as<double>() + (size_t)(K - 1) * b * b,
+                              (size_t)b * b * 8, hipMemcpyDeviceToHost, g->ctx->stream));
+      WL_TRY(recombine_device<T>(g, op->outer_basis.as<T>(), b, Ke, op->outer_coef.as<double>(), nullptr, nullptr,
+                                 Y[it]));
+    }
+    if (err_est) {
+      WL_HIP(hipStreamSynchronize(g->ctx->stream));
+      for (int it = 0; it < nt; ++it) err_est[it] = Ke == K ? residual(&last[(size_t)it * b * b]) : 0.0;
+    }
+    return WL_OK;
+  }
   std::vector<double> Tm = assemble_T(Ke, b, hA, hB);
   // T = U diag(lam) U^T in factored form (U is applied to blocks, never formed)
   SymEig E;
@@ -1087,20 +1177,7 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
     std::vector<double> F((size_t)m * b);
     for (int r = 0; r < m; ++r)
       for (int c = 0; c < b; ++c) F[(size_t)r * b + c] = Fall[(size_t)r * nb + it * b + c];
-    if (err_est) {
-      // || B_{K-1} F_last ||_F with F_last the last block row of F
-      double e2 = 0.0;
-      if (Ke == K) {
-        const double* Bl = &hB[(size_t)(K - 1) * b * b];
-        for (int r = 0; r < b; ++r)
-          for (int c = 0; c < b; ++c) {
-            double s = 0.0;
-            for (int k = 0; k < b; ++k) s += Bl[(size_t)r * b + k] * F[(size_t)((K - 1) * b + k) * b + c];
-            e2 += s * s;
-          }
-      }
-      err_est[it] = std::sqrt(e2);
-    }
+    if (err_est) err_est[it] = Ke == K ? residual(&F[(size_t)(K - 1) * b * b]) : 0.0;
     WL_TRY(recombine<T>(g, op->outer_basis.as<T>(), b, Ke, F, op->outer_coef, nullptr, nullptr, Y[it]));
     if (it + 1 < nt) WL_HIP(hipStreamSynchronize(g->ctx->stream));  // coefficient buffer is reused
   }

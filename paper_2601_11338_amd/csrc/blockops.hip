@@ -15,6 +15,8 @@
 //             factor, one workgroup per matrix (batched over graphs or operator groups).
 //  * probes:  Philox4x32-10 (Salmon et al., SC'11) Rademacher / Gaussian blocks.
 //  * small helpers: fills, scaled row sums, degree vector, CSR validation.
+#include <utility>
+
 #include "wl_internal.h"
 
 namespace {
@@ -1149,6 +1151,69 @@ __global__ void k_dtranspose(int b, const double* __restrict__ x, double* __rest
   for (int e = threadIdx.x; e < b * b; e += blockDim.x) y[(e % b) * b + e / b] = x[e];
 }
 
+// One term of a Chebyshev series in a block tridiagonal T (K blocks of b x b, A_j and
+// T_{j+1,j} = B_j): X0 <- T_k = two (al T X1 - be X1) - X0 with X1 = T_{k-1} and X0 = T_{k-2}
+// ((K b) x b each; first: X0 is only written and two is 1), F += c T_k.  Workgroup (j, q) owns
+// CHEB_ROWS rows of block row j; the three blocks of X1 it meets and its rows of T are staged in
+// LDS.  A launch costs about as long as its work (a 1280 x 32 term: 9.2 us).
+constexpr int CHEB_ROWS = 8;
+__global__ __launch_bounds__(256) void k_cheb_step(int b, int K, const double* __restrict__ A,
+                                                   const double* __restrict__ B, double al, double be, int first,
+                                                   const double* __restrict__ X1, double* __restrict__ X0, double c,
+                                                   double* __restrict__ F) {
+  extern __shared__ double sh[];
+  const int j = blockIdx.x, r0 = blockIdx.y * CHEB_ROWS, bb = b * b;
+  double* sX = sh;           // 3 b x b
+  double* sM = sh + 3 * bb;  // 3 CHEB_ROWS x b
+  for (int e = threadIdx.x; e < 3 * bb; e += 256) {
+    const int q = e / bb, jj = j - 1 + q;
+    sX[e] = jj >= 0 && jj < K ? X1[(int64_t)jj * bb + (e - q * bb)] : 0.0;
+  }
+  for (int e = threadIdx.x; e < 3 * CHEB_ROWS * b; e += 256) {
+    const int q = e / (CHEB_ROWS * b), w = e - q * CHEB_ROWS * b, r = r0 + w / b, k = w % b;
+    double v = 0.0;
+    if (r < b) {
+      if (q == 1) v = A[(int64_t)j * bb + r * b + k];
+      if (q == 0 && j > 0) v = B[(int64_t)(j - 1) * bb + r * b + k];
+      if (q == 2 && j + 1 < K) v = B[(int64_t)j * bb + k * b + r];
+    }
+    sM[e] = v;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < CHEB_ROWS * b; e += 256) {
+    const int r = r0 + e / b, col = e % b;
+    if (r >= b) break;
+    double s = 0.0;
+    for (int q = 0; q < 3; ++q) {
+      const double* M = sM + q * CHEB_ROWS * b + (r - r0) * b;
+      const double* X = sX + q * bb + col;
+      double s0 = 0.0, s1 = 0.0;
+      int k = 0;
+      for (; k + 1 < b; k += 2) {
+        s0 += M[k] * X[k * b];
+        s1 += M[k + 1] * X[(k + 1) * b];
+      }
+      if (k < b) s0 += M[k] * X[k * b];
+      s += s0 + s1;
+    }
+    const int64_t at = (int64_t)j * bb + r * b + col;
+    double v = al * s - be * sX[bb + r * b + col];
+    if (!first) v = 2.0 * v - X0[at];
+    X0[at] = v;
+    F[at] += c * v;
+  }
+}
+
+// X = E_1 R0, F = c X
+__global__ void k_cheb_init(int count, int bb, const double* __restrict__ R0, double c, double* __restrict__ X,
+                            double* __restrict__ F) {
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < count; e += gridDim.x * blockDim.x) {
+    const double v = e < bb ? R0[e] : 0.0;
+    X[e] = v;
+    F[e] = c * v;
+  }
+}
+
 template <typename T>
 __global__ void k_fill(int64_t count, T value, T* __restrict__ out) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
@@ -1678,6 +1743,24 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
     hipLaunchKernelGGL((k_chol<64, 256>), dim3(ngraphs), dim3(256), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
                        Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
   WL_HIP(hipGetLastError());
+  return WL_OK;
+}
+
+wl_status launch_cheb(wl_ctx* ctx, int b, int K, const double* A, const double* B, const double* R0, double al,
+                      double be, const std::vector<double>& c, double* X0, double* X1, double* F) {
+  WL_CHECK(b >= 1 && b <= 64 && K >= 1 && c.size() >= 2, WL_EINVAL, "Chebyshev series: bad sizes");
+  const int count = K * b * b;
+  hipLaunchKernelGGL(k_cheb_init, dim3(grid_for(count, 256, 512)), dim3(256), 0, ctx->stream, count, b * b, R0, c[0],
+                     X1, F);
+  WL_HIP(hipGetLastError());
+  const dim3 grid((unsigned)K, (unsigned)((b + CHEB_ROWS - 1) / CHEB_ROWS));
+  const size_t lds = (size_t)3 * (b + CHEB_ROWS) * b * sizeof(double);
+  for (size_t k = 1; k < c.size(); ++k) {
+    hipLaunchKernelGGL(k_cheb_step, grid, dim3(256), lds, ctx->stream, b, K, A, B, al, be, k == 1 ? 1 : 0, X1, X0,
+                       c[k], F);
+    WL_HIP(hipGetLastError());
+    std::swap(X0, X1);
+  }
   return WL_OK;
 }
 

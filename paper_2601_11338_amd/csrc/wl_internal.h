@@ -340,6 +340,12 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
 wl_status launch_lanczos_proj(wl_ctx* ctx, int b, int nbv, const double* P, double* Aout, double* Cc,
                               double* ref_out = nullptr, int ngraphs = 1, int64_t gs = 0);
 
+// F = sum_k c_k T_k(al T - be) E_1 R0 (Chebyshev polynomials; (K b) x b doubles) for the block
+// tridiagonal T of K blocks A_j, T_{j+1,j} = B_j (b x b row-major, consecutive).  X0, X1: work
+// of the size of F.  One launch per term, no synchronisation.
+wl_status launch_cheb(wl_ctx* ctx, int b, int K, const double* A, const double* B, const double* R0, double al,
+                      double be, const std::vector<double>& c, double* X0, double* X1, double* F);
+
 // Small device helpers on double matrices.
 wl_status launch_dadd(wl_ctx* ctx, int count, const double* x, double* y);   // y += x
 wl_status launch_dcopy(wl_ctx* ctx, int count, const double* x, double* y);  // y = x
