@@ -39,11 +39,26 @@ __global__ __launch_bounds__(256) void k_wspmm(int64_t n, const int32_t* __restr
   const int c = blockIdx.y * TB + lane % TB;
   const int s = lane / TB;
   const bool ok = c < b;
+  // U entries' indices and values are loaded together, then their U gathers (entry by entry
+  // a row waited for two loads per entry); the order of the sum is unchanged.  In the
+  // V-cycle of a 490k-node lattice, 16 columns: 23.3 us per launch on average with the
+  // coarsest sweeps, 18.8 us without those and with this.
+  constexpr int U = 8;
   double acc = 0.0;
   const int e1 = rp[r + 1];
-  for (int e = rp[r] + s; e < e1; e += S) {
-    const int j = ci[e];
-    if (ok) acc += v[e] * X[(int64_t)j * b + c];
+  for (int64_t e = rp[r] + s; e < e1; e += U * S) {
+    int j[U];
+    double a[U], x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = e + u * S < e1;
+      j[u] = in ? ci[e + u * S] : 0;
+      a[u] = in ? v[e + u * S] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = ok && e + u * S < e1 ? X[(int64_t)j[u] * b + c] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += a[u] * x[u];
   }
 #pragma unroll
   for (int off = TB; off < 16; off <<= 1) acc += __shfl_xor(acc, off, 16);
@@ -58,6 +73,53 @@ __global__ __launch_bounds__(256) void k_wspmm(int64_t n, const int32_t* __restr
       out = X[o] + jw[r] * (Z[o] - acc);
     Y[o] = out;
   }
+}
+
+// The coarsest-level solver in one launch: `sweeps` l1-Jacobi sweeps from zero, x <- x + jw
+// (B - M x), for column blockIdx.x.  Matrix and iterate stay in LDS; 256 / rows lanes share a
+// row (rpw rows at a time).  A launch per sweep took 8 to 10 us for a matrix of 64 rows (29 of
+// them per V-cycle); the whole solve takes 48 us.
+constexpr int COARSE_ROWS = 512;
+constexpr int COARSE_NNZ = 9000;  // 12 bytes each in LDS
+__global__ __launch_bounds__(256) void k_coarse_solve(int n, int nnz, const int32_t* __restrict__ rp,
+                                                      const int32_t* __restrict__ ci, const double* __restrict__ v,
+                                                      const double* __restrict__ jw, const double* __restrict__ B,
+                                                      int b, int sweeps, int lpr, double* __restrict__ out) {
+  extern __shared__ double sh[];
+  double* sv = sh;            // nnz
+  double* sx = sv + nnz;      // 2 n
+  double* sj = sx + 2 * n;    // n
+  double* sb = sj + n;        // n
+  int* srp = reinterpret_cast<int*>(sb + n);  // n + 1
+  int* sci = srp + n + 1;                     // nnz
+  const int c = blockIdx.x, t = threadIdx.x;
+  for (int e = t; e < nnz; e += 256) {
+    sv[e] = v[e];
+    sci[e] = ci[e];
+  }
+  for (int r = t; r < n; r += 256) {
+    const double bv = B[(int64_t)r * b + c], w = jw[r];
+    sb[r] = bv;
+    sj[r] = w;
+    sx[r] = w * bv;
+  }
+  for (int r = t; r <= n; r += 256) srp[r] = rp[r];
+  __syncthreads();
+  const int sub = t % lpr, rpw = 256 / lpr;
+  for (int s = 1; s < sweeps; ++s) {
+    const double* x = sx + ((s - 1) & 1) * n;
+    double* y = sx + (s & 1) * n;
+    for (int r0 = 0; r0 < n; r0 += rpw) {
+      const int r = r0 + t / lpr;
+      double acc = 0.0;
+      if (r < n)
+        for (int e = srp[r] + sub; e < srp[r + 1]; e += lpr) acc += sv[e] * x[sci[e]];
+      for (int off = lpr / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+      if (r < n && sub == 0) y[r] = x[r] + sj[r] * (sb[r] - acc);
+    }
+    __syncthreads();
+  }
+  for (int r = t; r < n; r += 256) out[(int64_t)r * b + c] = sx[((sweeps - 1) & 1) * n + r];
 }
 
 // X = jw (.) B row-wise (the first l1-Jacobi sweep from zero)
@@ -140,13 +202,28 @@ __global__ __launch_bounds__(256) void k_cg_p(int64_t n, int b, const double* __
   }
 }
 
-// out[c] = sum over workgroups of partials (fixed order)
-__global__ void k_colsum_finish(int nparts, int b, const double* __restrict__ partials, double* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= b) return;
-  double s = 0.0;
-  for (int k = 0; k < nparts; ++k) s += partials[(int64_t)k * b + c];
-  out[c] = s;
+// out[c] = sum over workgroups of partials (fixed order): one workgroup, 256 / bp phases of
+// partials per column, then a tree.  (One thread per column walking them all: 114 us for
+// 479 partials; now 5.1 us.)
+__global__ __launch_bounds__(256) void k_colsum_finish(int nparts, int b, int bp, const double* __restrict__ partials,
+                                                       double* __restrict__ out) {
+  __shared__ double red[256];
+  const int c = threadIdx.x % bp, ph = threadIdx.x / bp, np = 256 / bp;
+  double u[4] = {0.0, 0.0, 0.0, 0.0};
+  if (c < b) {
+    int k = ph;
+    for (; k + 3 * np < nparts; k += 4 * np)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u[i] += partials[(int64_t)(k + i * np) * b + c];
+    for (; k < nparts; k += np) u[0] += partials[(int64_t)k * b + c];
+  }
+  red[threadIdx.x] = (u[0] + u[1]) + (u[2] + u[3]);
+  __syncthreads();
+  for (int h = 128; h >= bp; h >>= 1) {
+    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if ((int)threadIdx.x < b) out[threadIdx.x] = red[threadIdx.x];
 }
 
 // Y = c0 x (phi X), or Y = w (.) Xw - c0 x (L X)
@@ -237,7 +314,7 @@ wl_status coldot(wl_ctx* ctx, AmgState& st, int64_t n, int b, const double* X, c
   hipLaunchKernelGGL(k_coldot, dim3(g), dim3(256), 0, ctx->stream, n, b, pow2_at_least(b), X, Y,
                      st.partials.as<double>());
   WL_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_colsum_finish, dim3((b + 63) / 64), dim3(64), 0, ctx->stream, (int)g, b,
+  hipLaunchKernelGGL(k_colsum_finish, dim3(1), dim3(256), 0, ctx->stream, (int)g, b, pow2_at_least(b),
                      st.partials.as<double>(), out);
   WL_HIP(hipGetLastError());
   return WL_OK;
@@ -287,6 +364,17 @@ wl_status vcycle(wl_op* op, AmgState& st, int l, const double* bv, double* out, 
     st.products += (double)L.nnz * b;
     return launch_wspmm(ctx, n, L.rp, L.ci, L.v, xin, b, WM_SWEEP, bv, L.jw.as<double>(), xout);
   };
+  if (last && l > 0 && n >= 1 && n <= COARSE_ROWS && L.nnz <= COARSE_NNZ && st.prm.coarse_sweeps >= 1) {
+    int lpr = 1;
+    while (lpr < 64 && 2 * lpr * n <= 256) lpr <<= 1;
+    const size_t lds = (size_t)(L.nnz + 4 * n) * 8 + (size_t)(n + 1 + L.nnz) * 4;
+    hipLaunchKernelGGL(k_coarse_solve, dim3(b), dim3(256), lds, ctx->stream, (int)n, (int)L.nnz, L.rp.as<int32_t>(),
+                       L.ci.as<int32_t>(), L.v.as<double>(), L.jw.as<double>(), bv, b, st.prm.coarse_sweeps, lpr,
+                       out);
+    WL_HIP(hipGetLastError());
+    st.products += (double)L.nnz * b * (st.prm.coarse_sweeps - 1);
+    return WL_OK;
+  }
   // first sweep from zero: x = M^-1 b
   hipLaunchKernelGGL(k_rowscale, dim3(grid_elems(n * b)), dim3(256), 0, ctx->stream, n, b, L.jw.as<double>(), bv,
                      last && st.prm.coarse_sweeps == 1 ? out : x);
@@ -445,7 +533,7 @@ wl_status phi_amg<double>(wl_op* op, const double* X, double* Y, int b, const do
     hipLaunchKernelGGL(k_cg_xr, dim3(gd), dim3(256), 0, ctx->stream, n, b, bp, rz, pq, x, r, p, q,
                        st.partials.as<double>());
     WL_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_colsum_finish, dim3((b + 63) / 64), dim3(64), 0, ctx->stream, (int)gd, b,
+    hipLaunchKernelGGL(k_colsum_finish, dim3(1), dim3(256), 0, ctx->stream, (int)gd, b, bp,
                        st.partials.as<double>(), rr);
     WL_HIP(hipGetLastError());
     WL_HIP(hipMemcpyAsync(h.data(), rr, b * 8, hipMemcpyDeviceToHost, ctx->stream));
