@@ -1,16 +1,16 @@
 // Tall-skinny block kernels for the Krylov drivers and estimators (gfx950).
 //
-//  * gram:    X^T Y for n x B blocks (B <= 64), double accumulation.  FP32 blocks of
-//             16, 32 or 64 columns use the FP64 matrix cores on 16-row chunks;
-//             other shapes stage 32-row tiles in LDS with every thread owning
-//             entries (i, j); single columns are plain 16-byte dot products.
+//  * gram:    X^T Y for n x B blocks (B <= 64), double accumulation, on the FP64 matrix
+//             cores in 16-row chunks from five columns on (FP32 blocks of 16, 32 or 64
+//             columns staged through LDS); two to four columns stage 32-row tiles in LDS
+//             with every thread owning an entry; single columns are 16-byte dot products.
 //             Per-workgroup partials are reduced by a second kernel in a fixed
 //             order, so results are bitwise reproducible.
-//  * update:  Out = w (.) Yin + beta * sum_k X_k C_k.  16-wide FP32 blocks run as a
-//             tall-skinny product on the FP32 matrix cores with the FP64 Gram of the
-//             result fused (block CholQR needs W^T W right after W is formed); other
-//             widths hold rows in registers with C_k (B x B) broadcast from LDS;
-//             single columns are 16-byte vector updates.
+//  * update:  Out = w (.) Yin + beta * sum_k X_k C_k, from five columns on as a
+//             tall-skinny product on the matrix cores of the block's precision with the
+//             FP64 Gram of the result fused (block CholQR needs W^T W right after W is
+//             formed); two to four columns hold rows in registers with C_k (B x B) broadcast
+//             from LDS; single columns are 16-byte vector updates.
 //  * chol:    Cholesky with deflation of a B x B Gram and the inverse of its
 //             factor, one workgroup per matrix (batched over graphs or operator groups).
 //  * probes:  Philox4x32-10 (Salmon et al., SC'11) Rademacher / Gaussian blocks.
@@ -23,25 +23,22 @@ namespace {
 
 constexpr int GRAM_TR = 32;  // rows per LDS tile in the Gram kernel
 
+// Blocks of up to four columns: a thread per entry (i, j) and row phase.
 template <int B>
 __global__ __launch_bounds__(256) void k_gram_partial(int64_t n, const float* __restrict__ Xf,
                                                       const double* __restrict__ Xd, int ldx, int64_t sX,
                                                       const float* __restrict__ Yf, const double* __restrict__ Yd,
                                                       int ldy, int bx, int by, double* __restrict__ partials) {
   constexpr int E = B * B;
-  constexpr int QE = E >= 256 ? E / 256 : 1;
+  static_assert(E < 256, "one entry per thread");
+  constexpr int P = 256 / E;  // row phases
   __shared__ double sx[GRAM_TR * B];
   __shared__ double sy[GRAM_TR * B];
   __shared__ double sred[256];
   const int tid = threadIdx.x;
   const int64_t xoff = (int64_t)blockIdx.y * sX;
-  double acc[QE];
-#pragma unroll
-  for (int q = 0; q < QE; ++q) acc[q] = 0.0;
-  // entries-per-thread layout for E < 256: P row phases
-  constexpr int P = E >= 256 ? 1 : 256 / E;
-  const int e_small = tid % E;
-  const int p_small = tid / E;
+  const int i = (tid % E) / B, j = (tid % E) % B, p = tid / E;
+  double acc = 0.0;
   const int64_t ntiles = (n + GRAM_TR - 1) / GRAM_TR;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t row0 = t * GRAM_TR;
@@ -57,38 +54,16 @@ __global__ __launch_bounds__(256) void k_gram_partial(int64_t n, const float* __
       sy[idx] = yv;
     }
     __syncthreads();
-    if constexpr (E >= 256) {
-#pragma unroll
-      for (int q = 0; q < QE; ++q) {
-        const int e = tid + q * 256;
-        const int i = e / B, j = e % B;
-        double s = acc[q];
-#pragma unroll 8
-        for (int r = 0; r < GRAM_TR; ++r) s += sx[r * B + i] * sy[r * B + j];
-        acc[q] = s;
-      }
-    } else {
-      if (p_small < P) {
-        const int i = e_small / B, j = e_small % B;
-        double s = acc[0];
-        for (int r = p_small; r < GRAM_TR; r += P) s += sx[r * B + i] * sy[r * B + j];
-        acc[0] = s;
-      }
-    }
+    if (p < P)
+      for (int r = p; r < GRAM_TR; r += P) acc += sx[r * B + i] * sy[r * B + j];
     __syncthreads();
   }
-  double* out = partials + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * E;
-  if constexpr (E >= 256) {
-#pragma unroll
-    for (int q = 0; q < QE; ++q) out[tid + q * 256] = acc[q];
-  } else {
-    sred[tid] = (p_small < P) ? acc[0] : 0.0;
-    __syncthreads();
-    if (tid < E) {
-      double s = 0.0;
-      for (int p = 0; p < P; ++p) s += sred[tid + p * E];
-      out[tid] = s;
-    }
+  sred[tid] = p < P ? acc : 0.0;
+  __syncthreads();
+  if (tid < E) {
+    double s = 0.0;
+    for (int q = 0; q < P; ++q) s += sred[tid + q * E];
+    partials[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * E + tid] = s;
   }
 }
 
@@ -286,6 +261,85 @@ __global__ __launch_bounds__(256) void k_gram_mfma(int64_t n, const float* __res
   for (int e = threadIdx.x; e < nb * B * B; e += 256) {
     const int q = e / (B * B);
     partials[((int64_t)(kb0 + q) * gx + rset) * (B * B) + (e - q * B * B)] = red[e];
+  }
+}
+
+// X_k^T Y for any widths up to 16 NT and both precisions on the FP64 matrix cores: the operand
+// elements of a 16-row chunk come straight from memory (16 lanes read 16 consecutive
+// columns), all requested before the first product, at addresses clamped into the
+// blocks; NB blocks X_k share the pass over Y.  Bound: the blocks' bytes.  Partials are
+// EB x EB (EB a power of two, at least both widths).  Against LDS tiles with one thread per
+// entry, [V_{j-1} V_j W]^T W of 200k rows in FP64, 8 columns: 14.4 us -> 13.5 us.
+template <typename T, int NT, int NB>
+__global__ __launch_bounds__(256) void k_gram_mx(int64_t n, const T* __restrict__ X, int ldx, int64_t sX, int nblk,
+                                                 const T* __restrict__ Y, int ldy, int bx, int by, int EB,
+                                                 double* __restrict__ partials) {
+  constexpr int B = 16 * NT;
+  __shared__ double red[NB * B * B];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kb0 = blockIdx.y * NB;
+  const int nb = (nblk - kb0) < NB ? (nblk - kb0) : NB;
+  const int g = lane >> 4, c = lane & 15;
+  v4d acc[NB][NT][NT];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int I = 0; I < NT; ++I)
+#pragma unroll
+      for (int J = 0; J < NT; ++J) acc[q][I][J] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int64_t nchunks = (n + 15) / 16;
+  for (int64_t ch = (int64_t)blockIdx.x * 4 + wave; ch < nchunks; ch += (int64_t)gridDim.x * 4) {
+    const int64_t r0 = ch * 16;
+    T ys[4][NT], xs[4][NB][NT];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int64_t row = min(r0 + 4 * m + g, n - 1);
+#pragma unroll
+      for (int J = 0; J < NT; ++J) ys[m][J] = Y[row * ldy + min(16 * J + c, by - 1)];
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int I = 0; I < NT; ++I)
+          xs[m][q][I] = X[(int64_t)(kb0 + min(q, nb - 1)) * sX + row * ldx + min(16 * I + c, bx - 1)];
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const bool rok = r0 + 4 * m + g < n;
+      double yb[NT];
+#pragma unroll
+      for (int J = 0; J < NT; ++J) yb[J] = (rok && 16 * J + c < by) ? (double)ys[m][J] : 0.0;
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int I = 0; I < NT; ++I) {
+          const double xa = (rok && q < nb && 16 * I + c < bx) ? (double)xs[m][q][I] : 0.0;
+#pragma unroll
+          for (int J = 0; J < NT; ++J)
+            acc[q][I][J] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, yb[J], acc[q][I][J], 0, 0, 0);
+        }
+    }
+  }
+  for (int w = 0; w < 4; ++w) {  // the four waves in a fixed order
+    if (wave == w) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int I = 0; I < NT; ++I)
+#pragma unroll
+          for (int J = 0; J < NT; ++J)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int idx = q * B * B + (16 * I + 4 * v + g) * B + 16 * J + c;
+              red[idx] = (w == 0 ? 0.0 : red[idx]) + acc[q][I][J][v];
+            }
+    }
+    __syncthreads();
+  }
+  const int E = EB * EB;
+  for (int e = threadIdx.x; e < nb * E; e += 256) {
+    const int q = e / E, i = (e - q * E) / EB, j = e % EB;
+    partials[((int64_t)(kb0 + q) * gridDim.x + blockIdx.x) * E + (e - q * E)] =
+        i < B && j < B ? red[q * B * B + i * B + j] : 0.0;
   }
 }
 
@@ -590,6 +644,184 @@ __global__ __launch_bounds__(256) void k_update_mfma32(int64_t n, const float* X
   P[i * 32 + 16 + j] = red[1][threadIdx.x];
   P[(16 + j) * 32 + i] = red[1][threadIdx.x];
   P[(16 + i) * 32 + 16 + j] = red[2][threadIdx.x];
+}
+
+// The same product for every other width b <= 64 and both precisions: a wave takes 16-row
+// chunks, the 16 x (4 VW) A operand of one round is one VW-wide load per lane (row l % 16, columns
+// VW (l / 16) ..; the round's step s sums over the columns {VW g + s : g}), NT 16-column
+// output tiles, C lane-ordered in LDS as VW-wide vectors.  Columns past b load as zeros and are
+// not stored, so a ragged width costs matrix-core slots but no extra bytes: the kernel is
+// bound by its HBM traffic (X_k and Out once each).  The rows a lane holds of the result
+// (FP32: 4 g + v, FP64: 4 v + g) are again the operands of the Gram.  Against the form with a row
+// of B values per thread and C broadcast from LDS: FP32, 30 columns, 3 blocks of 100k rows
+// 50.8 us -> 19.9 us with the Gram; FP64, 8 columns, 200k rows 20.2 us -> 13.6 us.
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  typedef v4f acc;
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int v) { return 4 * g + v; }
+};
+template <>
+struct Mfma<double> {
+  typedef v4d acc;
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int v) { return 4 * v + g; }
+};
+
+template <typename T, int VW>
+struct __align__(sizeof(T) * VW) LaneVec {
+  T v[VW];
+};
+
+// rounds of one block and LDS bytes of its coefficients
+constexpr int mx_rounds(int b, int vw) { return (b + 4 * vw - 1) / (4 * vw); }
+constexpr size_t mx_block_bytes(int b, int vw, int es) {
+  return (size_t)mx_rounds(b, vw) * ((b + 15) / 16) * 64 * vw * es;
+}
+
+template <typename T, int VW, int NT, bool GRAM>
+__global__ __launch_bounds__(256) void k_update_mx(int64_t n, int b, const T* X, int64_t sX, int nblk,
+                                                   const double* __restrict__ C, const T* Yin, double alpha,
+                                                   const T* __restrict__ wv, double beta, T* Out, int EB,
+                                                   double* __restrict__ partials, const double* __restrict__ skip,
+                                                   const double* __restrict__ skip_gram) {
+  if (skip && *skip != 0.0) return;  // identity update the caller elides
+  typedef LaneVec<T, VW> V;
+  typedef typename Mfma<T>::acc acc_t;
+  extern __shared__ __align__(16) unsigned char smem[];
+  V* sC = reinterpret_cast<V*>(smem);  // [block][round][tile][lane]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int KR = mx_rounds(b, VW), R = nblk * KR;
+  for (int e = threadIdx.x; e < R * NT * 64; e += 256) {
+    const int l = e & 63, t = (e >> 6) % NT, i = (e >> 6) / NT, k = i / KR, q = i - k * KR;
+    const int col = 16 * t + (l & 15);
+    V w;
+#pragma unroll
+    for (int s = 0; s < VW; ++s) {
+      const int r = 4 * VW * q + VW * (l >> 4) + s;
+      w.v[s] = r < b && col < b ? (T)C[((int64_t)k * b + r) * b + col] : T(0);
+    }
+    sC[e] = w;
+  }
+  __syncthreads();
+  const bool gram = GRAM && !(skip_gram && *skip_gram != 0.0);
+  const T tb = (T)beta, ta = (T)alpha;
+  constexpr int NP = NT * (NT + 1) / 2;  // tiles of the Gram's upper triangle
+  v4d gacc[GRAM ? NP : 1];
+  if constexpr (GRAM) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) gacc[p] = v4d{0.0, 0.0, 0.0, 0.0};
+  }
+  const int64_t nchunks = (n + 15) / 16;
+  for (int64_t ch = (int64_t)blockIdx.x * 4 + wave; ch < nchunks; ch += (int64_t)gridDim.x * 4) {
+    const int64_t r0 = ch * 16;
+    const T* xa = X + (r0 + c) * b + VW * g;
+    const bool rok = r0 + c < n;
+    acc_t d[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) d[t] = acc_t{0, 0, 0, 0};
+    constexpr int U = 4;  // rounds in flight
+    int k = 0, q = 0;     // block and round of the next load
+    for (int i0 = 0; i0 < R; i0 += U) {
+      V x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool ok = rok && i0 + u < R && 4 * VW * q + VW * g < b;
+        if (ok) {
+          x[u] = *reinterpret_cast<const V*>(xa + (int64_t)k * sX + 4 * VW * q);
+        } else {
+#pragma unroll
+          for (int s = 0; s < VW; ++s) x[u].v[s] = T(0);
+        }
+        if (++q == KR) {
+          q = 0;
+          ++k;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + u >= R) break;
+        const V* w = sC + (int64_t)(i0 + u) * NT * 64 + lane;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const V wt = w[t * 64];
+#pragma unroll
+          for (int s = 0; s < VW; ++s) d[t] = Mfma<T>::mul(x[u].v[s], wt.v[s], d[t]);
+        }
+      }
+    }
+    T o[NT][4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = r0 + Mfma<T>::row(g, v);
+      const bool ok = row < n;
+      const T wq = Yin && ok ? (wv ? wv[row] : ta) : T(0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int col = 16 * t + c;
+        o[t][v] = T(0);
+        if (ok && col < b) {
+          o[t][v] = tb * d[t][v];
+          if (Yin) o[t][v] += wq * Yin[row * b + col];
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = r0 + Mfma<T>::row(g, v);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (row < n && 16 * t + c < b) Out[row * b + 16 * t + c] = o[t][v];
+    }
+    if constexpr (GRAM) {
+      if (gram) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          int p = 0;
+#pragma unroll
+          for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = i; j < NT; ++j, ++p)
+              gacc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)o[i][v], (double)o[j][v], gacc[p], 0, 0, 0);
+        }
+      }
+    }
+  }
+  if constexpr (GRAM) {
+    if (!gram) return;  // uniform over the workgroup
+    __shared__ double red[256];
+    double* P = partials + (int64_t)blockIdx.x * EB * EB;
+    int p = 0;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = i; j < NT; ++j, ++p) {
+        for (int w = 0; w < 4; ++w) {
+          if (wave == w) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int idx = (4 * v + g) * 16 + c;  // FP64 16x16x4 output layout
+              red[idx] = (w == 0 ? 0.0 : red[idx]) + gacc[p][v];
+            }
+          }
+          __syncthreads();
+        }
+        const int a = 16 * i + (threadIdx.x >> 4), e = 16 * j + (threadIdx.x & 15);
+        if (a < EB && e < EB) {
+          const double v = red[threadIdx.x];
+          P[a * EB + e] = v;
+          if (i != j) P[e * EB + a] = v;
+        }
+        __syncthreads();
+      }
+  }
 }
 
 template <typename T, int B>
@@ -1450,6 +1682,19 @@ int fin_grid(int E) {
   return (E + EB - 1) / EB;
 }
 
+// blocks X_k that share a pass over Y: as many as the accumulators leave room for
+template <typename T, int B>
+void gram_mx(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int nblk, const T* Y, int ldy, int bx, int by,
+             int parts) {
+  constexpr int NT = B <= 16 ? 1 : B / 16, NB = NT == 1 ? 3 : (NT == 2 ? 2 : 1);
+  if (nblk == 1)
+    hipLaunchKernelGGL((k_gram_mx<T, NT, 1>), dim3(parts, 1), dim3(256), 0, ctx->stream, n, X, ldx, sX, nblk, Y, ldy,
+                       bx, by, B, ctx->partials.as<double>());
+  else
+    hipLaunchKernelGGL((k_gram_mx<T, NT, NB>), dim3(parts, (nblk + NB - 1) / NB), dim3(256), 0, ctx->stream, n, X,
+                       ldx, sX, nblk, Y, ldy, bx, by, B, ctx->partials.as<double>());
+}
+
 template <int B>
 wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64_t sX, int nblk, const void* Y,
                  int ldy, int bx, int by, double* out, const double* skip = nullptr) {
@@ -1513,25 +1758,123 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
   int64_t cap = (int64_t)(1 << 22) / ((int64_t)E * nblk);
   if (cap < 32) cap = 32;
   if (cap > 512) cap = 512;
-  int parts = (int)(ntiles < cap ? ntiles : cap);
-  if (parts < 1) parts = 1;
-  WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
-  dim3 grid(parts, nblk);
-  hipLaunchKernelGGL(k_gram_partial<B>, grid, dim3(256), 0, ctx->stream, n,
-                     isf ? (const float*)X : nullptr, isf ? nullptr : (const double*)X, ldx, sX,
-                     isf ? (const float*)Y : nullptr, isf ? nullptr : (const double*)Y, ldy, bx, by,
-                     ctx->partials.as<double>());
-  WL_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,
-                     ctx->partials.as<double>(), parts, B, bx, by, out, nullptr);
-  WL_HIP(hipGetLastError());
-  return WL_OK;
+  if constexpr (B >= 8) {
+    // a wave per 16-row chunk up to 256 workgroups, then four chunks per wave (5000 rows of 5:
+    // 9.0 us with four from the start, 5.5 us so)
+    int64_t parts = std::min(cap, std::max((n + 255) / 256, std::min<int64_t>((n + 63) / 64, 256)));
+    if (parts > 8) parts = parts / 8 * 8;
+    if (parts < 1) parts = 1;
+    WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
+    if (isf)
+      gram_mx<float, B>(ctx, n, (const float*)X, ldx, sX, nblk, (const float*)Y, ldy, bx, by, (int)parts);
+    else
+      gram_mx<double, B>(ctx, n, (const double*)X, ldx, sX, nblk, (const double*)Y, ldy, bx, by, (int)parts);
+    WL_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,
+                       ctx->partials.as<double>(), (int)parts, B, bx, by, out, skip);
+    WL_HIP(hipGetLastError());
+    return WL_OK;
+  } else {
+    int parts = (int)(ntiles < cap ? ntiles : cap);
+    if (parts < 1) parts = 1;
+    WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
+    dim3 grid(parts, nblk);
+    hipLaunchKernelGGL(k_gram_partial<B>, grid, dim3(256), 0, ctx->stream, n,
+                       isf ? (const float*)X : nullptr, isf ? nullptr : (const double*)X, ldx, sX,
+                       isf ? (const float*)Y : nullptr, isf ? nullptr : (const double*)Y, ldy, bx, by,
+                       ctx->partials.as<double>());
+    WL_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,
+                       ctx->partials.as<double>(), parts, B, bx, by, out, nullptr);
+    WL_HIP(hipGetLastError());
+    return WL_OK;
+  }
 }
 
 int pick_B(int b) {
   int B = 1;
   while (B < b) B <<= 1;
   return B;
+}
+
+// k_update_mx for blocks of b columns (rows of b values): *done = false where it does not
+// apply.  Combinations longer than the LDS holds run as chained launches that accumulate
+// into Out; where Out is one of the X_k they must fit one launch (up to 128 KiB instead of the
+// 64 KiB that keep two workgroups on a CU).
+template <typename T, int VW, int NT>
+wl_status update_mx(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C, const T* Yin,
+                    double alpha, const T* wv, double beta, T* Out, double* gram_out, const double* skip,
+                    const double* skip_gram, bool* done) {
+  const size_t bytes = mx_block_bytes(b, VW, sizeof(T));
+  const uintptr_t xo = reinterpret_cast<uintptr_t>(X), oo = reinterpret_cast<uintptr_t>(Out);
+  const bool alias = nblk > 0 && oo >= xo && oo < xo + ((uintptr_t)(nblk - 1) * sX + (uintptr_t)n * b) * sizeof(T);
+  int kmax = (int)(65536 / bytes);
+  if (nblk > kmax && (alias || kmax < 1)) {
+    kmax = (int)(131072 / bytes);
+    if (nblk > kmax && alias) return WL_OK;
+  }
+  *done = true;
+  const int64_t nchunks = (n + 15) / 16;
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(gram_out ? 512 : 1024, (nchunks + 3) / 4));
+  int EB = 1;
+  while (EB < b) EB <<= 1;
+  if (gram_out) WL_TRY(ctx->partials.ensure((size_t)grid * EB * EB * sizeof(double)));
+  int k0 = 0;
+  do {
+    const int kb = std::min(kmax, nblk - k0);
+    const bool first = k0 == 0, last = k0 + kb == nblk;
+    const T* Xk = X + (int64_t)k0 * sX;
+    const double* Ck = C + (int64_t)k0 * b * b;
+    const T* Yk = first ? Yin : Out;
+    const double ak = first ? alpha : 1.0;
+    const T* wk = first ? wv : nullptr;
+    if (last && gram_out)
+      hipLaunchKernelGGL((k_update_mx<T, VW, NT, true>), dim3(grid), dim3(256), kb * bytes, ctx->stream, n, b, Xk, sX,
+                         kb, Ck, Yk, ak, wk, beta, Out, EB, ctx->partials.as<double>(), skip, skip_gram);
+    else
+      hipLaunchKernelGGL((k_update_mx<T, VW, NT, false>), dim3(grid), dim3(256), kb * bytes, ctx->stream, n, b, Xk,
+                         sX, kb, Ck, Yk, ak, wk, beta, Out, EB, nullptr, skip, nullptr);
+    WL_HIP(hipGetLastError());
+    k0 += kb;
+  } while (k0 < nblk);
+  if (gram_out) {
+    hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(EB * EB), 1), dim3(256), 0, ctx->stream,
+                       ctx->partials.as<double>(), grid, EB, b, b, gram_out, skip_gram);
+    WL_HIP(hipGetLastError());
+  }
+  return WL_OK;
+}
+
+template <typename T, int VW>
+wl_status update_mx_nt(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C, const T* Yin,
+                       double alpha, const T* wv, double beta, T* Out, double* gram_out, const double* skip,
+                       const double* skip_gram, bool* done) {
+  if (b <= 16)
+    return update_mx<T, VW, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+  if (b <= 32)
+    return update_mx<T, VW, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+  if (b <= 48)
+    return update_mx<T, VW, 3>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+  return update_mx<T, VW, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+}
+
+// The widest loads that the width and the alignment of the blocks X_k allow (and that give
+// every lane of a round columns: 8 FP32 columns are four 8-byte loads, not two of 16).
+template <typename T>
+wl_status update_mx_any(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C,
+                        const T* Yin, double alpha, const T* wv, double beta, T* Out, double* gram_out,
+                        const double* skip, const double* skip_gram, bool* done) {
+  *done = false;
+  if (b < 5 || b > 64 || (skip && gram_out)) return WL_OK;
+  const uintptr_t xo = reinterpret_cast<uintptr_t>(X);
+  auto fits = [&](int vw) { return b % vw == 0 && sX % vw == 0 && xo % (vw * sizeof(T)) == 0; };
+  if constexpr (sizeof(T) == 4) {
+    if (b > 8 && fits(4))
+      return update_mx_nt<T, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+  }
+  if (fits(2))
+    return update_mx_nt<T, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+  return update_mx_nt<T, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
 }
 
 template <typename T, int B>
@@ -1604,7 +1947,14 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
       return WL_OK;
     }
   }
-  if constexpr (sizeof(T) == 4 && B >= 4) {
+  if constexpr (B >= 8) {
+    if (bx == by && ldx == bx && ldy == by) {
+      bool done = false;
+      WL_TRY(update_mx_any<T>(ctx, n, bx, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, &done));
+      if (done) return WL_OK;
+    }
+  }
+  if constexpr (sizeof(T) == 4 && B == 4) {
     const bool al = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Out) |
                       reinterpret_cast<uintptr_t>(Yin)) & 15u) == 0 && (sX % 4) == 0;
     if (bx == B && by == B && ldx == B && ldy == B && al) {

@@ -22,6 +22,8 @@
 //     wave, LDS across the four waves), so hub rows of heavy-tailed graphs do not
 //     serialise a single group.  Those workgroups come first in the grid;
 //   * blocks wider than one tile are processed as column tiles (grid y).
+#include <type_traits>
+
 #include "wl_internal.h"
 
 namespace {
@@ -134,10 +136,11 @@ __device__ __forceinline__ void c_term(int64_t r, int ld, int b, int col, int cl
   const T* z2 = ep.Z2 + r * (int64_t)ld;
   const int kw = ep.ctab ? ep.cgw : b;                    // rows of C that meet this column
   if (ep.ctab) z2 += (col / ep.cgw) * ep.cgw;             // the operator's own segment
-  constexpr int ZV = 16 / (int)sizeof(T);                 // values per 16-byte load
   int k = 0;
-  if ((reinterpret_cast<uintptr_t>(z2) & 15u) == 0) {
-    // the segment in 16-byte loads (the lanes of one row read the same lines)
+  // the segment in wide loads (the lanes of one row read the same lines): 16 bytes, or 8
+  // where an even width leaves rows 8-byte aligned only
+  auto wide = [&](auto zv) {
+    constexpr int ZV = decltype(zv)::value;
     for (; k + ZV <= kw; k += ZV) {
       const Frag<T, ZV> zf = ldf<T, ZV>(z2 + k);
 #pragma unroll
@@ -145,6 +148,11 @@ __device__ __forceinline__ void c_term(int64_t r, int ld, int b, int col, int cl
 #pragma unroll
         for (int i = 0; i < VW; ++i) y[i] -= zf.v[u] * sC[(k + u) * TILE + cl + i];
     }
+  };
+  if constexpr (sizeof(T) == 4 && VW == 2) {
+    if ((reinterpret_cast<uintptr_t>(z2) & 7u) == 0) wide(std::integral_constant<int, 2>());
+  } else {
+    if ((reinterpret_cast<uintptr_t>(z2) & 15u) == 0) wide(std::integral_constant<int, 16 / (int)sizeof(T)>());
   }
   for (; k < kw; ++k) {
     const T zk = z2[k];
