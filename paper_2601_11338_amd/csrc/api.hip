@@ -218,6 +218,11 @@ wl_status wl_ctx_create(int32_t device, void* stream, wl_ctx** out) {
   c->stream = static_cast<hipStream_t>(stream);
   const char* tr = std::getenv("WL_TRACE");
   if (tr && tr[0] && std::strcmp(tr, "0") != 0) c->trace = c->profiling = true;
+  void* flag = nullptr;
+  if (hipHostMalloc(&flag, 64, hipHostMallocDefault) == hipSuccess)
+    c->h_flag = static_cast<int*>(flag);
+  else
+    (void)hipGetLastError();  // small graphs then take the general path
   *out = c;
   return WL_OK;
 }
@@ -313,6 +318,7 @@ void ctx_release(wl_ctx* ctx) {
     ctx->scratch.release();
     ctx->check_count.release();
   }
+  if (ctx->h_flag) (void)hipHostFree(ctx->h_flag);
   delete ctx;
 }
 
@@ -673,6 +679,36 @@ wl_status apply_lanczos_op(wl_graph* g, const LanczosOp<T>& L, const T* V, T* W,
   return WL_OK;
 }
 
+// Host copies of the projected matrix that a Lanczos run left in S; waits for it.
+wl_status read_projection(wl_ctx* ctx, int b, int K, const double* S, std::vector<double>& hA,
+                          std::vector<double>& hB, std::vector<double>& hR0, int* K_eff) {
+  SmallLayout Ly{b, K, (size_t)b * b};
+  hA.assign((size_t)K * b * b, 0.0);
+  hB.assign((size_t)K * b * b, 0.0);
+  hR0.assign((size_t)b * b, 0.0);
+  WL_HIP(hipMemcpyAsync(hA.data(), S + Ly.A(0), hA.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
+  WL_HIP(hipMemcpyAsync(hB.data(), S + Ly.B(0), hB.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
+  WL_HIP(hipMemcpyAsync(hR0.data(), S + Ly.R0(), hR0.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
+  WL_HIP(hipStreamSynchronize(ctx->stream));
+  // effective dimension: stop after the first block whose coupling vanished entirely
+  int Ke = K;
+  for (int j = 0; j + 1 < K; ++j) {
+    double s = 0.0;
+    for (int e = 0; e < b * b; ++e) s += hB[(size_t)j * b * b + e] * hB[(size_t)j * b * b + e];
+    if (s == 0.0) {
+      Ke = j + 1;
+      break;
+    }
+  }
+  *K_eff = Ke;
+  for (double v : hA)
+    if (!is_finite(v)) {
+      wl_set_error("block Lanczos produced non-finite coefficients");
+      return WL_ENUMERIC;
+    }
+  return WL_OK;
+}
+
 // Runs K block Lanczos steps from X (n x b).  basis must hold (K+1) blocks, Wb one
 // block.  On return the host arrays hold A_j (K blocks), B_j (K blocks; B_{K-1}
 // is the residual coupling), R0 (X = V_0 R0).
@@ -738,9 +774,15 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
                                    S + Ly.Skip(), nullptr));
     }
   }
+  const bool one_launch = !ring && reorth > 1 && small_orth_ok(g, prec_of<T>(), b, K);
   for (int j = 0; j < K && (ring || reorth > 1); ++j) {
     T* Vj = slot(j);
     const T* Vp = j > 0 ? slot(j - 1) : nullptr;
+    if (one_launch) {
+      WL_TRY(apply_lanczos_op<T>(g, L, Vj, Wb, b, (const T*)nullptr, nullptr, nullptr));
+      WL_TRY(launch_small_orth<T>(g, K, j, reorth >= 3 ? -1 : 0, basis, Wb, S));
+      continue;
+    }
     WL_TRY(apply_lanczos_op<T>(g, L, Vj, Wb, b, Vp, j > 0 ? S + Ly.B(j - 1) : nullptr, S + Ly.P()));
     // A_j = V_j^T W ; W -= V_j A_j
     WL_TRY(launch_gram<T>(ctx, n, Vj, b, 0, 1, Wb, b, S + Ly.A(j)));
@@ -769,30 +811,7 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
                        S + Ly.B(j), 1, 0, nullptr, S + Ly.Ref(), ptol));
     WL_TRY(launch_update<T>(ctx, n, Vn, b, 0, 1, S + Ly.Ri2(), nullptr, 0.0, nullptr, 1.0, Vn, b, nullptr));
   }
-  hA.assign((size_t)K * b * b, 0.0);
-  hB.assign((size_t)K * b * b, 0.0);
-  hR0.assign((size_t)b * b, 0.0);
-  WL_HIP(hipMemcpyAsync(hA.data(), S + Ly.A(0), hA.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-  WL_HIP(hipMemcpyAsync(hB.data(), S + Ly.B(0), hB.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-  WL_HIP(hipMemcpyAsync(hR0.data(), S + Ly.R0(), hR0.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-  WL_HIP(hipStreamSynchronize(ctx->stream));
-  // effective dimension: stop after the first block whose coupling vanished entirely
-  int Ke = K;
-  for (int j = 0; j + 1 < K; ++j) {
-    double s = 0.0;
-    for (int e = 0; e < b * b; ++e) s += hB[(size_t)j * b * b + e] * hB[(size_t)j * b * b + e];
-    if (s == 0.0) {
-      Ke = j + 1;
-      break;
-    }
-  }
-  *K_eff = Ke;
-  for (double v : hA)
-    if (!is_finite(v)) {
-      wl_set_error("block Lanczos produced non-finite coefficients");
-      return WL_ENUMERIC;
-    }
-  return WL_OK;
+  return read_projection(ctx, b, K, S, hA, hB, hR0, K_eff);
 }
 
 // Assemble the (K b) x (K b) block tridiagonal T.
@@ -921,6 +940,8 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
     if (wv) return launch_axpby_rows<T>(g->ctx, n, b, wv, Xw, -1.0, X, Y);
     return launch_axpby_rows<T>(g->ctx, n, b, nullptr, X, 0.0, X, Y);
   }
+  if (small_series_ok(g, prec_of<T>(), K))
+    return launch_small_series<T>(g, s, mu, ex ? ratio : 0.0, K, X, Y, b, wv, Xw);
   // step 1: P_1 = s A X ; S = X + omega_1 P_1
   {
     EpiArgs<T> ep;
@@ -1066,10 +1087,36 @@ wl_status phi_lanczos(wl_op* op, const T* X, T* Y, int b, const T* wv, const T* 
   WL_TRY(op->wbuf.ensure((size_t)n * b * sizeof(T)));
   std::vector<double> hA, hB, hR0;
   int Ke = K;
-  WL_TRY(block_lanczos<T>(g, L, X, b, K, op->d.reorth, op->basis.as<T>(), op->wbuf.as<T>(), op->small, hA, hB, hR0,
-                          &Ke));
+  const bool full = (int64_t)(K + 1) * b * 2 > n;  // block_lanczos reorthogonalises fully there
+  if (small_lanczos_ok(g, prec_of<T>(), b, K, full ? 2 : op->d.reorth)) {
+    WL_TRY(op->small.ensure(SmallLayout{b, K, (size_t)b * b}.total() * sizeof(double)));
+    WL_TRY(op->coef.ensure((size_t)K * b * b * sizeof(double)));
+    const double scale =
+        op->d.func == WL_F_RESOLVENT ? 1.0 - op->d.mu * op->d.mu * op->d.param * op->d.param : 0.0;
+    WL_TRY(launch_small_lanczos<T>(g, L.a, L.b0, L.b1, X, b, K, op->d.reorth, op->basis.as<T>(),
+                                   op->small.as<double>(), scale, op->coef.as<double>(), wv, Xw, Y));
+    if (scale > 0.0) {
+      // recombined before the flag is known: where it reads 0 the result is made again below
+      if (b > 1) WL_TRY(recombine_device<T>(g, op->basis.as<T>(), b, K, op->coef.as<double>(), wv, Xw, Y));
+      WL_HIP(hipStreamSynchronize(g->ctx->stream));
+      if (*static_cast<volatile int*>(g->ctx->h_flag) == 1) return WL_OK;
+    }
+    WL_TRY(read_projection(g->ctx, b, K, op->small.as<double>(), hA, hB, hR0, &Ke));
+  } else {
+    WL_TRY(block_lanczos<T>(g, L, X, b, K, op->d.reorth, op->basis.as<T>(), op->wbuf.as<T>(), op->small, hA, hB,
+                            hR0, &Ke));
+  }
   std::vector<double> F;
-  WL_TRY(lanczos_coefficients(op, Ke, b, hA, hB, hR0, F));
+  wl_status st = lanczos_coefficients(op, Ke, b, hA, hB, hR0, F);
+  if (st == WL_ENOTSPD && !full && op->d.reorth <= 1 && !wl_no_alloc) {
+    // On graphs of few distinct eigenvalues (hubs) the space is exhausted within a few steps and a
+    // locally reorthogonalised basis goes on with rounding noise: the projection then gains
+    // negative eigenvalues or not by the last bit of its inner products.  An orthonormal
+    // basis decides whether the operator itself is indefinite.
+    WL_TRY(block_lanczos<T>(g, L, X, b, K, 2, op->basis.as<T>(), op->wbuf.as<T>(), op->small, hA, hB, hR0, &Ke));
+    st = lanczos_coefficients(op, Ke, b, hA, hB, hR0, F);
+  }
+  WL_TRY(st);
   return recombine<T>(g, op->basis.as<T>(), b, Ke, F, op->coef, wv, Xw, Y);
 }
 

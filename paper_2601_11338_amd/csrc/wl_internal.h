@@ -142,6 +142,7 @@ struct wl_ctx {
   hipStream_t stream = nullptr;
   DevBuf partials;  // reduction partials
   DevBuf scratch;   // small device-side matrices
+  int* h_flag = nullptr;  // pinned: result flag of a small evaluation (null: not available)
   DevBuf check_count;  // counter of the output scan (allocated when checks are enabled)
   uint32_t checks = 0;  // WL_CHECK_* flags
   bool profiling = false;
@@ -477,6 +478,26 @@ void lanczos_params(const wl_op* op, double* a, double* b0, double* b1);
 wl_status lanczos_coefficients(const wl_op* op, int Ke, int b, const std::vector<double>& hA,
                                const std::vector<double>& hB, const std::vector<double>& hR0,
                                std::vector<double>& F);
+
+// ------------------------------------------------------------------ small graphs
+// One-workgroup evaluations (each with the predicate of the shapes it takes).
+// K Lanczos steps from X: basis, A_j, B_j, R0 as block_lanczos leaves them.  scale > 0: also
+// F = scale T^{-1} E_1 R0 (b > 1), or Y = V F, wv (.) Xw - V F (b = 1), valid where *ctx->h_flag reads
+// 1 once the stream is drained.
+bool small_lanczos_ok(const wl_graph* g, int prec, int b, int K, int reorth);
+template <typename T>
+wl_status launch_small_lanczos(wl_graph* g, double a, double b0, double b1, const T* X, int b, int K, int reorth,
+                               T* basis, double* S, double scale, double* F, const T* wv, const T* Xw, T* Y);
+// Step j of a fully reorthogonalised single-vector process from W = Op V_j (no three-term
+// subtraction yet): A_j, B_j and V_{j+1}; V_lo .. V_j are projected out.
+bool small_orth_ok(const wl_graph* g, int prec, int b, int K);
+template <typename T>
+wl_status launch_small_orth(wl_graph* g, int K, int j, int lo, T* basis, const T* W, double* S);
+// The series of phi_recurrence (K >= 2 steps of scale s; ratio > 0: exponential weights).
+bool small_series_ok(const wl_graph* g, int prec, int K);
+template <typename T>
+wl_status launch_small_series(wl_graph* g, double s, double mu, double ratio, int K, const T* X, T* Y, int b,
+                              const T* wv, const T* Xw);
 
 // ------------------------------------------------------------------ grouped blocks
 // ng blocks of width gb side by side in one n x (ng gb) row-major block (group q owns
