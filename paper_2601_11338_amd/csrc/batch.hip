@@ -623,13 +623,14 @@ wl_status return_probabilities(wl_batch* bt, BatchWork& wk, int b, int K, double
   const int64_t gs = Ly.total();
   if (p_hat || p_err) {
     // Nystrom trace per graph from F_g and R0_g alone (Omega = V_0 R0, Y = V F).
-    std::vector<double> hF((size_t)ng * K * b * b), hS((size_t)ng * gs);
+    std::vector<double> hF((size_t)ng * K * b * b), hR((size_t)ng * b * b);
     WL_HIP(hipMemcpyAsync(hF.data(), wk.F.p, hF.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-    WL_HIP(hipMemcpyAsync(hS.data(), wk.S.p, hS.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
+    WL_HIP(hipMemcpy2DAsync(hR.data(), (size_t)b * b * 8, wk.S.as<double>() + Ly.R0(), (size_t)gs * 8,
+                            (size_t)b * b * 8, ng, hipMemcpyDeviceToHost, ctx->stream));
     WL_HIP(hipStreamSynchronize(ctx->stream));
     for (int g = 0; g < ng; ++g) {
       const double* Fg = &hF[(size_t)g * K * b * b];
-      const double* R0 = &hS[(size_t)g * gs + Ly.R0()];
+      const double* R0 = &hR[(size_t)g * b * b];
       const int M = b, m = K * b;
       std::vector<double> H((size_t)M * M, 0.0), Gm((size_t)M * M, 0.0);
       for (int i = 0; i < M; ++i)
@@ -640,43 +641,14 @@ wl_status return_probabilities(wl_batch* bt, BatchWork& wk, int b, int K, double
           H[(size_t)i * M + jj] = s1;
           Gm[(size_t)i * M + jj] = s2;
         }
-      // leave-one-out Nystrom (same formulas as wl_estimate)
-      std::vector<double> tj(M);
-      for (int j = 0; j < M; ++j) {
-        const int mm = M - 1;
-        std::vector<double> Sm((size_t)mm * mm), lam(mm), U((size_t)mm * mm);
-        std::vector<int> map;
-        for (int a = 0; a < M; ++a)
-          if (a != j) map.push_back(a);
-        for (int a = 0; a < mm; ++a)
-          for (int c = 0; c < mm; ++c)
-            Sm[(size_t)a * mm + c] =
-                0.5 * (H[(size_t)map[a] * M + map[c]] + H[(size_t)map[c] * M + map[a]]);
-        double trPG = 0.0, hPh = 0.0;
-        if (mm > 0 && dense_syev(mm, Sm.data(), lam.data(), U.data()) == 0) {
-          double lmax = 0.0;
-          for (double v : lam) lmax = std::max(lmax, v);
-          std::vector<double> P((size_t)mm * mm, 0.0);
-          for (int k = 0; k < mm; ++k) {
-            if (!(lam[k] > 1e-10 * lmax)) continue;
-            for (int a = 0; a < mm; ++a)
-              for (int c = 0; c < mm; ++c) P[(size_t)a * mm + c] += U[(size_t)a * mm + k] * U[(size_t)c * mm + k] / lam[k];
-          }
-          for (int a = 0; a < mm; ++a)
-            for (int c = 0; c < mm; ++c) {
-              trPG += P[(size_t)a * mm + c] * Gm[(size_t)map[c] * M + map[a]];
-              hPh += H[(size_t)j * M + map[a]] * P[(size_t)a * mm + c] * H[(size_t)j * M + map[c]];
-            }
-        }
-        tj[j] = trPG + H[(size_t)j * M + j] - hPh;
+      // leave-one-out Nystrom (same formulas as wl_estimate); without its cores' spectra the
+      // plain probe mean stands
+      double tr = 0.0, te = 0.0;
+      if (xnys_trace_host(M, H, Gm, 1e-10, &tr, &te)) {
+        for (int j = 0; j < M; ++j) tr += H[(size_t)j * M + j] / M;
       }
-      double mean = 0.0;
-      for (double v : tj) mean += v;
-      mean /= M;
-      double var = 0.0;
-      for (double v : tj) var += (v - mean) * (v - mean);
-      if (p_hat) p_hat[g] = mean / (double)bt->n[g];
-      if (p_err) p_err[g] = std::sqrt(var / (M - 1)) / std::sqrt((double)M) / (double)bt->n[g];
+      if (p_hat) p_hat[g] = tr / (double)bt->n[g];
+      if (p_err) p_err[g] = te / (double)bt->n[g];
     }
   }
   return WL_OK;
