@@ -942,18 +942,26 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
   }
   if (small_series_ok(g, prec_of<T>(), K))
     return launch_small_series<T>(g, s, mu, ex ? ratio : 0.0, K, X, Y, b, wv, Xw);
-  // step 1: P_1 = s A X ; S = X + omega_1 P_1
-  {
-    EpiArgs<T> ep;
-    ep.a = s;
-    ep.Sin = X;
+  // the running sum's part of step k (two terms at a time, see series_sum_source)
+  auto sum_terms = [&](EpiArgs<T>& ep, int k) {
+    const int src = series_sum_source(k, K);
+    if (src == SS_KEEP) return false;
+    ep.Sin = src == SS_Y ? Y : src == SS_X ? X : nullptr;
     ep.Sout = Y;
     ep.s0 = 1.0;
-    ep.sc = omega(1);
-    if (K == 1) {
+    ep.sc = omega(k);
+    ep.sz = k >= 2 ? omega(k - 2) : 0.0;
+    if (k == K) {
       ep.wv = wv;
       ep.Xw = Xw;
     }
+    return true;
+  };
+  // step 1: P_1 = s A X
+  {
+    EpiArgs<T> ep;
+    ep.a = s;
+    sum_terms(ep, 1);
     WL_TRY(launch_spmm<T>(g, X, K == 1 ? nullptr : A, b, ep, sh));
   }
   const T* Pm2 = X;  // P_{k-2}
@@ -965,20 +973,12 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
     ep.Z = Pm2;
     ep.b0 = (k == 2) ? 0.0 : s * s * mu * mu;
     ep.b1 = -s * s * mu;
-    ep.Sin = Y;
-    ep.Sout = Y;
-    ep.s0 = 1.0;
-    ep.sc = omega(k);
-    const bool last = k == K;
-    if (last) {
-      ep.wv = wv;
-      ep.Xw = Xw;
-    }
+    const bool sums = sum_terms(ep, k), last = k == K;
     ep.kclass = b >= 4 ? WL_KC_RECURRENCE : WL_KC_OTHER_SPMM;
     // P_k overwrites the buffer of P_{k-2} (row r of P_{k-2} is read and row r of
     // P_k written by the same lanes); P_0 = X is never overwritten.
     T* out = (k == 2) ? spare : const_cast<T*>(Pm2);
-    if (mu == 0.0) ep.Z = nullptr;
+    if (mu == 0.0 && !sums) ep.Z = nullptr;
     WL_TRY(launch_spmm<T>(g, Pm1, last ? nullptr : out, b, ep, sh));
     Pm2 = Pm1;
     Pm1 = out;

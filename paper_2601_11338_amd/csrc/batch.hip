@@ -370,7 +370,7 @@ struct wl_batch {
   std::vector<wl_op_desc> d;
   std::vector<int> K;
   int Kmax = 0;
-  DevBuf gtab;       // [Kmax][ng][5]
+  DevBuf gtab;       // [Kmax][ng][EPI_NC]
   DevBuf gtab_none;  // all-zero-finish copy used for phi 1 (no Laplacian finish)
   DevBuf w;          // walk degrees, N floats
   std::vector<int64_t> us;
@@ -444,21 +444,23 @@ wl_status batch_phi(wl_batch* bt, BatchWork& wk, const float* X, float* Y, int b
   float* B = wk.bufB.as<float>();
   const SpmmShape sh = shape_for(g, WL_FP32, b);
   const double* tab = laplacian ? bt->gtab.as<double>() : bt->gtab_none.as<double>();
-  const int64_t tstride = (int64_t)bt->ng * 5;
+  const int64_t tstride = (int64_t)bt->ng * EPI_NC;
   {
     EpiArgs<float> ep;
     ep.xmap = bt->use_xmap ? &bt->xmap : nullptr;
     ep.gid = bt->gid.as<int32_t>();
     ep.gtab = tab;
-    ep.Sin = X;
+    ep.Sin = Y;
+    ep.Sx = X;
     ep.Sout = Y;
     ep.s0 = 1.0;
+    ep.s_share = 0.5;
     if (laplacian) {
       ep.wv = bt->w.as<float>();
       ep.Xw = X;
     }
     ep.kclass = WL_KC_RECURRENCE;
-    WL_TRY(launch_spmm<float>(g, X, A, b, ep, sh));
+    WL_TRY(launch_spmm<float>(g, X, bt->Kmax == 1 ? nullptr : A, b, ep, sh));
   }
   const float* Pm2 = X;
   float* Pm1 = A;
@@ -469,15 +471,17 @@ wl_status batch_phi(wl_batch* bt, BatchWork& wk, const float* X, float* Y, int b
     ep.gtab = tab + (int64_t)(k - 1) * tstride;
     ep.Z = Pm2;
     ep.Sin = Y;
+    ep.Sx = X;
     ep.Sout = Y;
     ep.s0 = 1.0;
+    ep.s_share = 0.5;
     if (laplacian) {
       ep.wv = bt->w.as<float>();
       ep.Xw = X;
     }
     ep.kclass = WL_KC_RECURRENCE;
     float* out = (k == 2) ? B : const_cast<float*>(Pm2);
-    WL_TRY(launch_spmm<float>(g, Pm1, out, b, ep, sh));
+    WL_TRY(launch_spmm<float>(g, Pm1, k == bt->Kmax ? nullptr : out, b, ep, sh));
     Pm2 = Pm1;
     Pm1 = out;
   }
@@ -801,23 +805,13 @@ wl_status wl_batch_create(wl_ctx* ctx, int32_t ngraphs, wl_graph* const* graphs,
   if (hipMemcpy(bt->d_us.p, bt->us.data(), bt->us.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(bt->d_gu0.p, bt->gu0.data(), bt->gu0.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
     return fail(WL_EDEVICE);
-  // coefficient tables: step k (1-based) of graph g: {a, b0, b1, sc, fin}
-  std::vector<double> tab((size_t)bt->Kmax * ngraphs * 5, 0.0), tab0;
-  for (int gi = 0; gi < ngraphs; ++gi) {
-    const double sp = bt->d[gi].param, mu = bt->d[gi].mu;
-    double omega = 1.0;
-    for (int k = 1; k <= bt->K[gi]; ++k) {
-      if (bt->d[gi].func == WL_F_EXP) omega /= k;  // c_k / s^k = 1 / k!
-      double* c = &tab[((size_t)(k - 1) * ngraphs + gi) * 5];
-      c[0] = sp;
-      c[1] = k >= 3 ? sp * sp * mu * mu : 0.0;
-      c[2] = k >= 2 ? -sp * sp * mu : 0.0;
-      c[3] = omega;
-      c[4] = k == bt->K[gi] ? 1.0 : 0.0;
-    }
-  }
+  // coefficient tables: step k (1-based) of graph g (exponential: c_k / s^k = 1 / k!)
+  std::vector<double> tab((size_t)bt->Kmax * ngraphs * EPI_NC, 0.0), tab0;
+  for (int gi = 0; gi < ngraphs; ++gi)
+    series_table(&tab[(size_t)gi * EPI_NC], (int64_t)ngraphs * EPI_NC, bt->K[gi], bt->d[gi].param, bt->d[gi].mu,
+                 bt->d[gi].func == WL_F_EXP ? 1.0 : 0.0);
   tab0 = tab;
-  for (size_t i = 4; i < tab0.size(); i += 5) tab0[i] = 0.0;
+  for (size_t i = 4; i < tab0.size(); i += EPI_NC) tab0[i] = 0.0;
   s = bt->gtab.ensure(tab.size() * 8);
   if (s == WL_OK) s = bt->gtab_none.ensure(tab.size() * 8);
   if (s != WL_OK) return fail(s);

@@ -32,16 +32,17 @@ struct wl_multi {
   std::vector<int> K;
   std::vector<wl_op_desc> desc;  // Lanczos groups: each operator's description
   std::vector<char> fin_at;  // fin_at[k]: some operator's series ends at step k
+  std::vector<double> sum_at;  // sum_at[k]: share of the operators whose running sum takes terms at step k
   DevBuf tab;      // [Kmax][nops][5] {a, b0, b1, omega, finish}
   DevBuf tab_phi;  // the same without the finish flags
   DevBuf W;        // walk degrees, n x nops
   bool w_valid = false;
   DevBuf Xrep, A, B, ones;
-  DevBuf ltab;                      // Lanczos groups: [nops][5] {a, b0, b1, 0, 0}
+  DevBuf ltab;                      // Lanczos groups: [nops][EPI_NC] {a, b0, b1, 0, ...}
   DevBuf basis, small, coef, tmpX, tmpY, tmpW;
   // walk degrees riding beside the blocks (wl_multi_apply_fdeg): one extra group of 16
   // columns whose column q < nops is operator q's vector of ones
-  DevBuf tab_pk, tab_pk_phi;  // series: [Kmax][2 nops][5], entries nops + q without finish
+  DevBuf tab_pk, tab_pk_phi;  // series: [Kmax][2 nops][EPI_NC], entries nops + q without finish
   DevBuf cmap;                // operator of each column of the packed block
   int cmap_b = 0;
   DevBuf Xpk, Ypk, Wg;
@@ -124,15 +125,19 @@ wl_status multi_apply(wl_multi* m, const T* X, int b, T* Y, bool laplacian) {
   hipLaunchKernelGGL(k_replicate<T>, dim3(grid), dim3(256), 0, ctx->stream, n, b, m->nops, X, Xr);
   WL_HIP(hipGetLastError());
   const double* tab = (laplacian ? m->tab : m->tab_phi).as<double>();
-  const int64_t ts = (int64_t)m->nops * 5;
+  const int64_t ts = (int64_t)m->nops * EPI_NC;
   const SpmmShape sh = shape_for(g, m->prec, wd);
   auto base = [&](int k) {
     EpiArgs<T> ep;
     ep.ctab = tab + (int64_t)(k - 1) * ts;
     ep.cgw = b;
-    ep.Sin = k == 1 ? Xr : Y;
-    ep.Sout = Y;
-    ep.s0 = 1.0;
+    if (m->sum_at[k] > 0.0) {  // some group's running sum takes terms at this step
+      ep.Sin = Y;
+      ep.Sx = Xr;
+      ep.Sout = Y;
+      ep.s0 = 1.0;
+      ep.s_share = m->sum_at[k];
+    }
     if (laplacian && m->fin_at[k]) {  // only steps where some group finishes read w and X
       ep.wv = m->W.as<T>();
       ep.wld = m->nops;
@@ -574,16 +579,20 @@ wl_status multi_series_fdeg(wl_multi* m, const T* X, int b, int nx, T* Y, T* W, 
   hipLaunchKernelGGL(k_pack_fdeg<T>, dim3(elem_grid(n * wd)), dim3(256), 0, ctx->stream, n, b, nx, nops, X, Xr);
   WL_HIP(hipGetLastError());
   const double* tab = (laplacian ? m->tab_pk : m->tab_pk_phi).as<double>();
-  const int64_t ts = (int64_t)2 * nops * 5;
+  const int64_t ts = (int64_t)2 * nops * EPI_NC;
   const SpmmShape sh = shape_for(g, m->prec, wd);
   auto base = [&](int k) {
     EpiArgs<T> ep;
     ep.ctab = tab + (int64_t)(k - 1) * ts;
     ep.cgw = b;
     ep.cmap = m->cmap.as<int32_t>();
-    ep.Sin = k == 1 ? Xr : Yp;
-    ep.Sout = Yp;
-    ep.s0 = 1.0;
+    if (m->sum_at[k] > 0.0) {
+      ep.Sin = Yp;
+      ep.Sx = Xr;
+      ep.Sout = Yp;
+      ep.s0 = 1.0;
+      ep.s_share = m->sum_at[k];
+    }
     if (laplacian && m->fin_at[k]) {
       ep.wv = m->W.as<T>();
       ep.wld = nops;
@@ -749,8 +758,11 @@ wl_status multi_groups_create(wl_op* op, int G, wl_multi** out) {
   m->K.assign(G, op->K);
   m->desc.assign(G, op->d);
   m->Kmax = std::max(op->K, 1);
-  std::vector<double> lt((size_t)G * 5, 0.0);
-  for (int i = 0; i < G; ++i) lanczos_params(op, &lt[i * 5], &lt[i * 5 + 1], &lt[i * 5 + 2]);
+  std::vector<double> lt((size_t)G * EPI_NC, 0.0);
+  for (int i = 0; i < G; ++i) {
+    double* c = &lt[(size_t)i * EPI_NC];
+    lanczos_params(op, c, c + 1, c + 2);
+  }
   wl_status s = m->ltab.ensure(lt.size() * 8);
   if (s == WL_OK && hipMemcpy(m->ltab.p, lt.data(), lt.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
     wl_set_error("column groups: coefficient upload failed");
@@ -837,8 +849,11 @@ wl_status wl_multi_create(wl_op* const* ops, int32_t nops, wl_multi** out) {
   wl_status s = WL_OK;
   if (method == WL_M_LANCZOS) {
     // every group's Lanczos matrix a A + (b0 + b1 D)
-    std::vector<double> lt((size_t)nops * 5, 0.0);
-    for (int i = 0; i < nops; ++i) lanczos_params(ops[i], &lt[i * 5], &lt[i * 5 + 1], &lt[i * 5 + 2]);
+    std::vector<double> lt((size_t)nops * EPI_NC, 0.0);
+    for (int i = 0; i < nops; ++i) {
+      double* c = &lt[(size_t)i * EPI_NC];
+      lanczos_params(ops[i], c, c + 1, c + 2);
+    }
     s = m->ltab.ensure(lt.size() * 8);
     if (s == WL_OK && hipMemcpy(m->ltab.p, lt.data(), lt.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
       wl_set_error("wl_multi_create: coefficient upload failed");
@@ -847,40 +862,35 @@ wl_status wl_multi_create(wl_op* const* ops, int32_t nops, wl_multi** out) {
   } else {
     m->fin_at.assign(m->Kmax + 1, 0);
     for (int i = 0; i < nops; ++i) m->fin_at[m->K[i]] = 1;
-    // step k (1-based) of operator i: a = s, b0 = s^2 mu^2 (k >= 3), b1 = -s^2 mu (k >= 2),
-    // omega_k = c_k / s^k, finish at k = K_i; all zero past K_i (the group is done)
-    std::vector<double> tab((size_t)m->Kmax * nops * 5, 0.0);
+    // step k (1-based) of operator i, all zero past K_i (the group is done)
+    std::vector<double> tab((size_t)m->Kmax * nops * EPI_NC, 0.0);
+    m->sum_at.assign(m->Kmax + 1, 0.0);
     for (int i = 0; i < nops; ++i) {
       // scaling s as for one operator: exponential s = min(beta, 1 / lambda_max), weights
       // (beta / s)^k / k!; resolvent s = alpha, weights 1
       const bool ex = ops[i]->d.func == WL_F_EXP;
       const double sp = ex && ops[i]->lam > 0.0 ? std::min(ops[i]->d.param, 1.0 / ops[i]->lam) : ops[i]->d.param;
-      const double mu = ops[i]->d.mu, ratio = ex ? ops[i]->d.param / sp : 1.0;
-      double omega = 1.0;
-      for (int k = 1; k <= m->K[i]; ++k) {
-        if (ex) omega *= ratio / k;
-        double* c = &tab[((size_t)(k - 1) * nops + i) * 5];
-        c[0] = sp;
-        c[1] = k >= 3 ? sp * sp * mu * mu : 0.0;
-        c[2] = k >= 2 ? -sp * sp * mu : 0.0;
-        c[3] = omega;
-        c[4] = k == m->K[i] ? 1.0 : 0.0;
+      series_table(&tab[(size_t)i * EPI_NC], (int64_t)nops * EPI_NC, m->K[i], sp, ops[i]->d.mu,
+                   ex ? ops[i]->d.param / sp : 0.0);
+      for (int k = 1; k <= m->Kmax; ++k) {
+        const int src = (int)tab[((size_t)(k - 1) * nops + i) * EPI_NC + 6];
+        if (src != SS_KEEP && src != SS_DONE) m->sum_at[k] += 1.0 / nops;
       }
     }
     std::vector<double> tab_phi = tab;
-    for (size_t e = 4; e < tab_phi.size(); e += 5) tab_phi[e] = 0.0;
+    for (size_t e = 4; e < tab_phi.size(); e += EPI_NC) tab_phi[e] = 0.0;
     // packed evaluation with walk degrees: entries [0, nops) as above, entries
     // [nops, 2 nops) the same operators without finish (the walk-degree columns)
-    std::vector<double> tpk((size_t)m->Kmax * 2 * nops * 5, 0.0), tpk_phi;
+    std::vector<double> tpk((size_t)m->Kmax * 2 * nops * EPI_NC, 0.0), tpk_phi;
     for (int k = 0; k < m->Kmax; ++k)
       for (int i = 0; i < nops; ++i)
-        for (int e = 0; e < 5; ++e) {
-          const double v = tab[((size_t)k * nops + i) * 5 + e];
-          tpk[((size_t)k * 2 * nops + i) * 5 + e] = v;
-          tpk[((size_t)k * 2 * nops + nops + i) * 5 + e] = e == 4 ? 0.0 : v;
+        for (int e = 0; e < EPI_NC; ++e) {
+          const double v = tab[((size_t)k * nops + i) * EPI_NC + e];
+          tpk[((size_t)k * 2 * nops + i) * EPI_NC + e] = v;
+          tpk[((size_t)k * 2 * nops + nops + i) * EPI_NC + e] = e == 4 ? 0.0 : v;
         }
     tpk_phi = tpk;
-    for (size_t e = 4; e < tpk_phi.size(); e += 5) tpk_phi[e] = 0.0;
+    for (size_t e = 4; e < tpk_phi.size(); e += EPI_NC) tpk_phi[e] = 0.0;
     s = m->tab.ensure(tab.size() * 8);
     if (s == WL_OK) s = m->tab_phi.ensure(tab.size() * 8);
     if (s == WL_OK) s = m->tab_pk.ensure(tpk.size() * 8);

@@ -198,8 +198,8 @@ constexpr int EPI_COLS = 1, EPI_NFAC = 2;
 // global loads per column and row).  fin holds the finishing operator (-1: none).
 template <typename T, int TILE>
 struct ColCoef {
-  T a[TILE], sc[TILE], z0[TILE], z1[TILE];
-  int fin[TILE];
+  T a[TILE], sc[TILE], z0[TILE], z1[TILE], sz[TILE];
+  int fin[TILE], src[TILE];
 };
 
 template <typename T, int TILE>
@@ -208,18 +208,22 @@ __device__ __forceinline__ void stage_col_coef(const EpiArgs<T>& ep, int c0, int
     const int c = c0 + j;
     const int q = c < b ? ep.cmap[c] : -1;
     if (q >= 0) {  // else a padding column: all zero
-      const double* k = ep.ctab + 5 * (int64_t)q;
+      const double* k = ep.ctab + EPI_NC * (int64_t)q;
       cc.a[j] = (T)k[0];
       cc.z0[j] = (T)k[1];
       cc.z1[j] = (T)k[2];
       cc.sc[j] = (T)k[3];
       cc.fin[j] = ep.wv != nullptr && k[4] != 0.0 ? q : -1;
+      cc.sz[j] = (T)k[5];
+      cc.src[j] = (int)k[6];
     } else {
       cc.a[j] = T(0);
       cc.z0[j] = T(0);
       cc.z1[j] = T(0);
       cc.sc[j] = T(0);
       cc.fin[j] = -1;
+      cc.sz[j] = T(0);
+      cc.src[j] = SS_KEEP;
     }
   }
 }
@@ -232,8 +236,10 @@ __device__ __forceinline__ void epilogue_cols(int64_t r, int ld, int b, int col,
   T y[VW];
 #pragma unroll
   for (int i = 0; i < VW; ++i) y[i] = cc.a[cl + i] * acc.v[i];
+  Frag<T, VW> z;
+  zero(z);
   if (ep.Z) {
-    Frag<T, VW> z = ldf<T, VW>(ep.Z + off);
+    z = ldf<T, VW>(ep.Z + off);
 #pragma unroll
     for (int i = 0; i < VW; ++i) y[i] += (cc.z0[cl + i] + cc.z1[cl + i] * deg) * z.v[i];
   }
@@ -245,23 +251,49 @@ __device__ __forceinline__ void epilogue_cols(int64_t r, int ld, int b, int col,
     for (int i = 0; i < VW; ++i) o.v[i] = y[i];
     stf<T, VW>(Y + off, o);
   }
-  if (ep.Sout) {
-    Frag<T, VW> s, xw;
-    if (ep.Sin)
-      s = ldf_nt<T, VW>(ep.Sin + off);
+  int src[VW];  // where each column's running sum comes from
+  bool any = false, from_y = false, from_x = false;
+#pragma unroll
+  for (int i = 0; i < VW; ++i) {
+    src[i] = cc.src[cl + i];
+    any |= src[i] != SS_KEEP && src[i] != SS_DONE;
+    from_y |= src[i] == SS_Y;
+    from_x |= src[i] == SS_X;
+  }
+  if (ep.Sout && any) {
+    Frag<T, VW> s, sx, xw;
+    zero(sx);
+    // columns that keep their sum beside columns that change: it is read and written back
+    bool keeps = false;
+#pragma unroll
+    for (int i = 0; i < VW; ++i) keeps |= src[i] == SS_KEEP || src[i] == SS_DONE;
+    if (from_y || keeps)
+      s = ldf_nt<T, VW>(ep.Sout + off);
     else
       zero(s);
+    if (from_x) sx = ldf_nt<T, VW>(ep.Sx + off);
     if (ep.wv) xw = ldf_nt<T, VW>(ep.Xw + off);
     const T s0 = (T)ep.s0;
 #pragma unroll
     for (int i = 0; i < VW; ++i) {
-      T v = s0 * s.v[i] + cc.sc[cl + i] * y[i];
+      if (src[i] == SS_KEEP || src[i] == SS_DONE) continue;
+      const T from = src[i] == SS_Y ? s.v[i] : src[i] == SS_X ? sx.v[i] : T(0);
+      T v = s0 * from + cc.sc[cl + i] * y[i] + cc.sz[cl + i] * z.v[i];
       const int q = cc.fin[cl + i];
       if (q >= 0) v = ep.wv[r * (int64_t)ep.wld + q] * xw.v[i] - v;
       s.v[i] = v;
     }
     stf_nt<T, VW>(ep.Sout + off, s);
   }
+}
+
+// Source and target of the running sum for a table's entry (an operator without Sout has
+// none).
+template <typename T>
+__device__ __forceinline__ void sum_source(double code, const EpiArgs<T>& ep, const T*& Sin, T*& Sout) {
+  const int src = (int)code;
+  Sin = src == SS_Y ? ep.Sin : src == SS_X ? ep.Sx : nullptr;
+  Sout = src == SS_KEEP || src == SS_DONE ? nullptr : ep.Sout;
 }
 
 template <typename T, int VW, bool MASK, int E, int TILE_>
@@ -274,31 +306,39 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
     return;
   }
   const int64_t off = r * (int64_t)ld + col;
-  double ca = ep.a, cb0 = ep.b0, cb1 = ep.b1, csc = ep.sc;
+  double ca = ep.a, cb0 = ep.b0, cb1 = ep.b1, csc = ep.sc, csz = ep.sz;
+  const T* Sin = ep.Sin;
+  T* Sout = ep.Sout;
   bool fin = ep.wv != nullptr;
   if (ep.gid) {
-    const double* c = ep.gtab + 5 * (int64_t)ep.gid[r];
+    const double* c = ep.gtab + EPI_NC * (int64_t)ep.gid[r];
     ca = c[0];
     cb0 = c[1];
     cb1 = c[2];
     csc = c[3];
     fin = fin && c[4] != 0.0;
+    csz = c[5];
+    sum_source(c[6], ep, Sin, Sout);
   }
   if (ep.ctab) {  // the VW columns of this lane lie in one operator's group
-    const double* c = ep.ctab + 5 * (col / ep.cgw);
+    const double* c = ep.ctab + EPI_NC * (col / ep.cgw);
     ca = c[0];
     cb0 = c[1];
     cb1 = c[2];
     csc = c[3];
     fin = fin && c[4] != 0.0;
+    csz = c[5];
+    sum_source(c[6], ep, Sin, Sout);
   }
   T y[VW];
   const T a = (T)ca;
 #pragma unroll
   for (int i = 0; i < VW; ++i) y[i] = a * acc.v[i];
-  if (ep.Z) {
+  Frag<T, VW> z;
+  zero(z);
+  if (ep.Z && (cb0 != 0.0 || cb1 != 0.0 || csz != 0.0)) {
     const T coef = (T)(cb0 + cb1 * (double)deg);
-    Frag<T, VW> z = ldf_m<T, VW, MASK>(ep.Z + off, true);
+    z = ldf_m<T, VW, MASK>(ep.Z + off, true);
 #pragma unroll
     for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
   }
@@ -314,15 +354,15 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
       stf<T, VW>(Y + off, o);
     }
   }
-  if (ep.Sout) {
+  if (Sout) {
     Frag<T, VW> s;
-    if (ep.Sin)
-      s = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Sin + off, true) : ldf_nt<T, VW>(ep.Sin + off);
+    if (Sin)
+      s = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(Sin + off, true) : ldf_nt<T, VW>(Sin + off);
     else
       zero(s);
-    const T s0 = (T)ep.s0, sc = (T)csc;
+    const T s0 = (T)ep.s0, sc = (T)csc, sz = (T)csz;
 #pragma unroll
-    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i];
+    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i] + sz * z.v[i];
     if (fin) {
       const T wr = ep.wld ? ep.wv[r * (int64_t)ep.wld + col / ep.cgw] : ep.wv[r];
       Frag<T, VW> xw = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Xw + off, true) : ldf_nt<T, VW>(ep.Xw + off);
@@ -335,9 +375,9 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
       for (int i = 0; i < VW; ++i) s.v[i] = xj.v[i] + jr * s.v[i];
     }
     if constexpr (MASK && VW == 1) {
-      ep.Sout[off] = s.v[0];
+      Sout[off] = s.v[0];
     } else {
-      stf_nt<T, VW>(ep.Sout + off, s);
+      stf_nt<T, VW>(Sout + off, s);
     }
   }
 }
@@ -375,8 +415,12 @@ constexpr int gather_unroll() {
   return VW == 1 && sizeof(T) == 4 ? 16 : 8;
 }
 
+// Eight waves per SIMD in FP32 (64 VGPRs; 72 to 90 are taken when left free): the gathers
+// are latency-bound, and a wave fewer costs more than the tighter registers (96 columns of
+// 1M nodes: 752 us a step at 72 VGPRs, 714 at 64; with the row streams requested ahead of
+// their use 84 VGPRs and 894 us).  FP64 blocks need twice the registers.
 template <typename T, int VW, int LPN, int G, bool MASK, int E>
-__global__ __launch_bounds__(256) void k_spmm(const int32_t* __restrict__ rowptr,
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void k_spmm(const int32_t* __restrict__ rowptr,
                                               const int32_t* __restrict__ colidx, int64_t n, int ld, int b,
                                               const T* __restrict__ X, T* Y, EpiArgs<T> ep,
                                               const int32_t* __restrict__ long_rows, int n_long,
@@ -436,8 +480,7 @@ __global__ __launch_bounds__(256) void k_spmm(const int32_t* __restrict__ rowptr
     constexpr int NSLOT = 256 / LPN;
     const int64_t r = long_rows[blockIdx.x];
     if (ep.gid) {  // whole workgroup decides together
-      const double* c = ep.gtab + 5 * (int64_t)ep.gid[r];
-      if (c[0] == 0.0 && c[3] == 0.0) return;
+      if (ep.gtab[EPI_NC * (int64_t)ep.gid[r] + 6] == SS_DONE) return;
     }
     const int slot = threadIdx.x / LPN;
     const int s = rowptr[r], e = rowptr[r + 1];
@@ -472,8 +515,7 @@ __global__ __launch_bounds__(256) void k_spmm(const int32_t* __restrict__ rowptr
   const int s = rowptr[r], e = rowptr[r + 1];
   if (e - s > long_thr) return;
   if (ep.gid) {  // graph finished its recurrence: nothing to gather or write
-    const double* c = ep.gtab + 5 * (int64_t)ep.gid[r];
-    if (c[0] == 0.0 && c[3] == 0.0) return;
+    if (ep.gtab[EPI_NC * (int64_t)ep.gid[r] + 6] == SS_DONE) return;
   }
   const int slot = (lane % G) / LPN;
   Frag<T, VW> acc;
@@ -542,8 +584,8 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
   if (ks) {
     // algorithmic bytes: CSR once, the gathered block once (compulsory), every row stream once
     const double s = sizeof(T), nb = (double)g->n * b;
-    int streams = 1 + (Y ? 1 : 0) + (ep.Z ? 1 : 0) + (ep.C ? 1 : 0) + (ep.Sin ? 1 : 0) + (ep.Sout ? 1 : 0) +
-                  (ep.Xw ? 1 : 0) + (ep.jx ? 1 : 0);
+    const double streams = 1 + (Y ? 1 : 0) + (ep.Z ? 1 : 0) + (ep.C ? 1 : 0) +
+                           ep.s_share * ((ep.Sin ? 1 : 0) + (ep.Sout ? 1 : 0)) + (ep.Xw ? 1 : 0) + (ep.jx ? 1 : 0);
     WL_TRY(kstats_end(ctx, ks, 4.0 * g->nnz + 4.0 * (g->n + 1) + s * nb * streams + (ep.wv ? s * g->n : 0.0) +
                                    (ep.jw ? s * g->n : 0.0)));
   }
@@ -577,7 +619,7 @@ bool aligned_to(const EpiArgs<T>& ep, const T* X, const T* Y, uintptr_t bytes) {
   const uintptr_t all = reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) |
                         reinterpret_cast<uintptr_t>(ep.Z) | reinterpret_cast<uintptr_t>(ep.Sin) |
                         reinterpret_cast<uintptr_t>(ep.Sout) | reinterpret_cast<uintptr_t>(ep.Xw) |
-                        reinterpret_cast<uintptr_t>(ep.jx);
+                        reinterpret_cast<uintptr_t>(ep.jx) | reinterpret_cast<uintptr_t>(ep.Sx);
   return (all & (bytes - 1)) == 0;
 }
 

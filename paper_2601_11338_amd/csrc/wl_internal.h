@@ -201,10 +201,49 @@ struct wl_op {
 void rk_cache_destroy(wl_op* op);
 
 // ------------------------------------------------------------------ launch interfaces
+// Running sum of a truncated series S = sum_k omega_k P_k, k = 0..K, P_0 = X.  A step
+// that adds every P_k as it is formed reads and writes S each time; the recurrence reads
+// P_{k-2} anyway, so the sum is taken two terms at a time: steps K, K-1, K-4, K-5, ...
+// add omega_k P_k + omega_{k-2} P_{k-2} and the others leave S alone.  That halves the
+// traffic of S, which where the rows stream from memory is what a step costs beyond its
+// gather: five exponentials beside their walk degrees (96 FP32 columns, 1M nodes, 10M
+// nonzeros) 641 us without the sum and 777 us with it, 730 us a step when every step had
+// it; 64 graphs of 50k nodes at 8 columns, 750 products of a diffusion, 56.0 -> 52.1 ms in all.
+// X itself enters as the first source (SS_X) or as the P_{k-2} of step 2.
+enum SeriesSum { SS_DONE = 0, SS_Y = 1, SS_X = 2, SS_ZERO = 3, SS_KEEP = 4 };
+constexpr int EPI_NC = 8;  // doubles per operator and step in gtab / ctab
+// Source of the sum at step k = 1..K (SS_KEEP: this step leaves it alone).
+inline int series_sum_source(int k, int K) {
+  const int r = (K - k) % 4;
+  if (r > 1) return SS_KEEP;
+  if (r == 1 ? k >= 4 : k >= 2) return SS_Y;  // an earlier step wrote the sum
+  return (k == 2 || (k == 1 && r == 1)) ? SS_ZERO : SS_X;
+}
+// Rows k = 1..K of a coefficient table (row stride in doubles): a = s, b0 = s^2 mu^2 from
+// k = 3, b1 = -s^2 mu from k = 2, omega_k = ratio^k / k! (ratio 0: 1), finish at k = K.
+// K = 0 (phi = I): one row that copies X into the sum.
+inline void series_table(double* c, int64_t stride, int K, double s, double mu, double ratio) {
+  if (K == 0) c[6] = SS_X;
+  double om2 = 0.0, om1 = 1.0;  // omega_{k-2}, omega_{k-1}
+  for (int k = 1; k <= K; ++k, c += stride) {
+    const double om = ratio > 0.0 ? om1 * (ratio / k) : 1.0;
+    const int src = series_sum_source(k, K);
+    c[0] = s;
+    c[1] = k >= 3 ? s * s * mu * mu : 0.0;
+    c[2] = k >= 2 ? -s * s * mu : 0.0;
+    c[3] = src == SS_KEEP ? 0.0 : om;
+    c[4] = k == K ? 1.0 : 0.0;
+    c[5] = src == SS_KEEP ? 0.0 : om2;
+    c[6] = src;
+    om2 = om1;
+    om1 = om;
+  }
+}
+
 // SpMM epilogue (per row r, on the b columns of the current tile):
 //   y        = a * (A X)[r] + (b0 + b1 * d_r) * Z[r] - Z2[r, :] * C    (terms optional)
 //   Y[r]     = y                                                       (if Y)
-//   Sout[r]  = s0 * Sin[r] + sc * y                                    (if Sout; Sin optional)
+//   Sout[r]  = s0 * Sin[r] + sc * y + sz * Z[r]                        (if Sout; Sin optional)
 //   if wv:     Sout[r] = wv[r] * Xw[r] - Sout[r]                       (walk-Laplacian finish)
 //   if jw:     Sout[r] = jx[r] + jw[r] * Sout[r]                       (Jacobi sweep finish)
 // C is b x b row-major double on the device (transC: use C^T).
@@ -218,20 +257,23 @@ struct EpiArgs {
   int transC = 0;
   const T* Sin = nullptr;
   T* Sout = nullptr;
-  double s0 = 0.0, sc = 0.0;
+  double s0 = 0.0, sc = 0.0, sz = 0.0;
+  const T* Sx = nullptr;  // with gtab or ctab: the SS_X source of the running sum
+  double s_share = 1.0;   // share of the block whose running sum this launch reads (byte counts)
   const T* wv = nullptr;
   const T* Xw = nullptr;
   // Jacobi finish (instead of the walk-Laplacian one): Sout[r] = jx[r] + jw[r] * Sout[r]
   const T* jw = nullptr;
   const T* jx = nullptr;
   int kclass = WL_KC_OTHER_SPMM;  // timing class when profiling is on
-  // Batched graphs: row r belongs to graph gid[r]; gtab holds, per graph, the five
-  // coefficients {a, b0, b1, sc, fin} of this launch (replacing a, b0, b1, sc; fin != 0
-  // applies the walk-Laplacian finish).  Rows of graphs with a = sc = 0 are skipped.
+  // Batched graphs: row r belongs to graph gid[r]; gtab holds, per graph, the EPI_NC
+  // coefficients {a, b0, b1, sc, fin, sz, S source} of this launch (replacing a, b0, b1,
+  // sc, sz; fin != 0 applies the walk-Laplacian finish; the source is a SeriesSum).  Rows
+  // of graphs whose source is SS_DONE are skipped.
   const int32_t* gid = nullptr;
   const double* gtab = nullptr;
-  // Several operators side by side: column c belongs to operator c / cgw, whose five
-  // coefficients of this launch are ctab[5 (c / cgw) ...]; the finish weight is then
+  // Several operators side by side: column c belongs to operator c / cgw, whose EPI_NC
+  // coefficients of this launch are ctab[EPI_NC (c / cgw) ...]; the finish weight is then
   // wv[r * wld + c / cgw] (wv holds one walk-degree column per operator).
   // With C as well, C is block diagonal: operator q's cgw x cgw block sits at
   // C + q * cgs, and Z2's row segment of that operator is what multiplies it.
@@ -239,7 +281,7 @@ struct EpiArgs {
   int cgw = 0;
   int wld = 0;
   int64_t cgs = 0;
-  // Per-column operators (with ctab): column c takes the coefficients ctab[5 cmap[c] ...]
+  // Per-column operators (with ctab): column c takes the coefficients ctab[EPI_NC cmap[c] ...]
   // and the finish weight wv[r * wld + cmap[c]] instead of those of c / cgw (cmap[c] < 0:
   // padding, all coefficients zero).  C stays block diagonal in cgw-wide groups.  This
   // lets one group of cgw columns hold single columns of different operators (their
