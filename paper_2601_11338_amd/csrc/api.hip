@@ -725,14 +725,22 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
   double* S = small.as<double>();
   const double tol = defl_tol<T>();
   const double ptol = post_tol<T>();
+  GramParts gp;  // the last update's Gram, where its sum is left to the factorisation
+  auto update = [&](const T* Xk, int nblk, const double* C, const T* Yin, double alpha, double beta, T* Out,
+                    double* gram, const double* skip = nullptr, const double* skip_gram = nullptr,
+                    const ProjArgs& pj = ProjArgs()) {
+    gp = GramParts();
+    return launch_update_skip<T>(ctx, n, Xk, b, nblk == 1 ? 0 : blk, nblk, C, Yin, alpha, nullptr, beta, Out, b, gram, skip,
+                                 skip_gram, pj, &gp);
+  };
   // V_0 R0 = X by CholQR2
   WL_TRY(launch_gram<T>(ctx, n, X, b, 0, 1, X, b, S + Ly.G()));
   WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, S + Ly.R1(), S + Ly.Ri1(), nullptr, nullptr, 1, 0,
                      S + Ly.Ref()));
-  WL_TRY(launch_update<T>(ctx, n, X, b, 0, 1, S + Ly.Ri1(), nullptr, 0.0, nullptr, 1.0, basis, b, S + Ly.G()));
+  WL_TRY(update(X, 1, S + Ly.Ri1(), nullptr, 0.0, 1.0, basis, S + Ly.G()));
   WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, S + Ly.R2(), S + Ly.Ri2(), S + Ly.R1(),
-                     S + Ly.R0(), 1, 0, nullptr, S + Ly.Ref(), ptol));
-  WL_TRY(launch_update<T>(ctx, n, basis, b, 0, 1, S + Ly.Ri2(), nullptr, 0.0, nullptr, 1.0, basis, b, nullptr));
+                     S + Ly.R0(), 1, 0, nullptr, S + Ly.Ref(), ptol, nullptr, 0.0, nullptr, -1, nullptr, &gp));
+  WL_TRY(update(basis, 1, S + Ly.Ri2(), nullptr, 0.0, 1.0, basis, nullptr));
   if (ring) reorth = 0;
   // A basis that will span more than half of the space loses orthogonality under local
   // reorthogonalisation as its Ritz values converge (at exhaustion the projected matrix
@@ -755,23 +763,20 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
       const int nbv = j > 0 && reorth >= 1 ? 2 : 1;
       const T* Vlo = nbv == 2 ? Vp : Vj;
       WL_TRY(launch_gram<T>(ctx, n, Vlo, b, blk, nbv + 1, Vn, b, S + Ly.P()));
-      WL_TRY(launch_lanczos_proj(ctx, b, nbv, S + Ly.P(), S + Ly.A(j), S + Ly.Cc(), S + Ly.Ref()));
-      WL_TRY(launch_update<T>(ctx, n, Vlo, b, blk, nbv + 1, S + Ly.Cc(), nullptr, 0.0, nullptr, 1.0, Vn, b,
-                              S + Ly.G()));
+      const ProjArgs pj{nbv, S + Ly.P(), S + Ly.A(j), S + Ly.Ref()};
+      WL_TRY(update(Vlo, nbv + 1, S + Ly.Cc(), nullptr, 0.0, 1.0, Vn, S + Ly.G(), nullptr, nullptr, pj));
       WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, nullptr, S + Ly.Ri1(), nullptr, S + Ly.R1(), 1, 0,
-                         nullptr, S + Ly.Ref(), ptol, S + Ly.Skip(), skip_ratio<T>()));
+                         nullptr, S + Ly.Ref(), ptol, S + Ly.Skip(), skip_ratio<T>(), nullptr, -1, nullptr, &gp));
       if (j + 1 == K) {  // residual coupling B_{K-1} (a-posteriori error estimates)
         WL_TRY(launch_dcopy(ctx, b * b, S + Ly.R1(), S + Ly.B(j)));
         break;
       }
       // the second CholQR pass runs only when the first factor was ill conditioned
       // (device flag): otherwise its Gram and update return at once and B_j = R1
-      WL_TRY(launch_update_skip<T>(ctx, n, Vn, b, 0, 1, S + Ly.Ri1(), nullptr, 0.0, nullptr, 1.0, Vn, b, S + Ly.G(),
-                                   nullptr, S + Ly.Skip()));
+      WL_TRY(update(Vn, 1, S + Ly.Ri1(), nullptr, 0.0, 1.0, Vn, S + Ly.G(), nullptr, S + Ly.Skip()));
       WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, S + Ly.R2(), S + Ly.Ri2(), S + Ly.R1(),
-                         S + Ly.B(j), 1, 0, nullptr, nullptr, 0.0, nullptr, 0.0, S + Ly.Skip()));
-      WL_TRY(launch_update_skip<T>(ctx, n, Vn, b, 0, 1, S + Ly.Ri2(), nullptr, 0.0, nullptr, 1.0, Vn, b, nullptr,
-                                   S + Ly.Skip(), nullptr));
+                         S + Ly.B(j), 1, 0, nullptr, nullptr, 0.0, nullptr, 0.0, S + Ly.Skip(), -1, nullptr, &gp));
+      WL_TRY(update(Vn, 1, S + Ly.Ri2(), nullptr, 0.0, 1.0, Vn, nullptr, S + Ly.Skip()));
     }
   }
   const bool one_launch = !ring && reorth > 1 && small_orth_ok(g, prec_of<T>(), b, K);
@@ -787,29 +792,29 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
     // A_j = V_j^T W ; W -= V_j A_j
     WL_TRY(launch_gram<T>(ctx, n, Vj, b, 0, 1, Wb, b, S + Ly.A(j)));
     const bool second = reorth >= 1;
-    WL_TRY(launch_update<T>(ctx, n, Vj, b, 0, 1, S + Ly.A(j), Wb, 1.0, nullptr, -1.0, Wb, b,
-                            second ? nullptr : S + Ly.G()));
+    WL_TRY(update(Vj, 1, S + Ly.A(j), Wb, 1.0, -1.0, Wb, second ? nullptr : S + Ly.G()));
     if (second) {
       // reorth 3: also against the block stored just before slot 0 (a locked vector)
       const int lo = reorth >= 3 ? -1 : (reorth >= 2 ? 0 : std::max(0, j - 1));
       const int nb = j - lo + 1;
       const T* Vlo = basis + (size_t)lo * blk;
       WL_TRY(launch_gram<T>(ctx, n, Vlo, b, blk, nb, Wb, b, S + Ly.P()));
-      WL_TRY(launch_update<T>(ctx, n, Vlo, b, blk, nb, S + Ly.P(), Wb, 1.0, nullptr, -1.0, Wb, b, S + Ly.G()));
+      WL_TRY(update(Vlo, nb, S + Ly.P(), Wb, 1.0, -1.0, Wb, S + Ly.G()));
       WL_TRY(launch_dadd(ctx, b * b, S + Ly.P() + (size_t)(nb - 1) * b * b, S + Ly.A(j)));
     }
     // W = V_{j+1} B_j by CholQR2
     WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, S + Ly.A(j), j > 0 ? S + Ly.B(j - 1) : nullptr, S + Ly.R1(),
-                       S + Ly.Ri1(), nullptr, nullptr, 1, 0, S + Ly.Ref()));
+                       S + Ly.Ri1(), nullptr, nullptr, 1, 0, S + Ly.Ref(), nullptr, 0.0, nullptr, 0.0, nullptr, -1,
+                       nullptr, &gp));
     if (j + 1 == K) {
       WL_TRY(launch_dcopy(ctx, b * b, S + Ly.R1(), S + Ly.B(j)));
       break;
     }
     T* Vn = slot(j + 1);
-    WL_TRY(launch_update<T>(ctx, n, Wb, b, 0, 1, S + Ly.Ri1(), nullptr, 0.0, nullptr, 1.0, Vn, b, S + Ly.G()));
+    WL_TRY(update(Wb, 1, S + Ly.Ri1(), nullptr, 0.0, 1.0, Vn, S + Ly.G()));
     WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, S + Ly.R2(), S + Ly.Ri2(), S + Ly.R1(),
-                       S + Ly.B(j), 1, 0, nullptr, S + Ly.Ref(), ptol));
-    WL_TRY(launch_update<T>(ctx, n, Vn, b, 0, 1, S + Ly.Ri2(), nullptr, 0.0, nullptr, 1.0, Vn, b, nullptr));
+                       S + Ly.B(j), 1, 0, nullptr, S + Ly.Ref(), ptol, nullptr, 0.0, nullptr, -1, nullptr, &gp));
+    WL_TRY(update(Vn, 1, S + Ly.Ri2(), nullptr, 0.0, 1.0, Vn, nullptr));
   }
   return read_projection(ctx, b, K, S, hA, hB, hR0, K_eff);
 }

@@ -435,13 +435,41 @@ __global__ __launch_bounds__(256) void k_update_f4(int64_t n, const float* X, in
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int UPD_MFMA_MAXK = 48;
 
+// Coefficient (r, c) of block k: C's, or with a projection step (pj.nbv > 0) what
+// k_lanczos_proj would have written for it, taken from the inner products themselves.
+__device__ __forceinline__ double coef_at(const double* __restrict__ C, const ProjArgs& pj, int b, int k, int r,
+                                          int c) {
+  if (pj.nbv == 0) return C[((int64_t)k * b + r) * b + c];
+  const double* Pk = pj.P + (int64_t)k * b * b;
+  if (k == pj.nbv) return r == c ? 1.0 : 0.0;
+  return k + 1 < pj.nbv ? -Pk[r * b + c] : -(0.5 * (Pk[r * b + c] + Pk[c * b + r]));
+}
+
+// The other results of the projection step (A_j and the block's scale), by workgroup 0.
+__device__ __forceinline__ void proj_outputs(const ProjArgs& pj, int b) {
+  if (pj.nbv == 0 || blockIdx.x != 0) return;
+  const int t = threadIdx.x;
+  const double* Aj = pj.P + (int64_t)(pj.nbv - 1) * b * b;
+  const double* Gp = Aj + (int64_t)b * b;
+  for (int e = t; e < b * b; e += 256) {
+    const int i = e / b, j = e % b;
+    pj.Aout[e] = 0.5 * (Aj[i * b + j] + Aj[j * b + i]);
+  }
+  if (t < 64) {
+    double m = t < b ? fmax(0.0, Gp[t * b + t]) : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (t == 0) *pj.ref = m;
+  }
+}
+
 template <bool GRAM>
 __global__ __launch_bounds__(256) void k_update_mfma16(int64_t n, const float* X, int64_t sX, int nblk,
                                                        const double* __restrict__ C, const float* Yin, double alpha,
                                                        const float* __restrict__ wv, double beta, float* Out,
                                                        double* __restrict__ partials,
                                                        const double* __restrict__ skip,
-                                                       const double* __restrict__ skip_gram) {
+                                                       const double* __restrict__ skip_gram, ProjArgs pj) {
   if (skip && *skip != 0.0) return;  // identity update the caller elides
   extern __shared__ float4 sCl[];  // nblk x 64 lane-ordered operands (nblk KiB)
   __shared__ double red[256];
@@ -449,9 +477,10 @@ __global__ __launch_bounds__(256) void k_update_mfma16(int64_t n, const float* X
   const int g = lane >> 4, c = lane & 15;
   for (int e = threadIdx.x; e < nblk * 64; e += 256) {
     const int k = e >> 6, l = e & 63, gg = l >> 4, cc = l & 15;
-    const double* Ck = C + (int64_t)k * 256 + (4 * gg) * 16 + cc;
-    sCl[e] = make_float4((float)Ck[0], (float)Ck[16], (float)Ck[32], (float)Ck[48]);
+    sCl[e] = make_float4((float)coef_at(C, pj, 16, k, 4 * gg, cc), (float)coef_at(C, pj, 16, k, 4 * gg + 1, cc),
+                         (float)coef_at(C, pj, 16, k, 4 * gg + 2, cc), (float)coef_at(C, pj, 16, k, 4 * gg + 3, cc));
   }
+  proj_outputs(pj, 16);
   __syncthreads();
   const bool gram = GRAM && !(skip_gram && *skip_gram != 0.0);
   const float tb = (float)beta, ta = (float)alpha;
@@ -539,7 +568,7 @@ __global__ __launch_bounds__(256) void k_update_mfma32(int64_t n, const float* X
                                                        const float* __restrict__ wv, double beta, float* Out,
                                                        double* __restrict__ partials,
                                                        const double* __restrict__ skip,
-                                                       const double* __restrict__ skip_gram) {
+                                                       const double* __restrict__ skip_gram, ProjArgs pj) {
   if (skip && *skip != 0.0) return;  // identity update the caller elides
   extern __shared__ float4 sCl[];     // [block][tile t][half h][lane], nblk x 4 KiB
   __shared__ double red[3][256];
@@ -548,9 +577,11 @@ __global__ __launch_bounds__(256) void k_update_mfma32(int64_t n, const float* X
   for (int e = threadIdx.x; e < nblk * 256; e += 256) {
     const int k = e >> 8, th = (e >> 6) & 3, l = e & 63;
     const int t = th >> 1, h = th & 1, gg = l >> 4, cc = l & 15;
-    const double* Ck = C + (int64_t)k * 1024 + (16 * h + 4 * gg) * 32 + 16 * t + cc;
-    sCl[e] = make_float4((float)Ck[0], (float)Ck[32], (float)Ck[64], (float)Ck[96]);
+    const int r = 16 * h + 4 * gg, q = 16 * t + cc;
+    sCl[e] = make_float4((float)coef_at(C, pj, 32, k, r, q), (float)coef_at(C, pj, 32, k, r + 1, q),
+                         (float)coef_at(C, pj, 32, k, r + 2, q), (float)coef_at(C, pj, 32, k, r + 3, q));
   }
+  proj_outputs(pj, 32);
   __syncthreads();
   const bool gram = GRAM && !(skip_gram && *skip_gram != 0.0);
   const float tb = (float)beta, ta = (float)alpha;
@@ -690,7 +721,7 @@ __global__ __launch_bounds__(256) void k_update_mx(int64_t n, int b, const T* X,
                                                    const double* __restrict__ C, const T* Yin, double alpha,
                                                    const T* __restrict__ wv, double beta, T* Out, int EB,
                                                    double* __restrict__ partials, const double* __restrict__ skip,
-                                                   const double* __restrict__ skip_gram) {
+                                                   const double* __restrict__ skip_gram, ProjArgs pj) {
   if (skip && *skip != 0.0) return;  // identity update the caller elides
   typedef LaneVec<T, VW> V;
   typedef typename Mfma<T>::acc acc_t;
@@ -706,10 +737,11 @@ __global__ __launch_bounds__(256) void k_update_mx(int64_t n, int b, const T* X,
 #pragma unroll
     for (int s = 0; s < VW; ++s) {
       const int r = 4 * VW * q + VW * (l >> 4) + s;
-      w.v[s] = r < b && col < b ? (T)C[((int64_t)k * b + r) * b + col] : T(0);
+      w.v[s] = r < b && col < b ? (T)coef_at(C, pj, b, k, r, col) : T(0);
     }
     sC[e] = w;
   }
+  proj_outputs(pj, b);
   __syncthreads();
   const bool gram = GRAM && !(skip_gram && *skip_gram != 0.0);
   const T tb = (T)beta, ta = (T)alpha;
@@ -1138,14 +1170,15 @@ __device__ __forceinline__ void chol_sync() {
   }
 }
 
-template <int B, int NT>
-__global__ __launch_bounds__(NT) void k_chol(int b, const double* __restrict__ G, double tol,
+template <int B, int NT, int NF>
+__global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G, double tol,
                                              const double* __restrict__ Aref, const double* __restrict__ Bref,
                                              double* __restrict__ R, double* __restrict__ Rinv,
                                              const double* __restrict__ Rprev, double* __restrict__ Bout,
                                              int64_t gs, double* __restrict__ ref_out, const double* ref_in,
                                              double post_tol, double* skip_out, double skip_ratio,
-                                             const double* skip_in, int dg, const double* dref) {
+                                             const double* skip_in, int dg, const double* dref,
+                                             const double* __restrict__ parts, int nparts, int PB) {
   const int64_t go = (int64_t)blockIdx.x * gs;  // batch: graph g's matrices at +g gs
   if (ref_out) ref_out += go;
   if (ref_in) ref_in += go;
@@ -1161,7 +1194,7 @@ __global__ __launch_bounds__(NT) void k_chol(int b, const double* __restrict__ G
   if (Bout) Bout += go;
   if (skip_in && *skip_in != 0.0) {
     // second pass not needed: identity factors, Bout = Rprev (the first pass's factor)
-    for (int e = t; e < b * b; e += NT) {
+    for (int e = t; e < b * b; e += NF) {
       const double id = (e / b == e % b) ? 1.0 : 0.0;
       if (R) R[e] = id;
       Rinv[e] = id;
@@ -1212,6 +1245,28 @@ __global__ __launch_bounds__(NT) void k_chol(int b, const double* __restrict__ G
     }
     return;
   }
+  // NF > NT: G is still in nparts partial sums of PB x PB entries, which all NF threads sum
+  // (fixed order: entry e, phase p takes partials p, p + P, ..; then a tree over the phases)
+  __shared__ double sG[NF > NT ? NF : 1];
+  if constexpr (NF > NT) {
+    const int E = PB * PB, P = NF / E, el = t % E, p = t / E;
+    const double* src = parts + el;
+    double u[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int q = p;
+    for (; q + 7 * P < nparts; q += 8 * P) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) u[i] += src[(int64_t)(q + i * P) * E];
+    }
+    for (; q < nparts; q += P) u[0] += src[(int64_t)q * E];
+    sG[t] = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
+    __syncthreads();
+    for (int h = P / 2; h > 0; h >>= 1) {
+      if (p < h) sG[t] += sG[t + h * E];
+      __syncthreads();
+    }
+    if (t >= NT) return;
+  }
+  auto gat = [&](int i, int j) { return NF > NT ? sG[i * PB + j] : G[i * b + j]; };
   constexpr int GR = NT / B, EPL = B / GR;
   static_assert(GR * EPL == B, "entries per thread");
   __shared__ double sR[B * B], sP[B * B];
@@ -1223,7 +1278,7 @@ __global__ __launch_bounds__(NT) void k_chol(int b, const double* __restrict__ G
 #pragma unroll
   for (int u = 0; u < EPL; ++u) {
     const int i = GR * u + g;
-    a[u] = (i < b && c < b) ? 0.5 * (G[i * b + c] + G[c * b + i]) : 0.0;
+    a[u] = (i < b && c < b) ? 0.5 * (gat(i, c) + gat(c, i)) : 0.0;
     e[u] = i == c ? 1.0 : 0.0;
   }
   if (Bout && Rprev) {
@@ -1682,6 +1737,21 @@ int fin_grid(int E) {
   return (E + EB - 1) / EB;
 }
 
+// A Gram left in its partial sums for the factorisation that follows: where one workgroup
+// of 1024 threads sums them in about the time of the launch it saves (up to 32768 values: 5
+// columns of 5000 rows, 79 partials, 2.8 + 3.2 us in two launches -> 4.1 us; FP64, 8 columns
+// of 200k rows, 512 partials, at the line, 4.6 + 3.2 -> 7.6), or, for a second pass that
+// mostly is not needed at all, up to 131072 (1 MB through one CU, about 10 us).
+// A Lanczos step is 8 launches so and was 11: 1.50 -> 1.31 ms for 30 steps of the first,
+// 3.18 -> 3.14 ms for the second.
+bool defer_sum(GramParts* gp, const double* parts, int64_t nparts, int PB, const double* skip) {
+  if (!gp || PB < 8 || PB > 32 || nparts * PB * PB > (skip ? 131072 : 32768)) return false;
+  gp->p = parts;
+  gp->nparts = (int)nparts;
+  gp->PB = PB;
+  return true;
+}
+
 // blocks X_k that share a pass over Y: as many as the accumulators leave room for
 template <typename T, int B>
 void gram_mx(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int nblk, const T* Y, int ldy, int bx, int by,
@@ -1804,7 +1874,7 @@ int pick_B(int b) {
 template <typename T, int VW, int NT>
 wl_status update_mx(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C, const T* Yin,
                     double alpha, const T* wv, double beta, T* Out, double* gram_out, const double* skip,
-                    const double* skip_gram, bool* done) {
+                    const double* skip_gram, const ProjArgs& pj, GramParts* gp, bool* done) {
   const size_t bytes = mx_block_bytes(b, VW, sizeof(T));
   const uintptr_t xo = reinterpret_cast<uintptr_t>(X), oo = reinterpret_cast<uintptr_t>(Out);
   const bool alias = nblk > 0 && oo >= xo && oo < xo + ((uintptr_t)(nblk - 1) * sX + (uintptr_t)n * b) * sizeof(T);
@@ -1813,6 +1883,7 @@ wl_status update_mx(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int n
     kmax = (int)(131072 / bytes);
     if (nblk > kmax && alias) return WL_OK;
   }
+  if (pj.nbv > 0 && nblk > kmax) return WL_OK;  // its coefficients are staged by one launch
   *done = true;
   const int64_t nchunks = (n + 15) / 16;
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(gram_out ? 512 : 1024, (nchunks + 3) / 4));
@@ -1830,14 +1901,14 @@ wl_status update_mx(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int n
     const T* wk = first ? wv : nullptr;
     if (last && gram_out)
       hipLaunchKernelGGL((k_update_mx<T, VW, NT, true>), dim3(grid), dim3(256), kb * bytes, ctx->stream, n, b, Xk, sX,
-                         kb, Ck, Yk, ak, wk, beta, Out, EB, ctx->partials.as<double>(), skip, skip_gram);
+                         kb, Ck, Yk, ak, wk, beta, Out, EB, ctx->partials.as<double>(), skip, skip_gram, pj);
     else
       hipLaunchKernelGGL((k_update_mx<T, VW, NT, false>), dim3(grid), dim3(256), kb * bytes, ctx->stream, n, b, Xk,
-                         sX, kb, Ck, Yk, ak, wk, beta, Out, EB, nullptr, skip, nullptr);
+                         sX, kb, Ck, Yk, ak, wk, beta, Out, EB, nullptr, skip, nullptr, pj);
     WL_HIP(hipGetLastError());
     k0 += kb;
   } while (k0 < nblk);
-  if (gram_out) {
+  if (gram_out && !defer_sum(gp, ctx->partials.as<double>(), grid, EB, skip_gram)) {
     hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(EB * EB), 1), dim3(256), 0, ctx->stream,
                        ctx->partials.as<double>(), grid, EB, b, b, gram_out, skip_gram);
     WL_HIP(hipGetLastError());
@@ -1848,14 +1919,18 @@ wl_status update_mx(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int n
 template <typename T, int VW>
 wl_status update_mx_nt(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C, const T* Yin,
                        double alpha, const T* wv, double beta, T* Out, double* gram_out, const double* skip,
-                       const double* skip_gram, bool* done) {
+                       const double* skip_gram, const ProjArgs& pj, GramParts* gp, bool* done) {
   if (b <= 16)
-    return update_mx<T, VW, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+    return update_mx<T, VW, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
   if (b <= 32)
-    return update_mx<T, VW, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+    return update_mx<T, VW, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
   if (b <= 48)
-    return update_mx<T, VW, 3>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
-  return update_mx<T, VW, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+    return update_mx<T, VW, 3>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
+  return update_mx<T, VW, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
 }
 
 // The widest loads that the width and the alignment of the blocks X_k allow (and that give
@@ -1863,24 +1938,28 @@ wl_status update_mx_nt(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, in
 template <typename T>
 wl_status update_mx_any(wl_ctx* ctx, int64_t n, int b, const T* X, int64_t sX, int nblk, const double* C,
                         const T* Yin, double alpha, const T* wv, double beta, T* Out, double* gram_out,
-                        const double* skip, const double* skip_gram, bool* done) {
+                        const double* skip, const double* skip_gram, const ProjArgs& pj, GramParts* gp,
+                        bool* done) {
   *done = false;
   if (b < 5 || b > 64 || (skip && gram_out)) return WL_OK;
   const uintptr_t xo = reinterpret_cast<uintptr_t>(X);
   auto fits = [&](int vw) { return b % vw == 0 && sX % vw == 0 && xo % (vw * sizeof(T)) == 0; };
   if constexpr (sizeof(T) == 4) {
     if (b > 8 && fits(4))
-      return update_mx_nt<T, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+      return update_mx_nt<T, 4>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
   }
   if (fits(2))
-    return update_mx_nt<T, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
-  return update_mx_nt<T, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, done);
+    return update_mx_nt<T, 2>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
+  return update_mx_nt<T, 1>(ctx, n, b, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                             done);
 }
 
 template <typename T, int B>
 wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int nblk, int bx, const double* C,
                    const T* Yin, int ldy, double alpha, const T* wv, double beta, T* Out, int by,
-                   double* gram_out, const double* skip, const double* skip_gram) {
+                   double* gram_out, const double* skip, const double* skip_gram, ProjArgs pj, GramParts* gp) {
   constexpr int E = B * B;
   if constexpr (sizeof(T) == 4 && B == 16) {
     const bool al = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Out) |
@@ -1895,15 +1974,17 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
         WL_TRY(ctx->partials.ensure((size_t)grid * 256 * sizeof(double)));
         hipLaunchKernelGGL(k_update_mfma16<true>, dim3((unsigned)grid), dim3(256), lds, ctx->stream, n,
                            (const float*)X, sX, nblk, C, (const float*)Yin, alpha, (const float*)wv, beta,
-                           (float*)Out, ctx->partials.as<double>(), skip, skip_gram);
+                           (float*)Out, ctx->partials.as<double>(), skip, skip_gram, pj);
         WL_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(256), 1), dim3(256), 0, ctx->stream,
-                           ctx->partials.as<double>(), (int)grid, 16, 16, 16, gram_out, skip_gram);
-        WL_HIP(hipGetLastError());
+        if (!defer_sum(gp, ctx->partials.as<double>(), grid, 16, skip_gram)) {
+          hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(256), 1), dim3(256), 0, ctx->stream,
+                             ctx->partials.as<double>(), (int)grid, 16, 16, 16, gram_out, skip_gram);
+          WL_HIP(hipGetLastError());
+        }
       } else {
         hipLaunchKernelGGL(k_update_mfma16<false>, dim3((unsigned)grid), dim3(256), lds, ctx->stream, n,
                            (const float*)X, sX, nblk, C, (const float*)Yin, alpha, (const float*)wv, beta,
-                           (float*)Out, nullptr, skip, nullptr);
+                           (float*)Out, nullptr, skip, nullptr, pj);
         WL_HIP(hipGetLastError());
       }
       return WL_OK;
@@ -1917,7 +1998,8 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
     const uintptr_t xo = reinterpret_cast<uintptr_t>(X), oo = reinterpret_cast<uintptr_t>(Out);
     const bool chain_alias = nblk > UPD32_MAXK && oo >= xo &&
                              oo < xo + ((uintptr_t)(nblk - 1) * (uintptr_t)sX + (uintptr_t)n * 32) * sizeof(float);
-    if (bx == 32 && by == 32 && ldx == 32 && ldy == 32 && al && !(skip && gram_out) && !chain_alias) {
+    if (bx == 32 && by == 32 && ldx == 32 && ldy == 32 && al && !(skip && gram_out) && !chain_alias &&
+        (pj.nbv == 0 || nblk <= UPD32_MAXK)) {
       const int64_t nchunks = (n + 15) / 16;
       int64_t grid = (nchunks + 15) / 16;  // about four chunks per wave
       if (grid > 1024) grid = 1024;
@@ -1934,13 +2016,14 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
         if (last && gram_out) {
           hipLaunchKernelGGL(k_update_mfma32<true>, dim3((unsigned)grid), dim3(256), lds, ctx->stream, n, Xk, sX, kb,
                              C + (int64_t)k0 * 1024, Yk, ak, wk, beta, (float*)Out, ctx->partials.as<double>(), skip,
-                             skip_gram);
+                             skip_gram, pj);
           WL_HIP(hipGetLastError());
-          hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(1024), 1), dim3(256), 0, ctx->stream,
+          if (!defer_sum(gp, ctx->partials.as<double>(), grid, 32, skip_gram))
+            hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(1024), 1), dim3(256), 0, ctx->stream,
                              ctx->partials.as<double>(), (int)grid, 32, 32, 32, gram_out, skip_gram);
         } else {
           hipLaunchKernelGGL(k_update_mfma32<false>, dim3((unsigned)grid), dim3(256), lds, ctx->stream, n, Xk, sX, kb,
-                             C + (int64_t)k0 * 1024, Yk, ak, wk, beta, (float*)Out, nullptr, skip, nullptr);
+                             C + (int64_t)k0 * 1024, Yk, ak, wk, beta, (float*)Out, nullptr, skip, nullptr, pj);
         }
         WL_HIP(hipGetLastError());
       }
@@ -1950,10 +2033,13 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
   if constexpr (B >= 8) {
     if (bx == by && ldx == bx && ldy == by) {
       bool done = false;
-      WL_TRY(update_mx_any<T>(ctx, n, bx, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, &done));
+      WL_TRY(update_mx_any<T>(ctx, n, bx, X, sX, nblk, C, Yin, alpha, wv, beta, Out, gram_out, skip, skip_gram, pj, gp,
+                              &done));
       if (done) return WL_OK;
     }
   }
+  if (pj.nbv > 0)  // the other kernels read the projection's coefficients from memory
+    WL_TRY(launch_lanczos_proj(ctx, bx, pj.nbv, pj.P, pj.Aout, const_cast<double*>(C), pj.ref, 1, 0));
   if constexpr (sizeof(T) == 4 && B == 4) {
     const bool al = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Out) |
                       reinterpret_cast<uintptr_t>(Yin)) & 15u) == 0 && (sX % 4) == 0;
@@ -2037,24 +2123,24 @@ wl_status launch_gram(wl_ctx* ctx, int64_t n, const T* X, int bx, int64_t sX, in
 template <typename T>
 wl_status launch_update_skip(wl_ctx* ctx, int64_t n, const T* X, int bx, int64_t sX, int nblk, const double* C,
                              const T* Yin, double alpha, const T* wv, double beta, T* Out, int by, double* gram_out,
-                             const double* skip, const double* skip_gram) {
+                             const double* skip, const double* skip_gram, const ProjArgs& pj, GramParts* gp) {
   WL_CHECK(bx >= 1 && bx <= 64 && by >= 1 && by <= 64, WL_EINVAL, "update: block sizes out of range");
   const int B = pick_B(bx > by ? bx : by);
   switch (B) {
     case 1: return update_B<T, 1>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     case 2: return update_B<T, 2>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     case 4: return update_B<T, 4>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     case 8: return update_B<T, 8>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     case 16: return update_B<T, 16>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     case 32: return update_B<T, 32>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
     default: return update_B<T, 64>(ctx, n, X, bx, sX, nblk, bx, C, Yin, by, alpha, wv, beta, Out, by, gram_out,
-                                                   skip, skip_gram);
+                                                   skip, skip_gram, pj, gp);
   }
 }
 
@@ -2077,21 +2163,25 @@ wl_status launch_lanczos_proj(wl_ctx* ctx, int b, int nbv, const double* P, doub
 wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const double* Aref, const double* Bref,
                       double* R, double* Rinv, const double* Rprev, double* Bout, int ngraphs, int64_t gs,
                       double* ref_out, const double* ref_in, double post_tol, double* skip_out, double skip_ratio,
-                      const double* skip_in, int dg, const double* dref) {
+                      const double* skip_in, int dg, const double* dref, const GramParts* gp) {
   WL_CHECK(b >= 1 && b <= 64 && ngraphs >= 1, WL_EINVAL, "chol: b out of range");
+  const bool sum = gp && gp->nparts > 0;
+  WL_CHECK(!sum || (ngraphs == 1 && b > gp->PB / 2 && b <= gp->PB && gp->PB >= 8 && gp->PB <= 32), WL_EINTERNAL,
+           "chol: partial sums of another shape");
+  auto run = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(ngraphs), dim3(threads), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv, Rprev,
+                       Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref,
+                       sum ? gp->p : nullptr, sum ? gp->nparts : 0, sum ? gp->PB : 0);
+  };
   // the smallest size that holds the matrix, 16 entries per thread at most
   if (b <= 8)
-    hipLaunchKernelGGL((k_chol<8, 64>), dim3(ngraphs), dim3(64), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv, Rprev,
-                       Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+    sum ? run(k_chol<8, 64, 1024>, 1024) : run(k_chol<8, 64, 64>, 64);
   else if (b <= 16)
-    hipLaunchKernelGGL((k_chol<16, 64>), dim3(ngraphs), dim3(64), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
-                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+    sum ? run(k_chol<16, 64, 1024>, 1024) : run(k_chol<16, 64, 64>, 64);
   else if (b <= 32)
-    hipLaunchKernelGGL((k_chol<32, 256>), dim3(ngraphs), dim3(256), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
-                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+    sum ? run(k_chol<32, 256, 1024>, 1024) : run(k_chol<32, 256, 256>, 256);
   else
-    hipLaunchKernelGGL((k_chol<64, 256>), dim3(ngraphs), dim3(256), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv,
-                       Rprev, Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref);
+    run(k_chol<64, 256, 256>, 256);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }
@@ -2247,7 +2337,7 @@ size_t update_partials_bound(int64_t n, int prec, int b) {
                                       double, const T*, double, T*, int, double*);                                 \
   template wl_status launch_update_skip<T>(wl_ctx*, int64_t, const T*, int, int64_t, int, const double*, const T*, \
                                            double, const T*, double, T*, int, double*, const double*,             \
-                                           const double*);                                                         \
+                                           const double*, const ProjArgs&, GramParts*);                                                         \
   template wl_status launch_fill<T>(wl_ctx*, int64_t, T, T*);                                                      \
   template wl_status launch_axpby_rows<T>(wl_ctx*, int64_t, int, const T*, const T*, double, const T*, T*);       \
   template wl_status launch_degrees<T>(wl_graph*, T*);                                                              \

@@ -344,13 +344,30 @@ wl_status launch_gram(wl_ctx* ctx, int64_t n, const T* X, int bx, int64_t sX, in
 template <typename T>
 wl_status launch_update(wl_ctx* ctx, int64_t n, const T* X, int bx, int64_t sX, int nblk, const double* C,
                         const T* Yin, double alpha, const T* wv, double beta, T* Out, int by, double* gram_out);
+// A block Lanczos projection folded into an update of its nbv + 1 blocks: the update takes its
+// coefficients from the inner products P and writes A_j and the block's scale (the results of
+// launch_lanczos_proj, whose launch it saves; kernels without this form run it, with C as
+// its target).  nbv = 0: none.
+struct ProjArgs {
+  int nbv = 0;
+  const double* P = nullptr;
+  double* Aout = nullptr;
+  double* ref = nullptr;
+};
+// A Gram whose partial sums are left to launch_chol (nparts = 0: the sum is in gram_out).
+// Nothing else may use ctx->partials in between.
+struct GramParts {
+  const double* p = nullptr;
+  int nparts = 0, PB = 0;
+};
 // The same with device flags (may be NULL): when *skip != 0 the update is an identity
 // the caller elides (the kernel returns at once); when *skip_gram != 0 the Gram of the
 // output is not needed.  Only the FP32 block paths honour them (others compute).
 template <typename T>
 wl_status launch_update_skip(wl_ctx* ctx, int64_t n, const T* X, int bx, int64_t sX, int nblk, const double* C,
                              const T* Yin, double alpha, const T* wv, double beta, T* Out, int by, double* gram_out,
-                             const double* skip, const double* skip_gram);
+                             const double* skip, const double* skip_gram,
+                             const ProjArgs& pj = ProjArgs(), GramParts* gp = nullptr);
 
 // Cholesky with deflation of the b x b Gram G (double, device):
 //   G = R^T R, R upper; Rinv the inverse on the non-deflated columns (zero elsewhere).
@@ -366,7 +383,7 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
                       double* R, double* Rinv, const double* Rprev, double* Bout, int ngraphs = 1,
                       int64_t gs = 0, double* ref_out = nullptr, const double* ref_in = nullptr,
                       double post_tol = 0.0, double* skip_out = nullptr, double skip_ratio = 0.0,
-                      const double* skip_in = nullptr, int dg = -1, const double* dref = nullptr);
+                      const double* skip_in = nullptr, int dg = -1, const double* dref = nullptr, const GramParts* gp = nullptr);
 // dg: index of a group (workgroup) whose columns are independent single-column
 // processes: its G is taken as diagonal, each column deflated against its own scale
 // (dref, optional: per-group b x b matrices whose diagonal is the column scale of the
