@@ -1170,6 +1170,19 @@ __device__ __forceinline__ void chol_sync() {
   }
 }
 
+// The step's last small matrices of one group of 16 columns: N_{j+1} = Rinv and the
+// three-term coefficient N_j B_j^T of the next product.
+template <int NT>
+__device__ __forceinline__ void next_factors(const NextArgs& nx, const double* Rinv, const double* Bj, int64_t go) {
+  for (int e = threadIdx.x; e < 256; e += NT) {
+    const int i = e >> 4, j = e & 15;
+    nx.Nnext[go + e] = Rinv[e];
+    double c = 0.0;
+    for (int k = 0; k < 16; ++k) c += nx.Ncur[go + i * 16 + k] * Bj[j * 16 + k];
+    nx.Ct[go + e] = c;
+  }
+}
+
 template <int B, int NT, int NF>
 __global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G, double tol,
                                              const double* __restrict__ Aref, const double* __restrict__ Bref,
@@ -1178,7 +1191,8 @@ __global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G
                                              int64_t gs, double* __restrict__ ref_out, const double* ref_in,
                                              double post_tol, double* skip_out, double skip_ratio,
                                              const double* skip_in, int dg, const double* dref,
-                                             const double* __restrict__ parts, int nparts, int PB) {
+                                             const double* __restrict__ parts, int nparts, int PB,
+                                             int64_t pstride, NextArgs nx) {
   const int64_t go = (int64_t)blockIdx.x * gs;  // batch: graph g's matrices at +g gs
   if (ref_out) ref_out += go;
   if (ref_in) ref_in += go;
@@ -1199,6 +1213,9 @@ __global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G
       if (R) R[e] = id;
       Rinv[e] = id;
       if (Bout) Bout[e] = Rprev ? Rprev[e] : id;
+    }
+    if constexpr (NF > NT && B == 16) {
+      if (nx.Nnext) next_factors<NF>(nx, nx.Ri1 + go, Rprev, go);
     }
     return;
   }
@@ -1250,14 +1267,14 @@ __global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G
   __shared__ double sG[NF > NT ? NF : 1];
   if constexpr (NF > NT) {
     const int E = PB * PB, P = NF / E, el = t % E, p = t / E;
-    const double* src = parts + el;
+    const double* src = parts + (int64_t)blockIdx.x * E + el;
     double u[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int q = p;
     for (; q + 7 * P < nparts; q += 8 * P) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) u[i] += src[(int64_t)(q + i * P) * E];
+      for (int i = 0; i < 8; ++i) u[i] += src[(q + i * P) * pstride];
     }
-    for (; q < nparts; q += P) u[0] += src[(int64_t)q * E];
+    for (; q < nparts; q += P) u[0] += src[q * pstride];
     sG[t] = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
     __syncthreads();
     for (int h = P / 2; h > 0; h >>= 1) {
@@ -1405,6 +1422,12 @@ __global__ __launch_bounds__(NF) void k_chol(int b, const double* __restrict__ G
   for (int u = 0; u < EPL; ++u) {
     const int i = GR * u + g;
     if (i < b && c < b) Rinv[c * b + i] = c <= i ? e[u] : 0.0;
+  }
+  if constexpr (NF > NT && B == 16) {
+    if (nx.Nnext) {
+      __syncthreads();  // Rinv and Bout of all threads
+      next_factors<NT>(nx, Rinv, Bout, go);
+    }
   }
   // Is a second CholQR pass needed?  One pass with the Gram accumulated in FP64 leaves
   // the new block orthonormal to about u_64 kappa^2; kappa^2 is the ratio of the largest
@@ -1749,6 +1772,7 @@ bool defer_sum(GramParts* gp, const double* parts, int64_t nparts, int PB, const
   gp->p = parts;
   gp->nparts = (int)nparts;
   gp->PB = PB;
+  gp->stride = (int64_t)PB * PB;
   return true;
 }
 
@@ -2163,15 +2187,16 @@ wl_status launch_lanczos_proj(wl_ctx* ctx, int b, int nbv, const double* P, doub
 wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const double* Aref, const double* Bref,
                       double* R, double* Rinv, const double* Rprev, double* Bout, int ngraphs, int64_t gs,
                       double* ref_out, const double* ref_in, double post_tol, double* skip_out, double skip_ratio,
-                      const double* skip_in, int dg, const double* dref, const GramParts* gp) {
+                      const double* skip_in, int dg, const double* dref, const GramParts* gp, const NextArgs& nx) {
   WL_CHECK(b >= 1 && b <= 64 && ngraphs >= 1, WL_EINVAL, "chol: b out of range");
   const bool sum = gp && gp->nparts > 0;
-  WL_CHECK(!sum || (ngraphs == 1 && b > gp->PB / 2 && b <= gp->PB && gp->PB >= 8 && gp->PB <= 32), WL_EINTERNAL,
+  WL_CHECK((!sum && !nx.Nnext) || (sum && b > gp->PB / 2 && b <= gp->PB && gp->PB >= 8 && gp->PB <= 32 && (!nx.Nnext || b == 16)),
+           WL_EINTERNAL,
            "chol: partial sums of another shape");
   auto run = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, dim3(ngraphs), dim3(threads), 0, ctx->stream, b, G, tol, Aref, Bref, R, Rinv, Rprev,
                        Bout, gs, ref_out, ref_in, post_tol, skip_out, skip_ratio, skip_in, dg, dref,
-                       sum ? gp->p : nullptr, sum ? gp->nparts : 0, sum ? gp->PB : 0);
+                       sum ? gp->p : nullptr, sum ? gp->nparts : 0, sum ? gp->PB : 0, sum ? gp->stride : 0, nx);
   };
   // the smallest size that holds the matrix, 16 entries per thread at most
   if (b <= 8)

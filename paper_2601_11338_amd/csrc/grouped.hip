@@ -544,7 +544,7 @@ wl_status launch_ggram(wl_ctx* ctx, int64_t n, int gb, int ng, const T* X, int64
 template <typename T>
 wl_status launch_gupdate(wl_ctx* ctx, int64_t n, int gb, int ng, const T* X, int64_t sX, int nblk,
                          const double* C, int64_t cs, const T* Yin, double alpha, const T* wv, double beta, T* Out,
-                         double* gram_out, int64_t gs, const double* skip, const double* skip_gram, int dg) {
+                         double* gram_out, int64_t gs, const double* skip, const double* skip_gram, int dg, GramParts* gp) {
   WL_CHECK(grouped_supported(prec_of<T>(), gb, ng), WL_EUNSUPPORTED, "grouped update: unsupported group shape");
   WL_CHECK(nblk >= 0 && nblk <= (gb == 1 ? G1_MAXK : G16_LDS_KB), WL_EINVAL, "grouped update: too many blocks");
   WL_CHECK(!(skip && gram_out && skip_gram != skip), WL_EINVAL,
@@ -596,7 +596,12 @@ wl_status launch_gupdate(wl_ctx* ctx, int64_t n, int gb, int ng, const T* X, int
     }
     WL_HIP(hipGetLastError());
   }
-  if (gram_out) {
+  if (gram_out && gp && gb == 16) {  // summed by the factorisation
+    gp->p = ctx->partials.as<double>();
+    gp->nparts = nparts;
+    gp->PB = 16;
+    gp->stride = (int64_t)ng * E;
+  } else if (gram_out) {
     const int64_t tot = (int64_t)ng * E;
     hipLaunchKernelGGL(k_gfinalize, dim3((unsigned)((tot + 15) / 16)), dim3(256), 0, ctx->stream,
                        ctx->partials.as<double>(), nparts, ng, 1, E, gram_out, gs, skip_gram, dg, gb);
@@ -670,22 +675,6 @@ __global__ __launch_bounds__(256) void k_lanczos_proj_deferred(int nbv, const do
   }
 }
 
-// After the step's CholQR: N_{j+1} = skip ? Ri1 : Ri2 (the block was normalised
-// explicitly by Ri1 only where a second pass was needed), and the three-term
-// coefficient of the next product for the stored W_j: Ct = N_j B_j^T (16 x 16).
-__global__ __launch_bounds__(256) void k_lanczos_next(const double* __restrict__ skip, const double* __restrict__ Ri1,
-                                                      const double* __restrict__ Ri2, const double* __restrict__ Ncur,
-                                                      const double* __restrict__ B, double* __restrict__ Nnext,
-                                                      double* __restrict__ Ct, int64_t gs) {
-  const int64_t go = (int64_t)blockIdx.x * gs;
-  const int t = threadIdx.x, i = t >> 4, j = t & 15;
-  const bool sk = skip[go] != 0.0;
-  Nnext[go + t] = sk ? Ri1[go + t] : Ri2[go + t];
-  double c = 0.0;
-  for (int k = 0; k < 16; ++k) c += Ncur[go + i * 16 + k] * B[go + j * 16 + k];
-  Ct[go + t] = c;
-}
-
 }  // namespace
 
 wl_status launch_eye_groups(wl_ctx* ctx, int ng, double* N0, int64_t gs) {
@@ -699,13 +688,6 @@ wl_status launch_lanczos_proj_deferred(wl_ctx* ctx, int ng, int nbv, const doubl
   WL_CHECK(nbv == 1 || nbv == 2, WL_EINVAL, "lanczos projection: bad sizes");
   hipLaunchKernelGGL(k_lanczos_proj_deferred, dim3(ng), dim3(256), 0, ctx->stream, nbv, P, Nprev, Ncur, Aout, Cc, gs,
                      ref_out);
-  WL_HIP(hipGetLastError());
-  return WL_OK;
-}
-
-wl_status launch_lanczos_next(wl_ctx* ctx, int ng, const double* skip, const double* Ri1, const double* Ri2,
-                              const double* Ncur, const double* B, double* Nnext, double* Ct, int64_t gs) {
-  hipLaunchKernelGGL(k_lanczos_next, dim3(ng), dim3(256), 0, ctx->stream, skip, Ri1, Ri2, Ncur, B, Nnext, Ct, gs);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }
@@ -731,7 +713,7 @@ wl_status launch_group_copy(wl_ctx* ctx, int64_t n, int b, int ng, int q, const 
                                      int64_t, const double*, int);                                                 \
   template wl_status launch_gupdate<T>(wl_ctx*, int64_t, int, int, const T*, int64_t, int, const double*, int64_t, \
                                        const T*, double, const T*, double, T*, double*, int64_t, const double*,    \
-                                       const double*, int);                                                        \
+                                       const double*, int, GramParts*);                                            \
   template wl_status launch_group_copy<T>(wl_ctx*, int64_t, int, int, int, const T*, T*, bool);
 WL_INST_GROUPED(float)
 WL_INST_GROUPED(double)

@@ -259,12 +259,15 @@ wl_status lockstep_lanczos(wl_multi* m, const T* Xr, int G, int dg, int K, const
     }
     // only groups whose first factor was ill conditioned normalise the block now (and
     // take a second CholQR pass); the others keep W with N_{j+1} = R1^{-1}
+    // The factorisation of that pass sums its Gram and writes the step's last matrices: one
+    // launch where the reduction, the factorisation and N_{j+1}, N_j B_j^T were three that
+    // mostly had nothing to do (two groups of 160k rows: 11.2 us of kernels -> 3.7 us)
+    GramParts gp;
     WL_TRY(launch_gupdate<T>(ctx, n, 16, G, Vn, 0, 1, S + Ly.Ri1(), gs, nullptr, 0.0, nullptr, 1.0, Vn, S + Ly.G(),
-                             gs, S + Ly.Skip(), S + Ly.Skip(), dg));
+                             gs, S + Ly.Skip(), S + Ly.Skip(), dg, &gp));
     WL_TRY(launch_chol(ctx, 16, S + Ly.G(), tol, nullptr, nullptr, S + Ly.R2(), S + Ly.Ri2(), S + Ly.R1(),
-                       S + Ly.B(j), G, gs, nullptr, nullptr, 0.0, nullptr, 0.0, S + Ly.Skip(), dg));
-    WL_TRY(launch_lanczos_next(ctx, G, S + Ly.Skip(), S + Ly.Ri1(), S + Ly.Ri2(), S + L.N(j), S + Ly.B(j),
-                               S + L.N(j + 1), S + L.ctoff, gs));
+                       S + Ly.B(j), G, gs, nullptr, nullptr, 0.0, nullptr, 0.0, S + Ly.Skip(), dg, nullptr, &gp,
+                       NextArgs{S + Ly.Ri1(), S + L.N(j), S + L.N(j + 1), S + L.ctoff}));
   }
   return WL_OK;
 }

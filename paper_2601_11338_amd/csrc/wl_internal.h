@@ -359,6 +359,15 @@ struct ProjArgs {
 struct GramParts {
   const double* p = nullptr;
   int nparts = 0, PB = 0;
+  int64_t stride = 0;  // doubles between partials of one group (graph q's at + q PB PB)
+};
+// After the second factorisation of a step with deferred normalisation (16 columns, Gram in
+// partial sums): N_{j+1} = skip ? Ri1 : Rinv and Ct = N_j B_j^T (Nnext null: none).
+struct NextArgs {
+  const double* Ri1 = nullptr;
+  const double* Ncur = nullptr;
+  double* Nnext = nullptr;
+  double* Ct = nullptr;
 };
 // The same with device flags (may be NULL): when *skip != 0 the update is an identity
 // the caller elides (the kernel returns at once); when *skip_gram != 0 the Gram of the
@@ -383,7 +392,8 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
                       double* R, double* Rinv, const double* Rprev, double* Bout, int ngraphs = 1,
                       int64_t gs = 0, double* ref_out = nullptr, const double* ref_in = nullptr,
                       double post_tol = 0.0, double* skip_out = nullptr, double skip_ratio = 0.0,
-                      const double* skip_in = nullptr, int dg = -1, const double* dref = nullptr, const GramParts* gp = nullptr);
+                      const double* skip_in = nullptr, int dg = -1, const double* dref = nullptr,
+                      const GramParts* gp = nullptr, const NextArgs& nx = NextArgs());
 // dg: index of a group (workgroup) whose columns are independent single-column
 // processes: its G is taken as diagonal, each column deflated against its own scale
 // (dref, optional: per-group b x b matrices whose diagonal is the column scale of the
@@ -577,17 +587,15 @@ template <typename T>
 wl_status launch_gupdate(wl_ctx* ctx, int64_t n, int gb, int ng, const T* X, int64_t sX, int nblk,
                          const double* C, int64_t cs, const T* Yin, double alpha, const T* wv, double beta, T* Out,
                          double* gram_out, int64_t gs, const double* skip = nullptr,
-                         const double* skip_gram = nullptr, int dg = -1);
+                         const double* skip_gram = nullptr, int dg = -1, GramParts* gp = nullptr);
 // y_q = x_q (count doubles) for q < ng at stride gs
 wl_status launch_dcopy_groups(wl_ctx* ctx, int ng, int count, const double* x, double* y, int64_t gs);
 // Deferred normalisation of the lock-step Lanczos (16-wide groups): stored blocks W_j
 // with factors N_j (V_j = W_j N_j).  N_0 = I; the projection from the stored blocks'
-// Gram; the next factor and three-term coefficient N_j B_j^T after each CholQR.
+// Gram  (the next factor and N_j B_j^T come with the second factorisation, NextArgs).
 wl_status launch_eye_groups(wl_ctx* ctx, int ng, double* N0, int64_t gs);
 wl_status launch_lanczos_proj_deferred(wl_ctx* ctx, int ng, int nbv, const double* P, const double* Nprev,
                                        const double* Ncur, double* Aout, double* Cc, int64_t gs, double* ref_out);
-wl_status launch_lanczos_next(wl_ctx* ctx, int ng, const double* skip, const double* Ri1, const double* Ri2,
-                              const double* Ncur, const double* B, double* Nnext, double* Ct, int64_t gs);
 // Y (n x ng b) column group q = X (n x b), or X's column group q into Y (n x b)
 template <typename T>
 wl_status launch_group_copy(wl_ctx* ctx, int64_t n, int b, int ng, int q, const T* X, T* Y, bool into_group);

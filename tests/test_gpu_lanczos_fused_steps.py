@@ -52,3 +52,30 @@ def test_steps(lib, b, n, block):
         op = lib.Operator(g, 0.0, "exp", beta, dtype=dtype, krylov_dim=14, method="lanczos")
         Y = op.apply_phi(torch.tensor(X, dtype=dtype, device="cuda"))
         assert np.linalg.norm(Y.double().cpu().numpy() - ref) <= tol * np.linalg.norm(ref), dtype
+
+
+@pytest.mark.parametrize("n", [700, 5000, 40000])
+@pytest.mark.parametrize("block", ["gaussian", "near", "dependent"])
+def test_operators_in_lock_step(lib, n, block):
+    b, rp_ci = 16, synth.barabasi_albert(n, 3, 1)
+    rp, ci = rp_ci
+    A = sp.csr_matrix((np.ones(len(ci)), ci, rp), shape=(n, n))
+    lam = float(sp.linalg.eigsh(A, k=1, return_eigenvectors=False)[0])
+    X = synth.gaussian_block(n, b, seed=n)
+    if block == "near":
+        X[:, 1] = X[:, 0] + 1e-3 * X[:, 1]
+    if block == "dependent":
+        X[:, b - 1] = X[:, 0] - X[:, 1]
+    g = lib.Graph(lib.Context(0), rp, ci)
+    betas = [0.6 / lam, 0.3 / lam, 0.1 / lam]
+    m = lib.Multi([lib.Operator(g, 0.0, "exp", be, krylov_dim=14, method="lanczos") for be in betas])
+    Xd = torch.tensor(X, dtype=torch.float32, device="cuda")
+    Y = m.apply_phi(Xd)
+    Yf, W = m.apply_fdeg(Xd, laplacian=False)
+    for q, be in enumerate(betas):
+        ref = reference(A, X, 0.0, be)
+        w = reference(A, np.ones((n, 1)), 0.0, be)
+        for out in (Y, Yf):
+            got = out[:, q * b:(q + 1) * b].double().cpu().numpy()
+            assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref), q
+        assert np.linalg.norm(W[:, q:q + 1].double().cpu().numpy() - w) <= 1e-4 * np.linalg.norm(w), q
