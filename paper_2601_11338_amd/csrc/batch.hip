@@ -24,41 +24,49 @@
 
 namespace {
 
-constexpr int UNIT_ROWS = 2048;  // rows per reduction unit (multiple of 16)
+constexpr int UNIT_ROWS = 2048;  // rows per reduction unit (multiple of 64)
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 // Segmented Gram: for every unit u (rows [us[u], us[u+1]) of one graph, a multiple of
-// 16), partial[k][u] = X_k[rows]^T Y[rows] for b <= 16 columns, on the matrix cores
-// (FP64 accumulation, the operand layout of the single-graph Gram).
-template <int NB>
+// 64), partial[k][u] = X_k[rows]^T Y[rows] for b <= 16 columns, on the matrix cores
+// (FP64 accumulation, the operand layout of the single-graph Gram).  One workgroup per unit:
+// its waves take 32 rows in turn (64 up to 8 columns, where the upper half of the 16 operand
+// columns holds the next four rows and the two diagonal 8 x 8 blocks of the result are
+// added), all of whose operands are requested before the first product, and are summed in
+// LDS in a fixed order.  Bound: the blocks' bytes, once enough of them are in flight: with a
+// wave per unit and 16 rows a round, 64 graphs (1.1M rows, 540 units) kept two waves on a CU
+// waiting for 512-byte rounds (8 columns, three blocks 153 us -> 28.5 us, one block 63 -> 10.6).
+template <int NB, bool PACK>
 __global__ __launch_bounds__(256) void k_gram_seg(const int64_t* __restrict__ us, int nunits,
                                                   const float* __restrict__ X, int64_t sX, int nblk,
                                                   const float* __restrict__ Y, int b,
                                                   double* __restrict__ partials) {
+  constexpr int M = 8, STEP = PACK ? 8 : 4, ROWS = M * STEP;  // products and rows of a round
+  __shared__ double red[NB * 256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rsub = lane >> 4, c = lane & 15;
+  const int col = PACK ? c & 7 : c, rofs = rsub + (PACK ? 4 * (c >> 3) : 0);
   const int kb0 = blockIdx.y * NB;
   const int nb = (nblk - kb0) < NB ? (nblk - kb0) : NB;
-  const bool cok = c < b;
-  for (int u = blockIdx.x * 4 + wave; u < nunits; u += gridDim.x * 4) {
+  const bool cok = col < b;
+  const int cc = cok ? col : 0;  // lanes past the block width read column 0 and use zero
+  for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
     v4d acc[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) acc[q] = v4d{0.0, 0.0, 0.0, 0.0};
     const int64_t r0 = us[u], r1 = us[u + 1];
-    const int cc = cok ? c : 0;  // lanes past the block width read column 0 and use zero
-    for (int64_t r = r0; r < r1; r += 16) {
-      // every operand of the 16 rows is requested before the first product (a branch
-      // around each load would wait for it)
-      float yv[4], xv[NB][4];
+    for (int64_t r = r0 + wave * ROWS; r < r1; r += 4 * ROWS) {
+      // (a branch around each load would wait for it)
+      float yv[M], xv[NB][M];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int64_t row = r + 4 * m + rsub;
+      for (int m = 0; m < M; ++m) {
+        const int64_t row = r + STEP * m + rofs;
         yv[m] = Y[row * b + cc];
 #pragma unroll
         for (int q = 0; q < NB; ++q) xv[q][m] = X[(int64_t)(kb0 + min(q, nb - 1)) * sX + row * b + cc];
       }
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
+      for (int m = 0; m < M; ++m) {
         const double yb = cok ? (double)yv[m] : 0.0;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
@@ -67,13 +75,24 @@ __global__ __launch_bounds__(256) void k_gram_seg(const int64_t* __restrict__ us
         }
       }
     }
+    for (int w = 0; w < 4; ++w) {  // the four waves in a fixed order
+      if (wave == w) {
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (q >= nb) break;
-      double* out = partials + ((int64_t)(kb0 + q) * nunits + u) * 256;
+        for (int q = 0; q < NB; ++q)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) out[(4 * v + rsub) * 16 + c] = acc[q][v];
+          for (int v = 0; v < 4; ++v) {
+            const int idx = q * 256 + (4 * v + rsub) * 16 + c;
+            red[idx] = (w == 0 ? 0.0 : red[idx]) + acc[q][v];
+          }
+      }
+      __syncthreads();
     }
+    for (int e = threadIdx.x; e < nb * 256; e += 256) {
+      const int q = e >> 8, i = (e >> 4) & 15, j = e & 15;
+      if (PACK && (i >= 8 || j >= 8)) continue;  // not read for b <= 8
+      partials[((int64_t)(kb0 + q) * nunits + u) * 256 + (e & 255)] = red[e] + (PACK ? red[e + 8 * 16 + 8] : 0.0);
+    }
+    __syncthreads();  // red is written again for the next unit
   }
 }
 
@@ -390,18 +409,16 @@ wl_status batch_gram(wl_batch* bt, BatchWork& wk, const float* X, int64_t sX, in
   wl_ctx* ctx = bt->ctx;
   const int nunits = (int)bt->us.size() - 1;
   WL_TRY(wk.partials.ensure((size_t)nblk * nunits * 256 * sizeof(double)));
-  const int blocks = std::max(1, std::min(1024, (nunits + 3) / 4));
   const int NB = nblk >= 3 ? 3 : nblk;
-  dim3 grid(blocks, (nblk + NB - 1) / NB);
-  if (NB == 1)
-    hipLaunchKernelGGL(k_gram_seg<1>, grid, dim3(256), 0, ctx->stream, bt->d_us.as<int64_t>(), nunits, X, sX, nblk, Y,
-                       b, wk.partials.as<double>());
-  else if (NB == 2)
-    hipLaunchKernelGGL(k_gram_seg<2>, grid, dim3(256), 0, ctx->stream, bt->d_us.as<int64_t>(), nunits, X, sX, nblk, Y,
-                       b, wk.partials.as<double>());
+  dim3 grid(std::max(1, std::min(4096, nunits)), (nblk + NB - 1) / NB);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, ctx->stream, bt->d_us.as<int64_t>(), nunits, X, sX, nblk, Y, b,
+                       wk.partials.as<double>());
+  };
+  if (b <= 8)
+    NB == 1 ? run(k_gram_seg<1, true>) : NB == 2 ? run(k_gram_seg<2, true>) : run(k_gram_seg<3, true>);
   else
-    hipLaunchKernelGGL(k_gram_seg<3>, grid, dim3(256), 0, ctx->stream, bt->d_us.as<int64_t>(), nunits, X, sX, nblk, Y,
-                       b, wk.partials.as<double>());
+    NB == 1 ? run(k_gram_seg<1, false>) : NB == 2 ? run(k_gram_seg<2, false>) : run(k_gram_seg<3, false>);
   WL_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_gram_seg_finalize, dim3(16, nblk, bt->ng), dim3(256), 0, ctx->stream,
                      wk.partials.as<double>(), nunits, bt->d_gu0.as<int>(), b, out, gs);
