@@ -343,6 +343,34 @@ __global__ __launch_bounds__(256) void k_gram_mx(int64_t n, const T* __restrict_
   }
 }
 
+// Coefficient (r, c) of block k: C's, or with a projection step (pj.nbv > 0) what
+// k_lanczos_proj would have written for it, taken from the inner products themselves.
+__device__ __forceinline__ double coef_at(const double* __restrict__ C, const ProjArgs& pj, int b, int k, int r,
+                                          int c) {
+  if (pj.nbv == 0) return C[((int64_t)k * b + r) * b + c];
+  const double* Pk = pj.P + (int64_t)k * b * b;
+  if (k == pj.nbv) return r == c ? 1.0 : 0.0;
+  return k + 1 < pj.nbv ? -Pk[r * b + c] : -(0.5 * (Pk[r * b + c] + Pk[c * b + r]));
+}
+
+// The other results of the projection step (A_j and the block's scale), by workgroup 0.
+__device__ __forceinline__ void proj_outputs(const ProjArgs& pj, int b) {
+  if (pj.nbv == 0 || blockIdx.x != 0) return;
+  const int t = threadIdx.x;
+  const double* Aj = pj.P + (int64_t)(pj.nbv - 1) * b * b;
+  const double* Gp = Aj + (int64_t)b * b;
+  for (int e = t; e < b * b; e += 256) {
+    const int i = e / b, j = e % b;
+    pj.Aout[e] = 0.5 * (Aj[i * b + j] + Aj[j * b + i]);
+  }
+  if (t < 64) {
+    double m = t < b ? fmax(0.0, Gp[t * b + t]) : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (t == 0) *pj.ref = m;
+  }
+}
+
 // Out = (wv ? wv[r] : alpha) Yin + beta sum_k X_k C_k for FP32 blocks whose rows are
 // exactly B floats (B = 4 LPR): LPR lanes hold one row as float4 fragments (coalesced
 // 16-byte accesses across the wave); the row is shared inside its lane group with
@@ -353,7 +381,7 @@ template <int B>
 __global__ __launch_bounds__(256) void k_update_f4(int64_t n, const float* X, int64_t sX, int nblk, int kc,
                                                    const double* __restrict__ C, const float* Yin, double alpha,
                                                    const float* __restrict__ wv, double beta, float* Out,
-                                                   const double* __restrict__ skip) {
+                                                   const double* __restrict__ skip, ProjArgs pj) {
   if (skip && *skip != 0.0) return;  // identity update the caller elides
   constexpr int LPR = B / 4;
   constexpr int RPT = 256 / LPR;  // rows per tile
@@ -363,7 +391,9 @@ __global__ __launch_bounds__(256) void k_update_f4(int64_t n, const float* X, in
   const float tb = (float)beta;
   const bool once = kc >= nblk;
   if (once) {
-    for (int e = threadIdx.x; e < nblk * B * B; e += 256) sC[e] = (float)C[e];
+    for (int e = threadIdx.x; e < nblk * B * B; e += 256)
+      sC[e] = (float)coef_at(C, pj, B, e / (B * B), e / B % B, e % B);
+    proj_outputs(pj, B);
     __syncthreads();
   }
   const int64_t ntiles = (n + RPT - 1) / RPT;
@@ -434,34 +464,6 @@ __global__ __launch_bounds__(256) void k_update_f4(int64_t n, const float* X, in
 // each workgroup writes one 16 x 16 partial.
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int UPD_MFMA_MAXK = 48;
-
-// Coefficient (r, c) of block k: C's, or with a projection step (pj.nbv > 0) what
-// k_lanczos_proj would have written for it, taken from the inner products themselves.
-__device__ __forceinline__ double coef_at(const double* __restrict__ C, const ProjArgs& pj, int b, int k, int r,
-                                          int c) {
-  if (pj.nbv == 0) return C[((int64_t)k * b + r) * b + c];
-  const double* Pk = pj.P + (int64_t)k * b * b;
-  if (k == pj.nbv) return r == c ? 1.0 : 0.0;
-  return k + 1 < pj.nbv ? -Pk[r * b + c] : -(0.5 * (Pk[r * b + c] + Pk[c * b + r]));
-}
-
-// The other results of the projection step (A_j and the block's scale), by workgroup 0.
-__device__ __forceinline__ void proj_outputs(const ProjArgs& pj, int b) {
-  if (pj.nbv == 0 || blockIdx.x != 0) return;
-  const int t = threadIdx.x;
-  const double* Aj = pj.P + (int64_t)(pj.nbv - 1) * b * b;
-  const double* Gp = Aj + (int64_t)b * b;
-  for (int e = t; e < b * b; e += 256) {
-    const int i = e / b, j = e % b;
-    pj.Aout[e] = 0.5 * (Aj[i * b + j] + Aj[j * b + i]);
-  }
-  if (t < 64) {
-    double m = t < b ? fmax(0.0, Gp[t * b + t]) : 0.0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    if (t == 0) *pj.ref = m;
-  }
-}
 
 template <bool GRAM>
 __global__ __launch_bounds__(256) void k_update_mfma16(int64_t n, const float* X, int64_t sX, int nblk,
@@ -942,12 +944,13 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_vupdate(int64_t n, const T* X, int64_t sX, int nblk,
                                                  const double* __restrict__ C, const T* Yin, double alpha,
                                                  const T* __restrict__ wv, double beta, T* Out,
-                                                 double* __restrict__ partials, const double* __restrict__ skip) {
+                                                 double* __restrict__ partials, const double* __restrict__ skip, ProjArgs pj) {
   if (skip && *skip != 0.0) return;
   typedef typename Vec16<T>::type V;
   constexpr int W = Vec16<T>::W;
   __shared__ T sC[VUPD_MAXK];
-  if ((int)threadIdx.x < nblk) sC[threadIdx.x] = (T)C[threadIdx.x];
+  if ((int)threadIdx.x < nblk) sC[threadIdx.x] = (T)coef_at(C, pj, 1, threadIdx.x, 0, 0);
+  proj_outputs(pj, 1);
   __syncthreads();
   const T tb = (T)beta, ta = (T)alpha;
   double dot = 0.0;
@@ -1012,7 +1015,7 @@ template <typename T, int B>
 __global__ __launch_bounds__(256) void k_update(int64_t n, const T* X, int ldx, int64_t sX, int nblk,
                                                 int bx, const double* __restrict__ C, const T* Yin, int ldy,
                                                 double alpha, const T* __restrict__ wv, double beta, T* Out,
-                                                int by, double* __restrict__ gram_partials) {
+                                                int by, double* __restrict__ gram_partials, ProjArgs pj) {
   // rows of the result staged per chunk for the fused Gram (keeps LDS <= 64 KiB)
   constexpr int CHR = (256 * (B + 1) * (int)sizeof(T) <= 65536) ? 256 : 65536 / ((B + 1) * (int)sizeof(T)) / 64 * 64;
   __shared__ T sC[B * B];
@@ -1026,6 +1029,7 @@ __global__ __launch_bounds__(256) void k_update(int64_t n, const T* X, int ldx, 
   for (int q = 0; q < QE; ++q) gacc[q] = 0.0;
   constexpr int P = E >= 256 ? 1 : 256 / E;
   const int64_t ntiles = (n + 255) / 256;
+  proj_outputs(pj, bx);
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t row = t * 256 + tid;
     const bool ok = row < n;
@@ -1036,7 +1040,8 @@ __global__ __launch_bounds__(256) void k_update(int64_t n, const T* X, int ldx, 
       __syncthreads();
       for (int e = tid; e < B * B; e += 256) {
         const int i = e / B, j = e % B;
-        sC[e] = (i < bx && j < by) ? (T)C[((int64_t)k * bx + i) * by + j] : T(0);
+        sC[e] = (i < bx && j < by) ? (T)(pj.nbv > 0 ? coef_at(C, pj, bx, k, i, j) : C[((int64_t)k * bx + i) * by + j])
+                                   : T(0);
       }
       __syncthreads();
       if (ok) {
@@ -1767,8 +1772,10 @@ int fin_grid(int E) {
 // mostly is not needed at all, up to 131072 (1 MB through one CU, about 10 us).
 // A Lanczos step is 8 launches so and was 11: 1.50 -> 1.31 ms for 30 steps of the first,
 // 3.18 -> 3.14 ms for the second.
+// Narrow blocks the same: 2 FP32 columns of 6000 nodes 1.35 -> 1.10 ms for 30 steps, FP64
+// 2 columns of 35k nodes 1.44 -> 1.23.
 bool defer_sum(GramParts* gp, const double* parts, int64_t nparts, int PB, const double* skip) {
-  if (!gp || PB < 8 || PB > 32 || nparts * PB * PB > (skip ? 131072 : 32768)) return false;
+  if (!gp || PB > 32 || nparts * PB * PB > (skip ? 131072 : 32768)) return false;
   gp->p = parts;
   gp->nparts = (int)nparts;
   gp->PB = PB;
@@ -1791,7 +1798,7 @@ void gram_mx(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int nblk, 
 
 template <int B>
 wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64_t sX, int nblk, const void* Y,
-                 int ldy, int bx, int by, double* out, const double* skip = nullptr) {
+                 int ldy, int bx, int by, double* out, const double* skip = nullptr, GramParts* gp = nullptr) {
   constexpr int E = B * B;
   if constexpr (B >= 16) {
     if (isf) {
@@ -1878,6 +1885,7 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
                        isf ? (const float*)Y : nullptr, isf ? nullptr : (const double*)Y, ldy, bx, by,
                        ctx->partials.as<double>());
     WL_HIP(hipGetLastError());
+    if (nblk == 1 && defer_sum(gp, ctx->partials.as<double>(), parts, B, nullptr)) return WL_OK;
     hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,
                        ctx->partials.as<double>(), parts, B, bx, by, out, nullptr);
     WL_HIP(hipGetLastError());
@@ -2062,8 +2070,10 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
       if (done) return WL_OK;
     }
   }
-  if (pj.nbv > 0)  // the other kernels read the projection's coefficients from memory
+  if (pj.nbv > 0 && (bx != by || (B == 4 && nblk > 4))) {  // coefficients from memory
     WL_TRY(launch_lanczos_proj(ctx, bx, pj.nbv, pj.P, pj.Aout, const_cast<double*>(C), pj.ref, 1, 0));
+    pj = ProjArgs();
+  }
   if constexpr (sizeof(T) == 4 && B == 4) {
     const bool al = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Out) |
                       reinterpret_cast<uintptr_t>(Yin)) & 15u) == 0 && (sX % 4) == 0;
@@ -2075,9 +2085,9 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
       const int kc = std::max(1, std::min(nblk, 12288 / (B * B)));
       const size_t lds = (size_t)kc * B * B * sizeof(float);
       hipLaunchKernelGGL((k_update_f4<B>), dim3(grid), dim3(256), lds, ctx->stream, n, (const float*)X, sX, nblk,
-                         kc, C, (const float*)Yin, alpha, (const float*)wv, beta, (float*)Out, skip);
+                         kc, C, (const float*)Yin, alpha, (const float*)wv, beta, (float*)Out, skip, pj);
       WL_HIP(hipGetLastError());
-      if (gram_out) return gram_B<B>(ctx, n, Out, true, B, 0, 1, Out, B, B, B, gram_out, skip_gram);
+      if (gram_out) return gram_B<B>(ctx, n, Out, true, B, 0, 1, Out, B, B, B, gram_out, skip_gram, gp);
       return WL_OK;
     }
   }
@@ -2096,9 +2106,9 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
         parts = ctx->partials.as<double>();
       }
       hipLaunchKernelGGL(k_vupdate<T>, dim3((unsigned)grid), dim3(256), 0, ctx->stream, n, X, sX, nblk, C, Yin,
-                         alpha, wv, beta, Out, parts, skip);
+                         alpha, wv, beta, Out, parts, skip, pj);
       WL_HIP(hipGetLastError());
-      if (gram_out) {
+      if (gram_out && !defer_sum(gp, parts, grid, 1, skip_gram)) {
         hipLaunchKernelGGL(k_gram_finalize, dim3(1, 1), dim3(256), 0, ctx->stream, parts, (int)grid, 1, 1, 1,
                            gram_out, skip_gram);
         WL_HIP(hipGetLastError());
@@ -2115,9 +2125,9 @@ wl_status update_B(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int 
     parts = ctx->partials.as<double>();
   }
   hipLaunchKernelGGL((k_update<T, B>), dim3(grid), dim3(256), 0, ctx->stream, n, X, ldx, sX, nblk, bx, C, Yin, ldy,
-                     alpha, wv, beta, Out, by, parts);
+                     alpha, wv, beta, Out, by, parts, pj);
   WL_HIP(hipGetLastError());
-  if (gram_out) {
+  if (gram_out && !defer_sum(gp, parts, grid, B, nullptr)) {
     hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), 1), dim3(256), 0, ctx->stream, parts, grid, B, by, by,
                        gram_out, nullptr);
     WL_HIP(hipGetLastError());
@@ -2190,7 +2200,7 @@ wl_status launch_chol(wl_ctx* ctx, int b, const double* G, double tol, const dou
                       const double* skip_in, int dg, const double* dref, const GramParts* gp, const NextArgs& nx) {
   WL_CHECK(b >= 1 && b <= 64 && ngraphs >= 1, WL_EINVAL, "chol: b out of range");
   const bool sum = gp && gp->nparts > 0;
-  WL_CHECK((!sum && !nx.Nnext) || (sum && b > gp->PB / 2 && b <= gp->PB && gp->PB >= 8 && gp->PB <= 32 && (!nx.Nnext || b == 16)),
+  WL_CHECK((!sum && !nx.Nnext) || (sum && b > gp->PB / 2 && b <= gp->PB && gp->PB <= 32 && (!nx.Nnext || b == 16)),
            WL_EINTERNAL,
            "chol: partial sums of another shape");
   auto run = [&](auto kernel, int threads) {
