@@ -433,8 +433,9 @@ def run_batch512(args):
     alg = 0.0
     for k in range(1, int(Kg.max()) + 1):
         act = Kg >= k
-        streams = 4 if k == 1 else 5
-        alg += float((4 * nnz[act] + 4 * npad[act] + 4 * b * npad[act] * streams).sum())
+        # gathered block, P_k, P_{k-2}; the running sum only where it takes terms
+        streams = (2 if k == 1 else 3) + 2 * ((Kg - k) % 4 <= 1)
+        alg += float((4 * nnz[act] + 4 * npad[act] + 4 * b * npad[act] * streams[act]).sum())
         fin = Kg == k
         alg += float((4 * b * npad[fin] + 4 * npad[fin]).sum())
     alg *= K_out * args.steps
