@@ -878,7 +878,7 @@ wl_status recombine(wl_graph* g, const T* basis, int b, int K, const std::vector
 // Coefficients of exp(-t x) on [lo, hi] in Chebyshev polynomials of the interval,
 // e^{-t lo} e^{-z} (2 - [k = 0]) (-1)^k I_k(z) with z = t (hi - lo) / 2: ratios I_k / I_{k-1} by
 // the backward recurrence, scaled by e^{-z} (I_0 + 2 sum I_k) = 1.  Degree about 9 sqrt(z) (the
-// coefficients fall like exp(-k^2 / 2z) and end below 1e-19).
+// coefficients fall like exp(-k^2 / 2z) and end below 1e-19 of e^{-t lo}).
 std::vector<double> cheb_exp_coeffs(double t, double lo, double hi) {
   const double z = 0.5 * t * (hi - lo);
   const int deg = (int)std::ceil(9.1 * std::sqrt(z)) + 24;
@@ -892,10 +892,10 @@ std::vector<double> cheb_exp_coeffs(double t, double lo, double hi) {
     sum += 2.0 * p;
     c[k] = k & 1 ? -2.0 * p : 2.0 * p;
   }
+  c[0] = 1.0;
+  while (c.size() > 2 && std::fabs(c.back()) < 1e-19 * sum) c.pop_back();
   const double scale = std::exp(-t * lo) / sum;
-  c[0] = scale;
-  for (int k = 1; k <= deg; ++k) c[k] *= scale;
-  while (c.size() > 2 && std::fabs(c.back()) < 1e-19) c.pop_back();
+  for (double& v : c) v *= scale;
   return c;
 }
 
@@ -1139,6 +1139,66 @@ wl_status phi_apply_impl(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
 template wl_status phi_apply_impl<float>(wl_op*, const float*, float*, int, const float*, const float*);
 template wl_status phi_apply_impl<double>(wl_op*, const double*, double*, int, const double*, const double*);
 
+// Does the spectrum of the block tridiagonal T suit a Chebyshev series of exp(-t T) on [lo, hi]
+// for all times up to tmax?  Below lo the series grows faster than its coefficients fall, and
+// its rounding is that of e^{-t lo}, so for lambda_min(T) far above lo a small result drowns in
+// it (four cliques of 40 to 43 nodes, mean-free start, e^{-t lambda} = 1e-22: error 1e-14).  Hence
+// T - lo must be positive definite (by its Cholesky factors) and a Rayleigh quotient (inverse
+// iteration, an upper bound of lambda_min) at most 4 / tmax above lo.  Where it is not, lo moves up
+// to 2 / tmax below the quotient, if T - lo stays definite.  Returns 0: lo holds, 1: lo was
+// moved, 2: no interval found.  Deflated basis columns (zero rows of T) are left out.
+// 2 ms of host work at K = 40, b = 32, beside the first series on the device.
+static int exp_interval(int K, int b, const std::vector<double>& hA, const std::vector<double>& hB, double hi,
+                        double tmax, double* lo) {
+  const int m = K * b, bb = b * b;
+  std::vector<char> zero(m, 1);
+  for (int j = 0; j < K; ++j)
+    for (int r = 0; r < b; ++r)
+      for (int c = 0; c < b; ++c) {
+        const bool nz = hA[(size_t)j * bb + r * b + c] != 0.0 || hA[(size_t)j * bb + c * b + r] != 0.0 ||
+                        (j > 0 && hB[(size_t)(j - 1) * bb + r * b + c] != 0.0) ||
+                        (j + 1 < K && hB[(size_t)j * bb + c * b + r] != 0.0);
+        if (nz) zero[j * b + r] = 0;
+      }
+  BlockTridiagChol F;
+  auto definite = [&](double shift) {
+    std::vector<double> Ad(hA.begin(), hA.begin() + (size_t)K * bb);
+    for (int i = 0; i < m; ++i) {
+      double& d = Ad[(size_t)(i / b) * bb + (i % b) * (b + 1)];
+      d = zero[i] ? hi : d - shift;
+    }
+    return F.factor(K, b, Ad.data(), hB.data()) == 0;
+  };
+  if (!definite(*lo)) return 2;
+  std::vector<double> r(m), y(m);
+  uint32_t seed = 1;
+  for (int i = 0; i < m; ++i) {
+    seed = seed * 1664525u + 1013904223u;
+    r[i] = zero[i] ? 0.0 : (double)(int32_t)seed;
+  }
+  double gap = 0.0;  // Rayleigh quotient of T - lo
+  for (int it = 0; it < 8; ++it) {
+    double nr = 0.0, yr = 0.0, yy = 0.0;
+    for (double v : r) nr += v * v;
+    if (!(nr > 0.0)) return 0;  // T = 0
+    nr = 1.0 / std::sqrt(nr);
+    for (double& v : r) v *= nr;
+    y = r;
+    F.solve(1, y.data());
+    for (int i = 0; i < m; ++i) {
+      yr += y[i] * r[i];
+      yy += y[i] * y[i];
+    }
+    gap = yr / yy;
+    if (gap * tmax <= 4.0) return 0;
+    r = y;
+  }
+  const double up = *lo + gap - 2.0 / tmax;
+  if (!(up < hi) || !definite(up)) return 2;
+  *lo = up;
+  return 1;
+}
+
 constexpr int EXPV_CHEB_M = 100;       // rows of T from which the series runs on the device
 constexpr double EXPV_CHEB_Z = 4e4;    // t ||T|| / 2 up to which its degree (9 sqrt z) stays below 2000
 
@@ -1177,9 +1237,9 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
   };
   // exp(-t T) E_1 R0 as a Chebyshev series on the device where T is large (the host's
   // eigendecomposition takes 9 m^3 operations: 105 ms at m = 1280, against 2.4 ms for the
-  // three times 0.1, 1, 10) and the degree moderate.  The interval ends just below 0: L is
-  // positive semidefinite, and a Ritz value pushed below 0 by rounding stays next to it.  The
-  // work blocks lie in memory that the basis no longer needs, so no call needs more of it.
+  // three times 0.1, 1, 10) and the degree moderate, on an interval that starts just below 0 (L
+  // is positive semidefinite) unless T says otherwise.  The work blocks lie in memory that
+  // the basis no longer needs, so no call needs more of it.
   const double tmax = *std::max_element(t, t + nt), hi = block_tridiag_norm(Ke, b, hA, hB);
   if (m >= EXPV_CHEB_M && hi > 0.0 && is_finite(hi) && 0.5 * tmax * hi <= EXPV_CHEB_Z &&
       (size_t)n * sizeof(T) >= (size_t)m * sizeof(double)) {
@@ -1188,22 +1248,30 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
     double *X0 = S + Ly.P(), *X1 = op->outer_w.as<double>();  // m b doubles each
     WL_TRY(op->outer_coef.ensure((size_t)m * b * sizeof(double)));
     std::vector<double> last((size_t)nt * b * b);
-    for (int it = 0; it < nt; ++it) {
-      const double lo = t[it] > 0.0 ? -std::min(0.01 * hi, 1.0 / t[it]) : -0.01 * hi;
+    double lo = tmax > 0.0 ? -std::min(0.01 * hi, 1.0 / tmax) : -0.01 * hi;
+    int fits = tmax > 0.0 ? -1 : 0;  // not known yet
+    for (int it = 0; it < nt && fits < 2; ++it) {
       std::vector<double> c = t[it] > 0.0 ? cheb_exp_coeffs(t[it], lo, hi) : std::vector<double>{1.0, 0.0};
       WL_TRY(launch_cheb(g->ctx, b, Ke, S + Ly.A(0), S + Ly.B(0), S + Ly.R0(), 2.0 / (hi - lo), (hi + lo) / (hi - lo),
                          c, X0, X1, op->outer_coef.as<double>()));
+      WL_TRY(recombine_device<T>(g, op->outer_basis.as<T>(), b, Ke, op->outer_coef.as<double>(), nullptr, nullptr,
+                                 Y[it]));
+      if (fits < 0) {
+        fits = exp_interval(Ke, b, hA, hB, hi, tmax, &lo);
+        if (fits == 1) it = -1;  // again from the first time, on the new interval
+        if (fits != 0) continue;
+      }
       if (err_est && Ke == K)
         WL_HIP(hipMemcpyAsync(&last[(size_t)it * b * b], op->outer_coef.as<double>() + (size_t)(K - 1) * b * b,
                               (size_t)b * b * 8, hipMemcpyDeviceToHost, g->ctx->stream));
-      WL_TRY(recombine_device<T>(g, op->outer_basis.as<T>(), b, Ke, op->outer_coef.as<double>(), nullptr, nullptr,
-                                 Y[it]));
     }
-    if (err_est) {
-      WL_HIP(hipStreamSynchronize(g->ctx->stream));
-      for (int it = 0; it < nt; ++it) err_est[it] = Ke == K ? residual(&last[(size_t)it * b * b]) : 0.0;
+    if (fits < 2) {
+      if (err_est) {
+        WL_HIP(hipStreamSynchronize(g->ctx->stream));
+        for (int it = 0; it < nt; ++it) err_est[it] = Ke == K ? residual(&last[(size_t)it * b * b]) : 0.0;
+      }
+      return WL_OK;
     }
-    return WL_OK;
   }
   std::vector<double> Tm = assemble_T(Ke, b, hA, hB);
   // T = U diag(lam) U^T in factored form (U is applied to blocks, never formed)

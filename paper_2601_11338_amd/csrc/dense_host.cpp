@@ -457,9 +457,13 @@ void ltsolve(int b, const double* L, double* X, int nrhs) {
 }
 }  // namespace
 
-int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const double* B, int nrhs, double* X) {
+int BlockTridiagChol::factor(int K_, int b_, const double* Ad, const double* Bo) {
+  K = K_;
+  b = b_;
   const int bb = b * b;
-  std::vector<double> L((size_t)K * bb), Mb((size_t)K * bb, 0.0);
+  L.assign((size_t)K * bb, 0.0);
+  M.assign((size_t)K * bb, 0.0);
+  std::vector<double> Bt(bb);
   for (int j = 0; j < K; ++j) {
     double* Lj = &L[(size_t)j * bb];
     std::memcpy(Lj, Ad + (size_t)j * bb, sizeof(double) * bb);
@@ -467,8 +471,7 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
       for (int c = r + 1; c < b; ++c) Lj[r * b + c] = Lj[c * b + r] = 0.5 * (Lj[r * b + c] + Lj[c * b + r]);
     if (j > 0) {
       // M_j = B_{j-1} L_{j-1}^{-T}:  solve M L^T = B  <=>  L M^T = B^T
-      double* Mj = &Mb[(size_t)j * bb];
-      std::vector<double> Bt(bb);
+      double* Mj = &M[(size_t)j * bb];
       const double* Bj = Bo + (size_t)(j - 1) * bb;
       for (int r = 0; r < b; ++r)
         for (int c = 0; c < b; ++c) Bt[r * b + c] = Bj[c * b + r];
@@ -476,7 +479,7 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
       for (int r = 0; r < b; ++r)
         for (int c = 0; c < b; ++c) Mj[r * b + c] = Bt[c * b + r];
       for (int r = 0; r < b; ++r)
-        for (int c = 0; c < b; ++c) {
+        for (int c = 0; c <= r; ++c) {  // (the factorisation reads the lower triangle)
           double s = 0.0;
           for (int k = 0; k < b; ++k) s += Mj[r * b + k] * Mj[c * b + k];
           Lj[r * b + c] -= s;
@@ -484,12 +487,16 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
     }
     if (chol_lower(b, Lj)) return 1;
   }
-  std::memcpy(X, B, sizeof(double) * (size_t)K * b * nrhs);
+  return 0;
+}
+
+void BlockTridiagChol::solve(int nrhs, double* X) const {
+  const int bb = b * b;
   for (int j = 0; j < K; ++j) {
     double* xj = X + (size_t)j * b * nrhs;
     if (j > 0) {
       const double* xp = X + (size_t)(j - 1) * b * nrhs;
-      const double* Mj = &Mb[(size_t)j * bb];
+      const double* Mj = &M[(size_t)j * bb];
       for (int r = 0; r < b; ++r)
         for (int c = 0; c < nrhs; ++c) {
           double s = 0.0;
@@ -503,7 +510,7 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
     double* xj = X + (size_t)j * b * nrhs;
     if (j + 1 < K) {
       const double* xn = X + (size_t)(j + 1) * b * nrhs;
-      const double* Mn = &Mb[(size_t)(j + 1) * bb];
+      const double* Mn = &M[(size_t)(j + 1) * bb];
       for (int r = 0; r < b; ++r)
         for (int c = 0; c < nrhs; ++c) {
           double s = 0.0;
@@ -513,6 +520,13 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
     }
     ltsolve(b, &L[(size_t)j * bb], xj, nrhs);
   }
+}
+
+int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const double* B, int nrhs, double* X) {
+  BlockTridiagChol F;
+  if (F.factor(K, b, Ad, Bo)) return 1;
+  std::memcpy(X, B, sizeof(double) * (size_t)K * b * nrhs);
+  F.solve(nrhs, X);
   return 0;
 }
 

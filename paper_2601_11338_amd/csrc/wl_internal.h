@@ -481,6 +481,15 @@ void host_chol_deflate(int M, const std::vector<double>& G, double tol, double r
                        std::vector<double>& Rinv, std::vector<char>& keep);
 // Eigenvalues only of a symmetric tridiagonal matrix (diag a, offdiag b).
 int tridiag_eigvals(int m, const double* a, const double* b, double* lam);
+// Cholesky factors of the symmetric part of a block tridiagonal matrix (K diagonal blocks Ad,
+// T_{j+1,j} = Bo_j; b x b row-major).  factor: nonzero where it is not positive definite; solve:
+// X (K b x nrhs) <- T^{-1} X.
+struct BlockTridiagChol {
+  int K = 0, b = 0;
+  std::vector<double> L, M;
+  int factor(int K, int b, const double* Ad, const double* Bo);
+  void solve(int nrhs, double* X) const;
+};
 // Solve T X = B for block tridiagonal SPD T (K diagonal blocks Ad, K-1 off-diagonal
 // blocks Bo with T_{j+1,j} = Bo_j), blocks b x b row-major; B, X are (K*b) x nrhs.
 int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const double* B, int nrhs, double* X);
