@@ -242,10 +242,17 @@ __global__ void k_dtranspose_batched(int b, const double* __restrict__ x, double
 // e^{-t lo} sum_k c_k T_k(x), c_k = 2 e^{-z} I_k(z) (-1)^k, z = t (hi - lo) / 2, of degree about
 // 9 sqrt(z), in substeps of z <= EXP_ZMAX.  Bound: latency of one product with T per term (a
 // Taylor series needed about 18 t ||T|| products: 64 graphs, K = 30, b = 8, t up to 10,
-// 20.4 ms; this 0.96 ms).
+// 20.4 ms; this 0.95 ms).
+// The rounding of a substep is that of its start, so a substep whose largest entry falls below
+// EXP_DROP of that (a start block without T's slow directions: all of it decays) is made again in
+// halves; halves grow together where the decay has ended.  Times beyond EXP_MAXSTEPS
+// substeps (t ||T|| = 4e8, where everything that is not null to FP32 rounding has decayed)
+// count as that.
 constexpr int EXP_MAXM = 512;  // K b
 constexpr int EXP_MAXDEG = 480;
-constexpr double EXP_ZMAX = 2000.0;
+constexpr double EXP_ZMAX = 2000.0, EXP_MAXSTEPS = 1e5;
+constexpr double EXP_DROP = 1e-5;
+constexpr double EXP_ZMIN = 4.0;  // (e^{-2 z} > EXP_DROP from here down)
 __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double* __restrict__ S, int64_t gs,
                                                       int64_t offA, int64_t offB, int64_t offR0,
                                                       const double* __restrict__ tvals, double* __restrict__ F,
@@ -293,35 +300,52 @@ __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double
   }
   if (t == 0) snorm = red[0];
   __syncthreads();
-  const double tv = tvals[g], hi = snorm;
-  if (tv > 0.0 && hi > 0.0) {
-    const double lo = -fmin(0.01 * hi, 1.0 / tv);
-    const int steps = (int)fmin(1e6, fmax(1.0, ceil(tv * (hi - lo) / (2.0 * EXP_ZMAX))));
-    const double z = tv * (hi - lo) / (2.0 * steps), al = 2.0 / (hi - lo), be = (hi + lo) / (hi - lo);
-    if (t == 0) {
-      // ratios I_k / I_{k-1} by the backward recurrence, then e^{-z} (I_0 + 2 sum I_k) = 1
-      const int deg = (int)fmin((double)(EXP_MAXDEG - 1), ceil(9.1 * sqrt(z)) + 24.0);
-      double r = 0.0;
-      for (int k = deg + 32; k > deg; --k) r = 1.0 / (2.0 * k / z + r);
-      for (int k = deg; k > 0; --k) coef[k] = r = 1.0 / (2.0 * k / z + r);
-      double p = 1.0, sum = 1.0;
-      for (int k = 1; k <= deg; ++k) {
-        p *= coef[k];
-        sum += 2.0 * p;
-        coef[k] = k & 1 ? -2.0 * p : 2.0 * p;
-      }
-      const double scale = exp(-tv / steps * lo) / sum;
-      coef[0] = scale;
-      int last = deg;
-      for (int k = 1; k <= deg; ++k) coef[k] *= scale;
-      while (last > 1 && fabs(coef[last]) < 1e-19) --last;
-      slast = last;
-    }
+  // max |entry| of sV in all threads (every thread calls)
+  auto max_entry = [&]() {
+    double m = 0.0;
+    for (int e = t; e < mb; e += 256) m = fmax(m, fabs(sV[e]));
+    __syncthreads();  // red may still be read
+    red[t] = m;
     __syncthreads();
-    const int last = slast;
-    for (int st = 0; st < steps; ++st) {
+    for (int h = 128; h > 0; h >>= 1) {
+      if (t < h) red[t] = fmax(red[t], red[t + h]);
+      __syncthreads();
+    }
+    return red[0];
+  };
+  double* Fg = F + (int64_t)g * fgs;
+  const double hi = snorm;
+  if (tvals[g] > 0.0 && hi > 0.0) {
+    const double lo = -fmin(0.01 * hi, 1.0 / tvals[g]), al = 2.0 / (hi - lo), be = (hi + lo) / (hi - lo);
+    const double ztot = fmin(0.5 * tvals[g] * (hi - lo), EXP_ZMAX * EXP_MAXSTEPS);
+    int todo = (int)ceil(ztot / EXP_ZMAX);  // substeps left, of z each
+    double z = ztot / todo, v0 = max_entry();
+    bool fresh = true;
+    while (todo > 0 && v0 > 0.0 && v0 < INFINITY) {
+      if (fresh && t == 0) {
+        // ratios I_k / I_{k-1} by the backward recurrence, then e^{-z} (I_0 + 2 sum I_k) = 1
+        const int deg = (int)fmin((double)(EXP_MAXDEG - 1), ceil(9.1 * sqrt(z)) + 24.0);
+        double r = 0.0;
+        for (int k = deg + 32; k > deg; --k) r = 1.0 / (2.0 * k / z + r);
+        for (int k = deg; k > 0; --k) coef[k] = r = 1.0 / (2.0 * k / z + r);
+        double p = 1.0, sum = 1.0;
+        for (int k = 1; k <= deg; ++k) {
+          p *= coef[k];
+          sum += 2.0 * p;
+          coef[k] = k & 1 ? -2.0 * p : 2.0 * p;
+        }
+        const double scale = exp(-z * al * lo) / sum;
+        coef[0] = scale;
+        int last = deg;
+        for (int k = 1; k <= deg; ++k) coef[k] *= scale;
+        while (last > 1 && fabs(coef[last]) < 1e-19) --last;
+        slast = last;
+      }
+      __syncthreads();
+      const int last = slast;
       for (int e = t; e < mb; e += 256) {
         const double v = sV[e];
+        Fg[e] = v;  // where the substep starts
         sT[e] = v;  // T_0
         sV[e] = coef[0] * v;
       }
@@ -346,9 +370,25 @@ __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double
         sT = sU;
         sU = w;
       }
+      const double v1 = max_entry();
+      fresh = false;
+      if (v1 < EXP_DROP * v0 && z > EXP_ZMIN) {  // again from its start, in halves
+        for (int e = t; e < mb; e += 256) sV[e] = Fg[e];
+        __syncthreads();
+        z *= 0.5;
+        todo *= 2;
+        fresh = true;
+        continue;
+      }
+      --todo;
+      if (v1 > 0.01 * v0 && todo > 0 && todo % 2 == 0 && 2.0 * z <= EXP_ZMAX) {
+        z *= 2.0;
+        todo /= 2;
+        fresh = true;
+      }
+      v0 = v1;
     }
   }
-  double* Fg = F + (int64_t)g * fgs;
   for (int e = t; e < mb; e += 256) Fg[e] = sV[e];
 }
 

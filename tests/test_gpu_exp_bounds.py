@@ -51,6 +51,25 @@ def test_expv_far_below_the_start(lib, b, t):
         assert np.linalg.norm(o.cpu().numpy() - ref) <= 5e-7 * np.linalg.norm(ref), s
 
 
+# FP32: rates good to a few 6e-8, times t lambda <= 60
+@pytest.mark.parametrize("b", [2, 8])
+def test_batch_far_below_the_start(lib, b):
+    sizes, ctx = [64, 50, 129, 64], lib.Context(0)
+    tl = [0.0, 20.0, 45.0, 60.0]
+    graphs, descs, U, refs, ts = [], [], [], [], []
+    for i, (s, x) in enumerate(zip(sizes, tl)):
+        graphs.append(lib.Graph(ctx, *cliques([s])))
+        descs.append(dict(mu=0.0, func="exp", param=1.0 / s))
+        U.append(mean_free([s], b, i))
+        rate = clique_rates([s], 1.0 / s)[0]
+        ts.append(x / rate)
+        refs.append(np.exp(-x) * U[-1])
+    batch = lib.Batch(ctx, graphs, descs)
+    Y, _, _ = batch.expv(batch.pack([torch.tensor(u, dtype=torch.float32, device="cuda") for u in U]), ts, outer_dim=10)
+    for ref, x, y in zip(refs, tl, batch.unpack(Y)):
+        assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-4 * np.linalg.norm(ref), x
+
+
 # phi by 5 inner steps is not entrywise positive: T has an eigenvalue -4e-3, which the last time
 # leaves outside the interval.  The reference is the same process in 64 bits.
 @pytest.mark.parametrize("b,dim", [(10, 8), (20, 8)])  # 80 rows on the host, 160 on the device
