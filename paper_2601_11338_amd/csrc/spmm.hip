@@ -336,11 +336,14 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
   for (int i = 0; i < VW; ++i) y[i] = a * acc.v[i];
   Frag<T, VW> z;
   zero(z);
-  if (ep.Z && (cb0 != 0.0 || cb1 != 0.0 || csz != 0.0)) {
-    const T coef = (T)(cb0 + cb1 * (double)deg);
+  const bool zy = cb0 != 0.0 || cb1 != 0.0;  // (0 x infinity is not nothing)
+  if (ep.Z && (zy || csz != 0.0)) {
     z = ldf_m<T, VW, MASK>(ep.Z + off, true);
+    if (zy) {
+      const T coef = (T)(cb0 + cb1 * (double)deg);
 #pragma unroll
-    for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
+      for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
+    }
   }
   if constexpr ((E & EPI_NFAC) != 0 && VW > 1) right_factor<T, VW>(y, cl, TILE, sN);
   if (ep.C) c_term<T, VW>(r, ld, b, col, cl, TILE, ep, sC, y);
@@ -362,7 +365,11 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
       zero(s);
     const T s0 = (T)ep.s0, sc = (T)csc, sz = (T)csz;
 #pragma unroll
-    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i] + sz * z.v[i];
+    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i];
+    if (csz != 0.0) {
+#pragma unroll
+      for (int i = 0; i < VW; ++i) s.v[i] += sz * z.v[i];
+    }
     if (fin) {
       const T wr = ep.wld ? ep.wv[r * (int64_t)ep.wld + col / ep.cgw] : ep.wv[r];
       Frag<T, VW> xw = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Xw + off, true) : ldf_nt<T, VW>(ep.Xw + off);
