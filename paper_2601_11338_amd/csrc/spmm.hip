@@ -251,6 +251,10 @@ __device__ __forceinline__ void epilogue_cols(int64_t r, int ld, int b, int col,
     for (int i = 0; i < VW; ++i) o.v[i] = y[i];
     stf<T, VW>(Y + off, o);
   }
+  // The deferred-normalisation products form no running sum; without its registers they fit the
+  // 64 of the launch bound (with them four were spilled: a 32-wide product on 1M nodes of degree
+  // 10, 255.8 us; now 244.1).
+  if constexpr (NF) return;
   int src[VW];  // where each column's running sum comes from
   bool any = false, from_y = false, from_x = false;
 #pragma unroll
@@ -422,10 +426,15 @@ constexpr int gather_unroll() {
   return VW == 1 && sizeof(T) == 4 ? 16 : 8;
 }
 
-// Eight waves per SIMD in FP32 (64 VGPRs; 72 to 90 are taken when left free): the gathers
-// are latency-bound, and a wave fewer costs more than the tighter registers (96 columns of
-// 1M nodes: 752 us a step at 72 VGPRs, 714 at 64; with the row streams requested ahead of
-// their use 84 VGPRs and 894 us).  FP64 blocks need twice the registers.
+// Eight waves per SIMD in FP32 (64 VGPRs; 60 to 90 are taken when left free): the gathers
+// are latency-bound, and a wave fewer costs more than the tighter registers.  Measured on 1M
+// nodes of degree 10, ms for a whole evaluation of 30 terms or steps at 64 / 72 VGPRs (E as
+// below): E = 0, 5 operators of 16 columns 19.1 / 19.7; EPI_NFAC, the same 51.7 / 53.3;
+// EPI_COLS | EPI_NFAC, 1 operator and its walk degrees 13.7 / 13.7, 5 operators 56.3 / 56.5;
+// EPI_COLS, 5 operators and their walk degrees 21.6 / 23.2.  The last kind spills 4
+// registers in its epilogue all the same; forms that do not were slower (21.9 with one source vector
+// for both sources of the running sum, 24.9 with Z read again).  FP64 blocks need twice the
+// registers.
 template <typename T, int VW, int LPN, int G, bool MASK, int E>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void k_spmm(const int32_t* __restrict__ rowptr,
                                               const int32_t* __restrict__ colidx, int64_t n, int ld, int b,
@@ -549,6 +558,8 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
     }
     n_long = lo;
   }
+  WL_CHECK(!ep.Nm || (VW == 4 && !(ep.cmap && ep.Sout)), WL_EINTERNAL,
+           "spmm: the deferred-normalisation factor needs FP32 16-byte vectors and takes no running sum");
   constexpr int RPB = 256 / G;
   int64_t nshort = (g->n + RPB - 1) / RPB;
   EpiArgs<T> epx = ep;
@@ -573,10 +584,6 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
     else if (ep.Nm)
       hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, EPI_NFAC>), grid, dim3(256), lds, ctx->stream, g->rowptr,
                          g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
-  }
-  if (ep.Nm && VW != 4) {
-    wl_set_error("spmm: the deferred-normalisation factor needs FP32 16-byte vectors");
-    return WL_EINTERNAL;
   }
   constexpr bool COLS = !(sizeof(T) == 4 && VW == 2);  // 8-byte FP32 vectors are not chosen with cmap
   if constexpr (COLS) {
