@@ -1796,6 +1796,28 @@ void gram_mx(wl_ctx* ctx, int64_t n, const T* X, int ldx, int64_t sX, int nblk, 
                        ldx, sX, nblk, Y, ldy, bx, by, B, ctx->partials.as<double>());
 }
 
+// Partial sums per block that a Gram of nblk blocks leaves (gram_partials_bound plans by the
+// same functions).  FP32 blocks of 16 to 64 columns: row sets of k_gram_mfma, a multiple of the 8
+// XCDs; up to 1024 workgroups in all, and 256 per group of blocks (every row set writes one FP64
+// partial per block, which for many wide blocks is a fair share of the blocks' own bytes: 20
+// blocks of 32 columns, 262k rows, 168 MB at 1024 row sets beside 700 MB; 288 us -> 238, the
+// reduction behind it 13.5 -> 6.4).
+int64_t gram_row_sets(int64_t n, int B, int nblk) {
+  const int64_t sets = ((n + 15) / 16 + 15) / 16;
+  const int64_t groups = B >= 64 ? nblk : B == 32 || nblk == 2 ? (nblk + 1) / 2 : (nblk + 2) / 3;
+  return (std::max<int64_t>(1, std::min(sets, std::max<int64_t>(256, 1024 / groups))) + 7) / 8 * 8;
+}
+// The other blocks: k_gram_mx from five columns on, a wave per 16-row chunk up to 256 workgroups,
+// then four chunks per wave (5000 rows of 5: 9.0 us with four from the start, 5.5 us so); below,
+// a 32-row tile each.  2^22 entries in all, between 32 and 512 per block.
+int64_t gram_parts(int64_t n, int B, int nblk) {
+  const int64_t cap = std::min<int64_t>(512, std::max<int64_t>(32, ((int64_t)1 << 22) / ((int64_t)B * B * nblk)));
+  if (B < 8) return std::max<int64_t>(1, std::min((n + GRAM_TR - 1) / GRAM_TR, cap));
+  int64_t parts = std::min(cap, std::max((n + 255) / 256, std::min<int64_t>((n + 63) / 64, 256)));
+  if (parts > 8) parts = parts / 8 * 8;
+  return std::max<int64_t>(1, parts);
+}
+
 template <int B>
 wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64_t sX, int nblk, const void* Y,
                  int ldy, int bx, int by, double* out, const double* skip = nullptr, GramParts* gp = nullptr) {
@@ -1804,16 +1826,7 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
     if (isf) {
       // matrix-core path, FP64 accumulation
       constexpr int NT = B / 16;
-      const int64_t nchunks = (n + 15) / 16;
-      int64_t blocks = (nchunks + 15) / 16;
-      // row sets: a multiple of the 8 XCDs; up to 1024 workgroups in all, and 256 per group
-      // of blocks (every row set writes one FP64 partial per block, which for many wide blocks
-      // is a fair share of the blocks' own bytes: 20 blocks of 32 columns, 262k rows, 168 MB
-      // at 1024 row sets beside 700 MB; 288 us -> 238, the reduction behind it 13.5 -> 6.4)
-      const int64_t groups = NT >= 4 ? nblk : NT == 2 || nblk == 2 ? (nblk + 1) / 2 : (nblk + 2) / 3;
-      blocks = std::min(blocks, std::max<int64_t>(256, 1024 / groups));
-      if (blocks < 1) blocks = 1;
-      blocks = (blocks + 7) / 8 * 8;
+      const int64_t blocks = gram_row_sets(n, B, nblk);
       const int nparts = (int)blocks;  // one partial per row set and block
       WL_TRY(ctx->partials.ensure((size_t)nparts * nblk * E * sizeof(double)));
       double* pp = ctx->partials.as<double>();
@@ -1860,16 +1873,8 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
       return WL_OK;
     }
   }
-  const int64_t ntiles = (n + GRAM_TR - 1) / GRAM_TR;
-  int64_t cap = (int64_t)(1 << 22) / ((int64_t)E * nblk);
-  if (cap < 32) cap = 32;
-  if (cap > 512) cap = 512;
+  const int64_t parts = gram_parts(n, B, nblk);
   if constexpr (B >= 8) {
-    // a wave per 16-row chunk up to 256 workgroups, then four chunks per wave (5000 rows of 5:
-    // 9.0 us with four from the start, 5.5 us so)
-    int64_t parts = std::min(cap, std::max((n + 255) / 256, std::min<int64_t>((n + 63) / 64, 256)));
-    if (parts > 8) parts = parts / 8 * 8;
-    if (parts < 1) parts = 1;
     WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
     if (isf)
       gram_mx<float, B>(ctx, n, (const float*)X, ldx, sX, nblk, (const float*)Y, ldy, bx, by, (int)parts);
@@ -1881,10 +1886,8 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
     WL_HIP(hipGetLastError());
     return WL_OK;
   } else {
-    int parts = (int)(ntiles < cap ? ntiles : cap);
-    if (parts < 1) parts = 1;
     WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
-    dim3 grid(parts, nblk);
+    dim3 grid((unsigned)parts, nblk);
     hipLaunchKernelGGL(k_gram_partial<B>, grid, dim3(256), 0, ctx->stream, n,
                        isf ? (const float*)X : nullptr, isf ? nullptr : (const double*)X, ldx, sX,
                        isf ? (const float*)Y : nullptr, isf ? nullptr : (const double*)Y, ldy, bx, by,
@@ -1892,7 +1895,7 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
     WL_HIP(hipGetLastError());
     if (nblk == 1 && defer_sum(gp, ctx->partials.as<double>(), parts, B, nullptr)) return WL_OK;
     hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,
-                       ctx->partials.as<double>(), parts, B, bx, by, out, nullptr);
+                       ctx->partials.as<double>(), (int)parts, B, bx, by, out, nullptr);
     WL_HIP(hipGetLastError());
     return WL_OK;
   }
@@ -2355,6 +2358,11 @@ size_t gram_partials_bound(int64_t n, int prec, int b, int nblk) {
   const int64_t ntiles = std::max<int64_t>(1, (n + GRAM_TR - 1) / GRAM_TR);
   const int64_t cap = std::min<int64_t>(512, std::max<int64_t>(32, ((int64_t)1 << 22) / (E * nblk)));
   doubles = std::max<int64_t>(doubles, std::min(ntiles, cap) * nblk * E);
+  // the sums as taken, of every number of blocks up to nblk (their product is not monotone:
+  // the caps round down and the row sets up to 8)
+  for (int k = 1; k <= nblk; ++k)
+    doubles = std::max(doubles, (prec == WL_FP32 && B >= 16 ? gram_row_sets(n, (int)B, k) : gram_parts(n, (int)B, k)) *
+                                    k * E);
   return (size_t)doubles * sizeof(double);
 }
 
