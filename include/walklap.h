@@ -236,7 +236,10 @@ wl_status wl_op_info(const wl_op* op, int32_t* degree_or_steps, int32_t* method)
  * Cached in the operator after the first call.                                   */
 wl_status wl_fdeg(wl_op* op, void* d_w);
 
-/* Y = phi X (n x b).                                                              */
+/* Y = phi X (n x b).  A Lanczos resolvent whose projected matrix comes out indefinite
+ * under reorth 0 or 1 (on graphs of few distinct eigenvalues rounding alone does it) is
+ * evaluated once more with full reorthogonalisation, which decides whether the result is
+ * WL_ENOTSPD; the _ws and _noalloc calls do the same on their region.              */
 wl_status wl_apply_phi(wl_op* op, const void* d_X, void* d_Y, int32_t b);
 
 /* Y = L X = w * X - phi X (eq. f-laplacian / eq. weighted_laplacian), never
@@ -512,6 +515,7 @@ wl_status wl_diag_est(wl_op* op, int32_t target, double t, int32_t M, uint64_t s
  *     kernels cover FP32 with b = 16 and b = 1 (nops <= 8, any precision); other
  *     shapes, and Krylov spaces so small that full reorthogonalisation is needed
  *     ((steps + 1) 2 b > n), are evaluated operator by operator into the same layout.
+ *     The lock step returns WL_ENOTSPD at once where wl_apply_phi evaluates again.
  * wl_multi_create: 1 <= nops <= 64 operators (WL_EUNSUPPORTED for mixed methods and for
  * WL_M_ARNOLDI operators, which are evaluated alone); the
  * handle keeps the graph alive (not the operators, whose descriptors it copies).

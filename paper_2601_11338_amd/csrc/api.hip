@@ -713,10 +713,11 @@ wl_status read_projection(wl_ctx* ctx, int b, int K, const double* S, std::vecto
 // block.  On return the host arrays hold A_j (K blocks), B_j (K blocks; B_{K-1}
 // is the residual coupling), R0 (X = V_0 R0).
 // ring = true keeps only three basis blocks (slot j mod 3) and needs reorth = 0.
+// gram_blocks: most blocks of one Gram (the partial sums of three are planned for every call).
 template <typename T>
 wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, int K, int reorth, T* basis, T* Wb,
                         DevBuf& small, std::vector<double>& hA, std::vector<double>& hB, std::vector<double>& hR0,
-                        int* K_eff, bool ring = false) {
+                        int* K_eff, bool ring = false, int gram_blocks = 1 << 20) {
   wl_ctx* ctx = g->ctx;
   const int64_t n = g->n;
   const int64_t blk = n * b;
@@ -798,7 +799,9 @@ wl_status block_lanczos(wl_graph* g, const LanczosOp<T>& L, const T* X, int b, i
       const int lo = reorth >= 3 ? -1 : (reorth >= 2 ? 0 : std::max(0, j - 1));
       const int nb = j - lo + 1;
       const T* Vlo = basis + (size_t)lo * blk;
-      WL_TRY(launch_gram<T>(ctx, n, Vlo, b, blk, nb, Wb, b, S + Ly.P()));
+      for (int k0 = 0; k0 < nb; k0 += gram_blocks)
+        WL_TRY(launch_gram<T>(ctx, n, Vlo + (size_t)k0 * blk, b, blk, std::min(gram_blocks, nb - k0), Wb, b,
+                              S + Ly.P() + (size_t)k0 * b * b));
       WL_TRY(update(Vlo, nb, S + Ly.P(), Wb, 1.0, -1.0, Wb, S + Ly.G()));
       WL_TRY(launch_dadd(ctx, b * b, S + Ly.P() + (size_t)(nb - 1) * b * b, S + Ly.A(j)));
     }
@@ -1113,12 +1116,14 @@ wl_status phi_lanczos(wl_op* op, const T* X, T* Y, int b, const T* wv, const T* 
   }
   std::vector<double> F;
   wl_status st = lanczos_coefficients(op, Ke, b, hA, hB, hR0, F);
-  if (st == WL_ENOTSPD && !full && op->d.reorth <= 1 && !wl_no_alloc) {
+  if (st == WL_ENOTSPD && !full && op->d.reorth <= 1) {
     // On graphs of few distinct eigenvalues (hubs) the space is exhausted within a few steps and a
     // locally reorthogonalised basis goes on with rounding noise: the projection then gains
     // negative eigenvalues or not by the last bit of its inner products.  An orthonormal
-    // basis decides whether the operator itself is indefinite.
-    WL_TRY(block_lanczos<T>(g, L, X, b, K, 2, op->basis.as<T>(), op->wbuf.as<T>(), op->small, hA, hB, hR0, &Ke));
+    // basis decides whether the operator itself is indefinite.  (Grams of three blocks at a time,
+    // so that calls on a caller's region decide the same way.)
+    WL_TRY(block_lanczos<T>(g, L, X, b, K, 2, op->basis.as<T>(), op->wbuf.as<T>(), op->small, hA, hB, hR0, &Ke, false,
+                            3));
     st = lanczos_coefficients(op, Ke, b, hA, hB, hR0, F);
   }
   WL_TRY(st);
