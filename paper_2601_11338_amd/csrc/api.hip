@@ -162,7 +162,7 @@ SpmmShape shape_for(wl_graph* g, int prec, int b) {
   auto it = g->tuned.find(prec * 1000 + std::min(b, 999));
   if (it != g->tuned.end()) return it->second;
   SpmmShape s;
-  const int lpn = segment_lanes(prec, b);
+  const int lpn = std::min(segment_lanes(prec, b), spmm_max_lanes(g->n));
   int ns = 1;
   while (ns < 64 && 8.0 * ns * std::sqrt(2.0) < g->mean_deg) ns <<= 1;  // nearest power of two
   if (lpn == 4 && g->mean_deg >= 6.0) ns = std::max(ns, 2);

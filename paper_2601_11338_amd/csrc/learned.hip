@@ -114,25 +114,25 @@ __device__ __forceinline__ RowSums row_sums(const int32_t* __restrict__ rowptr, 
   return r;
 }
 
-// Row of this thread's group and its neighbour sums: the first n_long workgroups take one
-// long row each, the others 16 short rows.  False: nothing to do for this thread; sub is
-// the thread's place in its group.
-__device__ __forceinline__ bool row_task(int64_t n, const int32_t* __restrict__ rowptr,
+// f(row, this thread's place in its group, neighbour sums) for every row: the first n_long
+// workgroups take one long row each, the others 16 short rows at a time (a launch is limited to
+// 2^32 threads, which one group per row would reach at 2^28 rows).
+constexpr int64_t ROWSUM_WGS = 1 << 20;
+template <typename F>
+__device__ __forceinline__ void for_rows(int64_t n, const int32_t* __restrict__ rowptr,
                                          const int32_t* __restrict__ colidx, const int32_t* __restrict__ long_rows,
-                                         int n_long, int64_t* row, int* sub, RowSums* rs) {
+                                         int n_long, F f) {
   if ((int)blockIdx.x < n_long) {
-    *row = long_rows[blockIdx.x];
-    *sub = threadIdx.x;
-    *rs = row_sums<256>(rowptr, colidx, rowptr[*row], rowptr[*row + 1], threadIdx.x);
-    return true;
+    const int64_t row = long_rows[blockIdx.x];
+    f(row, (int)threadIdx.x, row_sums<256>(rowptr, colidx, rowptr[row], rowptr[row + 1], threadIdx.x));
+    return;
   }
-  *row = ((int64_t)blockIdx.x - n_long) * 16 + (threadIdx.x >> 4);
-  *sub = threadIdx.x & 15;
-  if (*row >= n) return false;  // the 16 lanes of a group leave together
-  const int32_t a = rowptr[*row], b = rowptr[*row + 1];
-  if (b - a > ROWSUM_LONG) return false;
-  *rs = row_sums<16>(rowptr, colidx, a, b, *sub);
-  return true;
+  const int sub = threadIdx.x & 15;
+  const int64_t step = ((int64_t)gridDim.x - n_long) * 16;
+  for (int64_t row = ((int64_t)blockIdx.x - n_long) * 16 + (threadIdx.x >> 4); row < n; row += step) {
+    const int32_t a = rowptr[row], b = rowptr[row + 1];  // (the 16 lanes of a group stay together)
+    if (b - a <= ROWSUM_LONG) f(row, sub, row_sums<16>(rowptr, colidx, a, b, sub));
+  }
 }
 
 __global__ __launch_bounds__(256) void k_features(int64_t n, const int32_t* __restrict__ rowptr,
@@ -140,25 +140,24 @@ __global__ __launch_bounds__(256) void k_features(int64_t n, const int32_t* __re
                                                   const unsigned long long* __restrict__ tri2, double s,
                                                   float* __restrict__ feat, const int32_t* __restrict__ long_rows,
                                                   int n_long) {
-  int64_t i;
-  int f;
-  RowSums rs;
-  if (!row_task(n, rowptr, colidx, long_rows, n_long, &i, &f, &rs) || f >= NIN) return;
-  const double d = rowptr[i + 1] - rowptr[i];
-  const double t = tri2 ? 0.5 * (double)tri2[i] : 0.0;
-  // lane f of the group writes feature f
-  double x;
-  switch (f) {
-    case 0: x = s * d; break;
-    case 1: x = s * s * d; break;
-    case 2: x = s * s * s * 2.0 * t; break;
-    case 3: x = s * s * rs.s1; break;
-    case 4: x = s * (d > 0 ? rs.s1 / d : 0.0); break;
-    case 5: x = s * (d > 0 ? sqrt(rs.s2 / d) : 0.0); break;
-    case 6: x = s * rs.mx; break;
-    default: x = d >= 2 ? 2.0 * t / (d * (d - 1.0)) : 0.0; break;
-  }
-  feat[i * NIN + f] = (float)(f < 7 ? log1p(x) : x);
+  for_rows(n, rowptr, colidx, long_rows, n_long, [&](int64_t i, int f, const RowSums& rs) {
+    if (f >= NIN) return;
+    const double d = rowptr[i + 1] - rowptr[i];
+    const double t = tri2 ? 0.5 * (double)tri2[i] : 0.0;
+    // lane f of the group writes feature f
+    double x;
+    switch (f) {
+      case 0: x = s * d; break;
+      case 1: x = s * s * d; break;
+      case 2: x = s * s * s * 2.0 * t; break;
+      case 3: x = s * s * rs.s1; break;
+      case 4: x = s * (d > 0 ? rs.s1 / d : 0.0); break;
+      case 5: x = s * (d > 0 ? sqrt(rs.s2 / d) : 0.0); break;
+      case 6: x = s * rs.mx; break;
+      default: x = d >= 2 ? 2.0 * t / (d * (d - 1.0)) : 0.0; break;
+    }
+    feat[i * NIN + f] = (float)(f < 7 ? log1p(x) : x);
+  });
 }
 
 // out[j] = Y[nodes[j0 + j], j] for the unit-vector block e_{nodes[j0 .. j0+b)}
@@ -541,14 +540,13 @@ __global__ __launch_bounds__(256) void k_surrogate_diag(int64_t n, const int32_t
                                                         double c3, double c4, T* __restrict__ base,
                                                         T* __restrict__ scale,
                                                         const int32_t* __restrict__ long_rows, int n_long) {
-  int64_t r;
-  int sub;
-  RowSums rs;
-  if (!row_task(n, rowptr, colidx, long_rows, n_long, &r, &sub, &rs) || sub != 0) return;
-  double bs, sc;
-  surrogate_terms(rowptr[r + 1] - rowptr[r], rs.s1, (double)tri2[r], c2m, c3, c4, &bs, &sc);
-  if (base) base[r] = (T)bs;
-  if (scale) scale[r] = (T)sc;
+  for_rows(n, rowptr, colidx, long_rows, n_long, [&](int64_t r, int sub, const RowSums& rs) {
+    if (sub != 0) return;
+    double bs, sc;
+    surrogate_terms(rowptr[r + 1] - rowptr[r], rs.s1, (double)tri2[r], c2m, c3, c4, &bs, &sc);
+    if (base) base[r] = (T)bs;
+    if (scale) scale[r] = (T)sc;
+  });
 }
 
 // out[j] = (d[j] - base(nodes[j])) / scale(nodes[j]) in place (d: diag phi at the nodes)
@@ -577,6 +575,8 @@ __global__ void k_affine(int64_t n, const float* __restrict__ base, const float*
     y[i] = (base ? base[i] : 0.f) + (scale ? scale[i] : 1.f) * y[i];
 }
 
+// workgroups of the neighbour-sum kernels (nl: rows that take one of their own)
+dim3 rowsum_grid(int64_t n, int nl) { return dim3((unsigned)(nl + std::min((n + 15) / 16, ROWSUM_WGS))); }
 // rows that take a whole workgroup in the neighbour-sum kernels
 int rowsum_long(const wl_graph* g) {
   const auto& dd = g->h_long_deg;  // decreasing
@@ -634,7 +634,7 @@ wl_status wl_features(wl_graph* g, double scale, void* d_feat) {
   const unsigned long long* tri = nullptr;
   WL_TRY(graph_tri2(g, &tri));
   const int nl = rowsum_long(g);
-  hipLaunchKernelGGL(k_features, dim3((unsigned)(nl + (g->n + 15) / 16)), dim3(256), 0, st, g->n, g->rowptr,
+  hipLaunchKernelGGL(k_features, rowsum_grid(g->n, nl), dim3(256), 0, st, g->n, g->rowptr,
                      g->colidx, tri, scale, (float*)d_feat, g->long_rows.as<int32_t>(), nl);
   WL_HIP(hipGetLastError());
   WL_HIP(hipStreamSynchronize(st));
@@ -688,7 +688,7 @@ wl_status wl_surrogate_diag(wl_op* op, void* d_base, void* d_scale) {
   double c2m, c3, c4;
   surrogate_coeffs(op, &c2m, &c3, &c4);
   const int nl = rowsum_long(g);
-  const dim3 grid((unsigned)(nl + (g->n + 15) / 16));
+  const dim3 grid = rowsum_grid(g->n, nl);
   if (op->d.prec == WL_FP32)
     hipLaunchKernelGGL(k_surrogate_diag<float>, grid, dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri,
                        c2m, c3, c4, (float*)d_base, (float*)d_scale, g->long_rows.as<int32_t>(), nl);

@@ -667,7 +667,8 @@ wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep
     if (lanes < 16) return run_g<T, VW, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   }
   // even widths of FP32 blocks that are no multiple of 4 (or only 8-byte aligned): 8-byte
-  // vectors, a row in one segment up to 64 columns.  (30 columns, 100k nodes of degree 10,
+  // vectors, a row in one segment up to 64 columns (in tiles of 32 where spmm_max_lanes allows
+  // 16 lanes only).  (30 columns, 100k nodes of degree 10,
   // Lanczos epilogue: the scalar path's two 16-column tiles took 316 us, this 56 us.)
   if constexpr (sizeof(T) == 4) {
     if (b % 2 == 0 && !ep.cmap && (!ep.ctab || ep.cgw % 2 == 0) && aligned_to<T>(ep, X, Y, 8)) {
@@ -675,7 +676,7 @@ wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep
       if (lanes == 1) return run_g<T, 2, 1, false>(g, X, Y, b, ep, sh.G, sh.long_thr);
       if (lanes <= 4) return run_g<T, 2, 4, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
       if (lanes <= 8) return run_g<T, 2, 8, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-      if (lanes <= 16) return run_g<T, 2, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+      if (lanes <= 16 || spmm_max_lanes(g->n) < 32) return run_g<T, 2, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
       return run_g<T, 2, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
     }
   }
@@ -684,7 +685,7 @@ wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep
   if (b <= 2) return run_g<T, 1, 2, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   if (b <= 4) return run_g<T, 1, 4, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   if (b <= 8) return run_g<T, 1, 8, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-  if (b <= 16) return run_g<T, 1, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+  if (b <= 16 || spmm_max_lanes(g->n) < 32) return run_g<T, 1, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   return run_g<T, 1, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
 }
 

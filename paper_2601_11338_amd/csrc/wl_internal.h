@@ -112,6 +112,10 @@ struct SpmmShape {
   int long_thr = 512;  // rows with more neighbours go to whole workgroups
 };
 
+// Lanes that a row segment of the 8-byte and scalar products may take: 32 lanes a row reach the
+// 2^32 threads of a launch at 2^27 rows.
+inline int spmm_max_lanes(int64_t n) { return n < ((int64_t)1 << 27) ? 32 : 16; }
+
 // Live timing of kernel classes (opt-in): HIP events recorded around each launch
 // on the context stream, algorithmic bytes counted per launch.
 // Timing classes of sparse products: single-operator series steps (b >= 4), Lanczos
