@@ -986,7 +986,10 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
     // P_k overwrites the buffer of P_{k-2} (row r of P_{k-2} is read and row r of
     // P_k written by the same lanes); P_0 = X is never overwritten.
     T* out = (k == 2) ? spare : const_cast<T*>(Pm2);
-    if (mu == 0.0 && !sums) ep.Z = nullptr;
+    if (mu == 0.0) {
+      if (sums) ep.Sx = Pm2;
+      ep.Z = nullptr;
+    }
     WL_TRY(launch_spmm<T>(g, Pm1, last ? nullptr : out, b, ep, sh));
     Pm2 = Pm1;
     Pm1 = out;

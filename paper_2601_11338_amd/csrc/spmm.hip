@@ -189,9 +189,10 @@ __device__ __forceinline__ void right_factor(T* y, int cl, int TILE, const T* sN
   for (int i = 0; i < VW; ++i) y[i] = out[i];
 }
 
-// Epilogue variants (template bits of the kernel): per-column operators (ep.cmap) and
-// the deferred-normalisation right factor (ep.Nm).
-constexpr int EPI_COLS = 1, EPI_NFAC = 2;
+// Epilogue variants (template bits of the kernel): per-column operators (ep.cmap), the
+// deferred-normalisation right factor (ep.Nm), and a running sum with a Z of its own (ep.Sx
+// without tables; as a branch of the plain variant it cost every product up to 1%).
+constexpr int EPI_COLS = 1, EPI_NFAC = 2, EPI_SZ = 4;
 
 // Per-column coefficients of one column tile, resolved through ep.cmap once per
 // workgroup into LDS (the epilogue then reads them with a few LDS loads instead of
@@ -340,15 +341,14 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
   for (int i = 0; i < VW; ++i) y[i] = a * acc.v[i];
   Frag<T, VW> z;
   zero(z);
-  const bool zy = cb0 != 0.0 || cb1 != 0.0;  // (0 x infinity is not nothing)
-  if (ep.Z && (zy || csz != 0.0)) {
+  if (ep.Z && (cb0 != 0.0 || cb1 != 0.0 || csz != 0.0)) {
+    const T coef = (T)(cb0 + cb1 * (double)deg);
     z = ldf_m<T, VW, MASK>(ep.Z + off, true);
-    if (zy) {
-      const T coef = (T)(cb0 + cb1 * (double)deg);
 #pragma unroll
-      for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
-    }
+    for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
   }
+  if constexpr ((E & EPI_SZ) != 0)  // (before Y is written: it may be the same buffer)
+    z = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Sx + off, true) : ldf_nt<T, VW>(ep.Sx + off);
   if constexpr ((E & EPI_NFAC) != 0 && VW > 1) right_factor<T, VW>(y, cl, TILE, sN);
   if (ep.C) c_term<T, VW>(r, ld, b, col, cl, TILE, ep, sC, y);
   if (Y) {
@@ -369,11 +369,7 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
       zero(s);
     const T s0 = (T)ep.s0, sc = (T)csc, sz = (T)csz;
 #pragma unroll
-    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i];
-    if (csz != 0.0) {
-#pragma unroll
-      for (int i = 0; i < VW; ++i) s.v[i] += sz * z.v[i];
-    }
+    for (int i = 0; i < VW; ++i) s.v[i] = s0 * s.v[i] + sc * y[i] + sz * z.v[i];
     if (fin) {
       const T wr = ep.wld ? ep.wv[r * (int64_t)ep.wld + col / ep.cgw] : ep.wv[r];
       Frag<T, VW> xw = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Xw + off, true) : ldf_nt<T, VW>(ep.Xw + off);
@@ -558,6 +554,8 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
     }
     n_long = lo;
   }
+  const bool own_z = ep.Sx && !ep.gid && !ep.ctab;
+  WL_CHECK(!own_z || (!ep.Nm && !ep.Z), WL_EINTERNAL, "spmm: a sum with its own Z goes with no other variant");
   WL_CHECK(!ep.Nm || (VW == 4 && !(ep.cmap && ep.Sout)), WL_EINTERNAL,
            "spmm: the deferred-normalisation factor needs FP32 16-byte vectors and takes no running sum");
   constexpr int RPB = 256 / G;
@@ -591,14 +589,17 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
       hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, EPI_COLS>), grid, dim3(256), lds, ctx->stream, g->rowptr,
                          g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
   }
-  if (!ep.Nm && !ep.cmap)
+  if (own_z)
+    hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, EPI_SZ>), grid, dim3(256), lds, ctx->stream, g->rowptr,
+                       g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
+  else if (!ep.Nm && !ep.cmap)
     hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, 0>), grid, dim3(256), lds, ctx->stream, g->rowptr,
                        g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
   WL_HIP(hipGetLastError());
   if (ks) {
     // algorithmic bytes: CSR once, the gathered block once (compulsory), every row stream once
     const double s = sizeof(T), nb = (double)g->n * b;
-    const double streams = 1 + (Y ? 1 : 0) + (ep.Z ? 1 : 0) + (ep.C ? 1 : 0) +
+    const double streams = 1 + (Y ? 1 : 0) + (ep.Z || own_z ? 1 : 0) + (ep.C ? 1 : 0) +
                            ep.s_share * ((ep.Sin ? 1 : 0) + (ep.Sout ? 1 : 0)) + (ep.Xw ? 1 : 0) + (ep.jx ? 1 : 0);
     WL_TRY(kstats_end(ctx, ks, 4.0 * g->nnz + 4.0 * (g->n + 1) + s * nb * streams + (ep.wv ? s * g->n : 0.0) +
                                    (ep.jw ? s * g->n : 0.0)));

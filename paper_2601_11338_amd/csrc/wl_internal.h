@@ -262,7 +262,9 @@ struct EpiArgs {
   const T* Sin = nullptr;
   T* Sout = nullptr;
   double s0 = 0.0, sc = 0.0, sz = 0.0;
-  const T* Sx = nullptr;  // with gtab or ctab: the SS_X source of the running sum
+  // Without tables: Z of the running sum alone, where y has no use for it (Z is null then; 0 x
+  // infinity would be NaN).
+  const T* Sx = nullptr;  // With gtab or ctab: the SS_X source of the running sum
   double s_share = 1.0;   // share of the block whose running sum this launch reads (byte counts)
   const T* wv = nullptr;
   const T* Xw = nullptr;
