@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double
     sV[e] = r < b ? Sg[offR0 + r * b + c] : 0.0;
   }
   __syncthreads();
-  // ||T||_inf
+  // ||T||_inf (infinity where T is not finite: a maximum would pass over NaN)
   double mx = 0.0;
   for (int r = t; r < m; r += 256) {
     const int j = r / b, i = r % b;
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double
       if (j > 0) s += fabs(sB[(j - 1) * bb + i * b + c]);      // T_{j, j-1} = B_{j-1}
       if (j + 1 < K) s += fabs(sB[j * bb + c * b + i]);         // T_{j, j+1} = B_j^T
     }
-    mx = fmax(mx, s);
+    mx = fmax(mx, s < INFINITY ? s : INFINITY);
   }
   red[t] = mx;
   __syncthreads();
@@ -315,7 +315,9 @@ __global__ __launch_bounds__(256) void k_expT_batched(int K, int b, const double
   };
   double* Fg = F + (int64_t)g * fgs;
   const double hi = snorm;
-  if (tvals[g] > 0.0 && hi > 0.0) {
+  if (!(hi < INFINITY)) {
+    for (int e = t; e < mb; e += 256) sV[e] = NAN;
+  } else if (tvals[g] > 0.0 && hi > 0.0) {
     const double lo = -fmin(0.01 * hi, 1.0 / tvals[g]), al = 2.0 / (hi - lo), be = (hi + lo) / (hi - lo);
     const double ztot = fmin(0.5 * tvals[g] * (hi - lo), EXP_ZMAX * EXP_MAXSTEPS);
     int todo = (int)ceil(ztot / EXP_ZMAX);  // substeps left, of z each
