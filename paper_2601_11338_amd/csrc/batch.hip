@@ -705,10 +705,14 @@ wl_status return_probabilities(wl_batch* bt, BatchWork& wk, int b, int K, double
           Gm[(size_t)i * M + jj] = s2;
         }
       // leave-one-out Nystrom (same formulas as wl_estimate); without its cores' spectra the
-      // plain probe mean stands
+      // plain probe mean and its standard error stand
       double tr = 0.0, te = 0.0;
       if (xnys_trace_host(M, H, Gm, 1e-10, &tr, &te)) {
+        double var = 0.0;
+        tr = 0.0;
         for (int j = 0; j < M; ++j) tr += H[(size_t)j * M + j] / M;
+        for (int j = 0; j < M; ++j) var += (H[(size_t)j * M + j] - tr) * (H[(size_t)j * M + j] - tr);
+        te = std::sqrt(var / (M - 1)) / std::sqrt((double)M);
       }
       if (p_hat) p_hat[g] = tr / (double)bt->n[g];
       if (p_err) p_err[g] = te / (double)bt->n[g];
