@@ -802,3 +802,146 @@ int dense_phi1_times(int m, const double* M, int k, const double* B, double* out
     for (int j = 0; j < k; ++j) out[(size_t)i * k + j] = E[(size_t)i * a + m + j];
   return 0;
 }
+
+// ------------------------------------------------------------------ leave-one-out Nystrom traces
+// pseudo-inverse of the symmetric part of the (M-1) x (M-1) matrix H without j,
+// embedded into M x M
+int pinv_drop(int M, const std::vector<double>& H, int j, double rcond, std::vector<double>& P) {
+  const int m = M - 1;
+  std::vector<double> S((size_t)m * m), lam(m), U((size_t)m * m);
+  for (int a = 0, ia = 0; a < M; ++a) {
+    if (a == j) continue;
+    for (int c = 0, ic = 0; c < M; ++c) {
+      if (c == j) continue;
+      S[(size_t)ia * m + ic] = 0.5 * (H[(size_t)a * M + c] + H[(size_t)c * M + a]);
+      ++ic;
+    }
+    ++ia;
+  }
+  if (dense_syev(m, S.data(), lam.data(), U.data())) return 1;
+  double lmax = 0.0;
+  for (double v : lam) lmax = std::max(lmax, v);
+  P.assign((size_t)M * M, 0.0);
+  std::vector<int> map;
+  for (int a = 0; a < M; ++a)
+    if (a != j) map.push_back(a);
+  for (int k = 0; k < m; ++k) {
+    if (!(lam[k] > rcond * lmax)) continue;
+    const double inv = 1.0 / lam[k];
+    for (int a = 0; a < m; ++a) {
+      const double ua = U[(size_t)a * m + k] * inv;
+      if (ua == 0.0) continue;
+      for (int c = 0; c < m; ++c) P[(size_t)map[a] * M + map[c]] += ua * U[(size_t)c * m + k];
+    }
+  }
+  return 0;
+}
+
+namespace {
+
+// The leave-one-out values from one factorisation where no core is truncated: the core without
+// probe j has its eigenvalues between those of the whole symmetric part S, so for lambda_min(S)
+// above rcond lambda_max(S) every pseudo-inverse is an inverse, and with S = L L^T the embedded
+// inverse without j is L^{-T} (I - y y^T) L^{-1}, y along L^{-1} e_j.  Then tr(P_j G) = tr W - y^T W y
+// with W = L^{-1} G L^{-T}, and h^T P_j h is the squared norm of L^{-1} h without its part along y.
+// Taken while the condition number stays below 1e6.  (Integer cores of 3 to 12 probes of
+// condition 2e5 to 8e5, relative error of the mean against exact fractions: at most 6e-14; M
+// separate eigendecompositions of order M - 1, which took 25 of the 133 ms of an estimate
+// with 30 probes and 90 times, 4e-13; S^{-1} formed from one eigendecomposition 7e-12.)
+// Returns 1 when tj is filled, 0 where it does not apply, -1 on failure.
+int loo_by_inverse(int M, const std::vector<double>& H, const std::vector<double>& G, double rcond,
+                   std::vector<double>& tj) {
+  std::vector<double> S((size_t)M * M), lam(M), U(M);
+  for (int a = 0; a < M; ++a)
+    for (int c = 0; c < M; ++c) S[(size_t)a * M + c] = 0.5 * (H[(size_t)a * M + c] + H[(size_t)c * M + a]);
+  if (dense_syev_rows(M, S.data(), 1, lam.data(), U.data())) return -1;
+  double lmin = lam[0], lmax = lam[0];
+  for (double v : lam) {
+    lmin = std::min(lmin, v);
+    lmax = std::max(lmax, v);
+  }
+  if (!(lmax > 0.0) || !(lmin > std::max(rcond, 1e-6) * lmax)) return 0;
+  BlockTridiagChol F;
+  if (F.factor(1, M, S.data(), nullptr)) return 0;
+  auto solve = [&](std::vector<double>& X) {  // X (M x M) <- L^{-1} X
+    for (int i = 0; i < M; ++i) {
+      double* x = &X[(size_t)i * M];
+      for (int k = 0; k < i; ++k) {
+        const double l = F.L[(size_t)i * M + k];
+        for (int c = 0; c < M; ++c) x[c] -= l * X[(size_t)k * M + c];
+      }
+      for (int c = 0; c < M; ++c) x[c] /= F.L[(size_t)i * M + i];
+    }
+  };
+  auto transposed = [&](const std::vector<double>& X) {
+    std::vector<double> T((size_t)M * M);
+    for (int a = 0; a < M; ++a)
+      for (int c = 0; c < M; ++c) T[(size_t)c * M + a] = X[(size_t)a * M + c];
+    return T;
+  };
+  std::vector<double> W = G, Y((size_t)M * M, 0.0), Z = transposed(H);
+  solve(W);
+  W = transposed(W);
+  solve(W);
+  for (int a = 0; a < M; ++a) Y[(size_t)a * M + a] = 1.0;
+  solve(Y);
+  Y = transposed(Y);  // row j: L^{-1} e_j
+  solve(Z);
+  Z = transposed(Z);  // row j: L^{-1} h_j
+  double tr = 0.0;
+  for (int a = 0; a < M; ++a) tr += W[(size_t)a * M + a];
+  for (int j = 0; j < M; ++j) {
+    double* y = &Y[(size_t)j * M];
+    double* z = &Z[(size_t)j * M];
+    double yy = 0.0, yz = 0.0, yWy = 0.0, zz = 0.0;
+    for (int a = 0; a < M; ++a) yy += y[a] * y[a];
+    yy = 1.0 / std::sqrt(yy);
+    for (int a = 0; a < M; ++a) {
+      y[a] *= yy;
+      yz += y[a] * z[a];
+    }
+    for (int a = 0; a < M; ++a) {
+      double wy = 0.0;
+      for (int c = 0; c < M; ++c) wy += W[(size_t)a * M + c] * y[c];
+      yWy += y[a] * wy;
+      z[a] -= y[a] * yz;
+      zz += z[a] * z[a];
+    }
+    tj[j] = tr - yWy + H[(size_t)j * M + j] - zz;
+  }
+  return 1;
+}
+
+}  // namespace
+
+int xnys_trace_host(int M, const std::vector<double>& H, const std::vector<double>& G, double rcond, double* trace,
+                    double* trace_err) {
+  // t_j = tr(Hp_j G) + H_jj - h_j^T Hp_j h_j, Hp_j the pseudo-inverse of the core
+  // without probe j, h_j = row j of H: the leave-one-out estimate written with the
+  // M x M Grams alone (F_(j) = Y_{-j} Hp_j Y_{-j}^T, never formed)
+  if (M < 2) return -1;
+  std::vector<double> P, tj(M);
+  const int all = loo_by_inverse(M, H, G, rcond, tj);
+  if (all < 0) return -1;
+  for (int j = 0; j < M && all == 0; ++j) {
+    if (pinv_drop(M, H, j, rcond, P)) return -1;
+    double trPG = 0.0, hPh = 0.0;
+    for (int a = 0; a < M; ++a) {
+      double ph = 0.0;
+      for (int c = 0; c < M; ++c) {
+        trPG += P[(size_t)a * M + c] * G[(size_t)c * M + a];
+        ph += P[(size_t)a * M + c] * H[(size_t)j * M + c];
+      }
+      hPh += H[(size_t)j * M + a] * ph;
+    }
+    tj[j] = trPG + H[(size_t)j * M + j] - hPh;
+  }
+  double mean = 0.0;
+  for (double v : tj) mean += v;
+  mean /= M;
+  double var = 0.0;
+  for (double v : tj) var += (v - mean) * (v - mean);
+  *trace = mean;
+  *trace_err = std::sqrt(var / (M - 1)) / std::sqrt((double)M);
+  return 0;
+}

@@ -56,39 +56,6 @@ wl_status gram_full(wl_ctx* ctx, int64_t n, int M, const T* X, const T* Y, std::
   return WL_EUNSUPPORTED;
 }
 
-// pseudo-inverse of the symmetric part of the (M-1) x (M-1) matrix H without j,
-// embedded into M x M
-int pinv_drop(int M, const std::vector<double>& H, int j, double rcond, std::vector<double>& P) {
-  const int m = M - 1;
-  std::vector<double> S((size_t)m * m), lam(m), U((size_t)m * m);
-  for (int a = 0, ia = 0; a < M; ++a) {
-    if (a == j) continue;
-    for (int c = 0, ic = 0; c < M; ++c) {
-      if (c == j) continue;
-      S[(size_t)ia * m + ic] = 0.5 * (H[(size_t)a * M + c] + H[(size_t)c * M + a]);
-      ++ic;
-    }
-    ++ia;
-  }
-  if (dense_syev(m, S.data(), lam.data(), U.data())) return 1;
-  double lmax = 0.0;
-  for (double v : lam) lmax = std::max(lmax, v);
-  P.assign((size_t)M * M, 0.0);
-  std::vector<int> map;
-  for (int a = 0; a < M; ++a)
-    if (a != j) map.push_back(a);
-  for (int k = 0; k < m; ++k) {
-    if (!(lam[k] > rcond * lmax)) continue;
-    const double inv = 1.0 / lam[k];
-    for (int a = 0; a < m; ++a) {
-      const double ua = U[(size_t)a * m + k] * inv;
-      if (ua == 0.0) continue;
-      for (int c = 0; c < m; ++c) P[(size_t)map[a] * M + map[c]] += ua * U[(size_t)c * m + k];
-    }
-  }
-  return 0;
-}
-
 template <typename T>
 wl_status estimate_impl(wl_ctx* ctx, int estimator, int64_t n, int M, const T* Om, const T* Y, const T* cv,
                         double rcond, T* diag, double* trace, double* trace_err) {
@@ -147,87 +114,7 @@ wl_status estimate_impl(wl_ctx* ctx, int estimator, int64_t n, int M, const T* O
   return WL_OK;
 }
 
-// The leave-one-out values from one eigendecomposition where no core is truncated: the core
-// without probe j has its eigenvalues between those of the whole symmetric part S, so for
-// lambda_min(S) above rcond lambda_max(S) every pseudo-inverse is an inverse, and with
-// u = S^{-1} e_j the embedded inverse without j is S^{-1} - u u^T / u_j.  Taken while the condition
-// number stays below 1e6 (rounding below 1e-10 of the correction, as for M separate
-// eigendecompositions of order M - 1, which took 25 of the 133 ms of an estimate with 30 probes
-// and 90 times).  Returns 1 when tj is filled, 0 where it does not apply, -1 on failure.
-int loo_by_inverse(int M, const std::vector<double>& H, const std::vector<double>& G, double rcond,
-                   std::vector<double>& tj) {
-  std::vector<double> S((size_t)M * M), lam(M), U((size_t)M * M);
-  for (int a = 0; a < M; ++a)
-    for (int c = 0; c < M; ++c) S[(size_t)a * M + c] = 0.5 * (H[(size_t)a * M + c] + H[(size_t)c * M + a]);
-  if (dense_syev(M, S.data(), lam.data(), U.data())) return -1;
-  double lmin = lam[0], lmax = lam[0];
-  for (double v : lam) {
-    lmin = std::min(lmin, v);
-    lmax = std::max(lmax, v);
-  }
-  if (!(lmax > 0.0) || !(lmin > std::max(rcond, 1e-6) * lmax)) return 0;
-  std::vector<double> V((size_t)M * M, 0.0);  // S^{-1}
-  for (int k = 0; k < M; ++k)
-    for (int a = 0; a < M; ++a) {
-      const double ua = U[(size_t)a * M + k] / lam[k];
-      for (int c = 0; c < M; ++c) V[(size_t)a * M + c] += ua * U[(size_t)c * M + k];
-    }
-  double tr = 0.0;
-  for (int a = 0; a < M; ++a)
-    for (int c = 0; c < M; ++c) tr += V[(size_t)a * M + c] * G[(size_t)c * M + a];
-  for (int j = 0; j < M; ++j) {
-    const double* u = &V[(size_t)j * M];
-    const double* h = &H[(size_t)j * M];
-    const double uj = u[j];
-    double uGu = 0.0, hVh = 0.0, uh = 0.0;
-    for (int a = 0; a < M; ++a) {
-      double gu = 0.0, vh = 0.0;
-      for (int c = 0; c < M; ++c) {
-        gu += G[(size_t)a * M + c] * u[c];
-        vh += V[(size_t)a * M + c] * h[c];
-      }
-      uGu += u[a] * gu;
-      hVh += h[a] * vh;
-      uh += u[a] * h[a];
-    }
-    tj[j] = tr - uGu / uj + h[j] - (hVh - uh * uh / uj);
-  }
-  return 1;
-}
-
 }  // namespace
-
-int xnys_trace_host(int M, const std::vector<double>& H, const std::vector<double>& G, double rcond, double* trace,
-                    double* trace_err) {
-  // t_j = tr(Hp_j G) + H_jj - h_j^T Hp_j h_j, Hp_j the pseudo-inverse of the core
-  // without probe j, h_j = row j of H: the leave-one-out estimate written with the
-  // M x M Grams alone (F_(j) = Y_{-j} Hp_j Y_{-j}^T, never formed)
-  if (M < 2) return -1;
-  std::vector<double> P, tj(M);
-  const int all = loo_by_inverse(M, H, G, rcond, tj);
-  if (all < 0) return -1;
-  for (int j = 0; j < M && all == 0; ++j) {
-    if (pinv_drop(M, H, j, rcond, P)) return -1;
-    double trPG = 0.0, hPh = 0.0;
-    for (int a = 0; a < M; ++a) {
-      double ph = 0.0;
-      for (int c = 0; c < M; ++c) {
-        trPG += P[(size_t)a * M + c] * G[(size_t)c * M + a];
-        ph += P[(size_t)a * M + c] * H[(size_t)j * M + c];
-      }
-      hPh += H[(size_t)j * M + a] * ph;
-    }
-    tj[j] = trPG + H[(size_t)j * M + j] - hPh;
-  }
-  double mean = 0.0;
-  for (double v : tj) mean += v;
-  mean /= M;
-  double var = 0.0;
-  for (double v : tj) var += (v - mean) * (v - mean);
-  *trace = mean;
-  *trace_err = std::sqrt(var / (M - 1)) / std::sqrt((double)M);
-  return 0;
-}
 
 extern "C" {
 

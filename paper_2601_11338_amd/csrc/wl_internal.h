@@ -668,6 +668,9 @@ int aaa_poles(const std::vector<double>& z, const std::vector<double>& w, std::v
 // (real poles on the interval itself dropped).
 void exp_sample_points(double xmax, std::vector<double>& Z);
 int exp_poles(double xmax, double tol, int mmax, std::vector<std::complex<double>>& poles, double* max_err);
+// P (M x M) = pseudo-inverse of the symmetric part of H without row and column j (zero there).
+// Nonzero on failure.
+int pinv_drop(int M, const std::vector<double>& H, int j, double rcond, std::vector<double>& P);
 // Leave-one-out Nystrom trace estimate from H = Omega^T Y and G = Y^T Y (M x M,
 // row-major): the mean over j of tr F_(j) + omega_j^T (F - F_(j)) omega_j and its
 // standard error.  0 on success.
