@@ -1769,7 +1769,8 @@ int fin_grid(int E) {
 // of 1024 threads sums them in about the time of the launch it saves (up to 32768 values: 5
 // columns of 5000 rows, 79 partials, 2.8 + 3.2 us in two launches -> 4.1 us; FP64, 8 columns
 // of 200k rows, 512 partials, at the line, 4.6 + 3.2 -> 7.6), or, for a second pass that
-// mostly is not needed at all, up to 131072 (1 MB through one CU, about 10 us).
+// mostly is not needed at all, up to 131072 (1 MB through one CU: 33 us with the factorisation
+// where it is needed).
 // A Lanczos step is 8 launches so and was 11: 1.50 -> 1.31 ms for 30 steps of the first,
 // 3.18 -> 3.14 ms for the second.
 // Narrow blocks the same: 2 FP32 columns of 6000 nodes 1.35 -> 1.10 ms for 30 steps, FP64

@@ -569,7 +569,10 @@ wl_status launch_gupdate(wl_ctx* ctx, int64_t n, int gb, int ng, const T* X, int
     }
     if (gb == 16) {
       const int ngc = group_chunk(ng, std::max(nblk, 1));
-      nparts = gparts(((n + 15) / 16 + 15) / 16, 1024);
+      // a sum left to the factorisation is taken by one workgroup per group: 131072 values at
+      // most, as for a single operator (1M rows, the second pass forced in every step: sum and
+      // factorisation 48 us at 1024 partials and 34 at 512, the update before them 56 and 68)
+      nparts = gparts(((n + 15) / 16 + 15) / 16, gram_out && gp ? 512 : 1024);
       const dim3 grid((unsigned)nparts, (unsigned)((ng + ngc - 1) / ngc));
       const size_t lds = (size_t)ngc * nblk * 64 * sizeof(float4);
       const int ld = ng * 16;
