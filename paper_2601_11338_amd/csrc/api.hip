@@ -1147,68 +1147,23 @@ wl_status phi_apply_impl(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
 template wl_status phi_apply_impl<float>(wl_op*, const float*, float*, int, const float*, const float*);
 template wl_status phi_apply_impl<double>(wl_op*, const double*, double*, int, const double*, const double*);
 
-// Does the spectrum of the block tridiagonal T suit a Chebyshev series of exp(-t T) on [lo, hi]
-// for all times up to tmax?  Below lo the series grows faster than its coefficients fall, and
-// its rounding is that of e^{-t lo}, so for lambda_min(T) far above lo a small result drowns in
-// it (four cliques of 40 to 43 nodes, mean-free start, e^{-t lambda} = 1e-22: error 1e-14).  Hence
-// T - lo must be positive definite (by its Cholesky factors) and a Rayleigh quotient (inverse
-// iteration, an upper bound of lambda_min) at most 4 / tmax above lo.  Where it is not, lo moves up
-// to 2 / tmax below the quotient, if T - lo stays definite.  Returns 0: lo holds, 1: lo was
-// moved, 2: no interval found.  Deflated basis columns (zero rows of T) are left out.
-// 2 ms of host work at K = 40, b = 32, beside the first series on the device.
-static int exp_interval(int K, int b, const std::vector<double>& hA, const std::vector<double>& hB, double hi,
-                        double tmax, double* lo) {
-  const int m = K * b, bb = b * b;
-  std::vector<char> zero(m, 1);
-  for (int j = 0; j < K; ++j)
-    for (int r = 0; r < b; ++r)
-      for (int c = 0; c < b; ++c) {
-        const bool nz = hA[(size_t)j * bb + r * b + c] != 0.0 || hA[(size_t)j * bb + c * b + r] != 0.0 ||
-                        (j > 0 && hB[(size_t)(j - 1) * bb + r * b + c] != 0.0) ||
-                        (j + 1 < K && hB[(size_t)j * bb + c * b + r] != 0.0);
-        if (nz) zero[j * b + r] = 0;
-      }
-  BlockTridiagChol F;
-  auto definite = [&](double shift) {
-    std::vector<double> Ad(hA.begin(), hA.begin() + (size_t)K * bb);
-    for (int i = 0; i < m; ++i) {
-      double& d = Ad[(size_t)(i / b) * bb + (i % b) * (b + 1)];
-      d = zero[i] ? hi : d - shift;
-    }
-    return F.factor(K, b, Ad.data(), hB.data()) == 0;
-  };
-  if (!definite(*lo)) return 2;
-  std::vector<double> r(m), y(m);
-  uint32_t seed = 1;
-  for (int i = 0; i < m; ++i) {
-    seed = seed * 1664525u + 1013904223u;
-    r[i] = zero[i] ? 0.0 : (double)(int32_t)seed;
+// exp(-t T) for the nt times of a call: by series on the device (true), or by the host's
+// eigendecomposition.  A term takes a launch, 3.2 us up to 8 columns, 4.6 at 16, 9.2 at 32, and a
+// series of degree 9.1 sqrt(z) + 24 (z = t ||T|| / 2) for every time; the eigendecomposition 65 m^2 ns
+// on 16 threads (0.65 ms at m = 100, 1.8 at 160, 6.7 at 320, 26 at 640, 115 at 1280).  Times 1, 10,
+// 100 on 20k nodes, ||T|| = 26, ms for the whole call, series / host: m = 128 7.2 / 6.3,
+// m = 160 5.7 / 5.1, m = 320 9.1 / 13.3, m = 640 12.4 / 31.9.
+constexpr int EXPV_CHEB_M = 100;     // rows of T below which the host takes less than the launches
+constexpr double EXPV_CHEB_Z = 4e4;  // z up to which the degree stays below 2000
+static bool exp_by_series(int m, int b, const double* t, int nt, double hi) {
+  double terms = 0.0;
+  for (int i = 0; i < nt; ++i) {
+    const double z = 0.5 * t[i] * hi;
+    if (!(z <= EXPV_CHEB_Z)) return false;
+    terms += 9.1 * std::sqrt(z) + 24.0;
   }
-  double gap = 0.0;  // Rayleigh quotient of T - lo
-  for (int it = 0; it < 8; ++it) {
-    double nr = 0.0, yr = 0.0, yy = 0.0;
-    for (double v : r) nr += v * v;
-    if (!(nr > 0.0)) return 0;  // T = 0
-    nr = 1.0 / std::sqrt(nr);
-    for (double& v : r) v *= nr;
-    y = r;
-    F.solve(1, y.data());
-    for (int i = 0; i < m; ++i) {
-      yr += y[i] * r[i];
-      yy += y[i] * y[i];
-    }
-    gap = yr / yy;
-    if (gap * tmax <= 4.0) return 0;
-    r = y;
-  }
-  const double up = *lo + gap - 2.0 / tmax;
-  if (!(up < hi) || !definite(up)) return 2;
-  *lo = up;
-  return 1;
+  return m >= EXPV_CHEB_M && hi > 0.0 && terms * std::max(3.2, 0.29 * b) < 0.065 * m * m;
 }
-
-constexpr int EXPV_CHEB_M = 100;       // rows of T from which the series runs on the device
-constexpr double EXPV_CHEB_Z = 4e4;    // t ||T|| / 2 up to which its degree (9 sqrt z) stays below 2000
 
 template <typename T>
 wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* const* Y, int outer_dim,
@@ -1243,13 +1198,11 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
       }
     return std::sqrt(e2);
   };
-  // exp(-t T) E_1 R0 as a Chebyshev series on the device where T is large (the host's
-  // eigendecomposition takes 9 m^3 operations: 105 ms at m = 1280, against 2.4 ms for the
-  // three times 0.1, 1, 10) and the degree moderate, on an interval that starts just below 0 (L
-  // is positive semidefinite) unless T says otherwise.  The work blocks lie in memory that
-  // the basis no longer needs, so no call needs more of it.
+  // exp(-t T) E_1 R0 as a Chebyshev series on the device where that is the faster way, on an
+  // interval that starts just below 0 (L is positive semidefinite) unless T says otherwise.  The
+  // work blocks lie in memory that the basis no longer needs, so no call needs more of it.
   const double tmax = *std::max_element(t, t + nt), hi = block_tridiag_norm(Ke, b, hA, hB);
-  if (m >= EXPV_CHEB_M && hi > 0.0 && is_finite(hi) && 0.5 * tmax * hi <= EXPV_CHEB_Z &&
+  if (is_finite(hi) && exp_by_series(m, b, t, nt, hi) &&
       (size_t)n * sizeof(T) >= (size_t)m * sizeof(double)) {
     SmallLayout Ly{b, K, (size_t)b * b};
     double* S = op->outer_small.as<double>();
@@ -1257,7 +1210,10 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
     WL_TRY(op->outer_coef.ensure((size_t)m * b * sizeof(double)));
     std::vector<double> last((size_t)nt * b * b);
     double lo = tmax > 0.0 ? -std::min(0.01 * hi, 1.0 / tmax) : -0.01 * hi;
+    // the interval is checked beside the first series where that takes long (from 0.3 ms on)
+    auto check = [&]() { return exp_interval(Ke, b, hA, hB, hi, tmax, sizeof(T) == 4 ? 12.0 : 4.0, &lo); };
     int fits = tmax > 0.0 ? -1 : 0;  // not known yet
+    if (fits < 0 && (int64_t)m * b * b < 200000) fits = check() < 2 ? 0 : 2;
     for (int it = 0; it < nt && fits < 2; ++it) {
       std::vector<double> c = t[it] > 0.0 ? cheb_exp_coeffs(t[it], lo, hi) : std::vector<double>{1.0, 0.0};
       WL_TRY(launch_cheb(g->ctx, b, Ke, S + Ly.A(0), S + Ly.B(0), S + Ly.R0(), 2.0 / (hi - lo), (hi + lo) / (hi - lo),
@@ -1265,7 +1221,7 @@ wl_status expv_impl(wl_op* op, const T* U0, int b, const double* t, int nt, T* c
       WL_TRY(recombine_device<T>(g, op->outer_basis.as<T>(), b, Ke, op->outer_coef.as<double>(), nullptr, nullptr,
                                  Y[it]));
       if (fits < 0) {
-        fits = exp_interval(Ke, b, hA, hB, hi, tmax, &lo);
+        fits = check();
         if (fits == 1) it = -1;  // again from the first time, on the new interval
         if (fits != 0) continue;
       }

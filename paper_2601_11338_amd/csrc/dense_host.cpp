@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <thread>
@@ -528,6 +529,66 @@ int block_tridiag_solve(int K, int b, const double* Ad, const double* Bo, const 
   std::memcpy(X, B, sizeof(double) * (size_t)K * b * nrhs);
   F.solve(nrhs, X);
   return 0;
+}
+
+int exp_interval(int K, int b, const std::vector<double>& hA, const std::vector<double>& hB, double hi, double tmax,
+                 double loss, double* lo) {
+  const int m = K * b, bb = b * b;
+  std::vector<char> zero(m, 1);
+  for (int j = 0; j < K; ++j)
+    for (int r = 0; r < b; ++r)
+      for (int c = 0; c < b; ++c) {
+        const bool nz = hA[(size_t)j * bb + r * b + c] != 0.0 || hA[(size_t)j * bb + c * b + r] != 0.0 ||
+                        (j > 0 && hB[(size_t)(j - 1) * bb + r * b + c] != 0.0) ||
+                        (j + 1 < K && hB[(size_t)j * bb + c * b + r] != 0.0);
+        if (nz) zero[j * b + r] = 0;
+      }
+  BlockTridiagChol F;
+  auto definite = [&](double shift) {
+    std::vector<double> Ad(hA.begin(), hA.begin() + (size_t)K * bb);
+    for (int i = 0; i < m; ++i) {
+      double& d = Ad[(size_t)(i / b) * bb + (i % b) * (b + 1)];
+      d = zero[i] ? hi : d - shift;
+    }
+    return F.factor(K, b, Ad.data(), hB.data()) == 0;
+  };
+  if (!definite(*lo)) return 2;
+  std::vector<double> r(m), y(m);
+  uint32_t seed = 1;
+  for (int i = 0; i < m; ++i) {
+    seed = seed * 1664525u + 1013904223u;
+    r[i] = zero[i] ? 0.0 : (double)(int32_t)seed;
+  }
+  bool moved = false;
+  for (int round = 0; round < 6; ++round) {
+    double gap = 0.0;  // Rayleigh quotient of T - lo
+    for (int it = 0; it < 8; ++it) {
+      double nr = 0.0, yr = 0.0, yy = 0.0;
+      for (double v : r) nr += v * v;
+      if (!(nr > 0.0)) return 0;  // T = 0
+      nr = 1.0 / std::sqrt(nr);
+      for (double& v : r) v *= nr;
+      y = r;
+      F.solve(1, y.data());
+      for (int i = 0; i < m; ++i) {
+        yr += y[i] * r[i];
+        yy += y[i] * y[i];
+      }
+      gap = yr / yy;
+      if (gap * tmax <= loss) return moved ? 1 : 0;
+      r = y;
+    }
+    const double up = *lo + gap - 2.0 / tmax, half = *lo + 0.5 * gap;
+    if (up < hi && definite(up)) {
+      *lo = up;
+      return 1;
+    }
+    // the quotient has not converged (many eigenvalues far above lo): on from half way
+    if (!(half < hi) || !definite(half)) return 2;
+    *lo = half;
+    moved = true;
+  }
+  return 2;
 }
 
 // ------------------------------------------------------------------ deflating Cholesky

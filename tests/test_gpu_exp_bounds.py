@@ -34,17 +34,17 @@ def clique_rates(sizes, beta):
     return [np.exp(beta * (s - 1)) - np.exp(-beta) for s in sizes]
 
 
-# On cliques of 4 sizes L has 4 eigenvalues on mean-free blocks, so 4 steps are exact; exp(-t L) X
+# On cliques of 8 sizes L has 8 eigenvalues on mean-free blocks, so 8 steps are exact; exp(-t L) X
 # is 3e-5 to 1e-22 of X.  Relative errors: t lambda = 50 times the products' 1e-8.
-@pytest.mark.parametrize("t", [7.0, 20.0, 34.0])
-@pytest.mark.parametrize("b", [20, 32])  # 80 rows on the host, 128 on the device
+@pytest.mark.parametrize("t", [13.0, 36.0, 63.0])
+@pytest.mark.parametrize("b", [8, 16, 32])  # 64 rows on the host, 128 and 256 on the device
 def test_expv_far_below_the_start(lib, b, t):
-    sizes = [40, 41, 42, 43]
-    beta = 1.0 / 43
+    sizes = [40, 44, 48, 52, 56, 60, 64, 68]
+    beta = 1.0 / 68
     rp, ci = cliques(sizes)
     X = mean_free(sizes, b, 5)
     op = lib.Operator(lib.Graph(lib.Context(0), rp, ci), 0.0, "exp", beta, dtype=torch.float64)
-    outs, _ = op.expv(torch.tensor(X, device="cuda"), [0.5, t], outer_dim=4)
+    outs, _ = op.expv(torch.tensor(X, device="cuda"), [0.5, t], outer_dim=8)
     rate = np.repeat(clique_rates(sizes, beta), sizes)[:, None]
     for s, o in zip([0.5, t], outs):
         ref = np.exp(-s * rate) * X
@@ -70,9 +70,9 @@ def test_batch_far_below_the_start(lib, b):
         assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-4 * np.linalg.norm(ref), x
 
 
-# phi by 5 inner steps is not entrywise positive: T has an eigenvalue -4e-3, which the last time
-# leaves outside the interval.  The reference is the same process in 64 bits.
-@pytest.mark.parametrize("b,dim", [(10, 8), (20, 8)])  # 80 rows on the host, 160 on the device
+# phi by 5 inner steps is not entrywise positive: T has an eigenvalue -4e-3.  The reference is the
+# same process in 64 bits.
+@pytest.mark.parametrize("b,dim", [(10, 8), (20, 8)])  # 80 and 160 rows
 def test_expv_of_an_indefinite_projection(lib, b, dim):
     n, inner = 400, 5
     rp, ci = synth.barabasi_albert(n, 4, 2)
