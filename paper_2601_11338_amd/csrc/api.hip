@@ -969,6 +969,7 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
   {
     EpiArgs<T> ep;
     ep.a = s;
+    ep.own_z = mu == 0.0;  // one kernel for the whole series
     sum_terms(ep, 1);
     WL_TRY(launch_spmm<T>(g, X, K == 1 ? nullptr : A, b, ep, sh));
   }
@@ -986,9 +987,10 @@ wl_status phi_recurrence(wl_op* op, const T* X, T* Y, int b, const T* wv, const 
     // P_k overwrites the buffer of P_{k-2} (row r of P_{k-2} is read and row r of
     // P_k written by the same lanes); P_0 = X is never overwritten.
     T* out = (k == 2) ? spare : const_cast<T*>(Pm2);
-    if (mu == 0.0) {
-      if (sums) ep.Sx = Pm2;
+    if (mu == 0.0) {  // y has no use for P_{k-2} (0 x infinity would be NaN), the sum has
+      ep.own_z = 1;
       ep.Z = nullptr;
+      if (sums) ep.Sx = Pm2;
     }
     WL_TRY(launch_spmm<T>(g, Pm1, last ? nullptr : out, b, ep, sh));
     Pm2 = Pm1;

@@ -190,8 +190,8 @@ __device__ __forceinline__ void right_factor(T* y, int cl, int TILE, const T* sN
 }
 
 // Epilogue variants (template bits of the kernel): per-column operators (ep.cmap), the
-// deferred-normalisation right factor (ep.Nm), and a running sum with a Z of its own (ep.Sx
-// without tables; as a branch of the plain variant it cost every product up to 1%).
+// deferred-normalisation right factor (ep.Nm), and a running sum with a Z of its own (ep.own_z;
+// as a branch of the plain variant it cost every product up to 1%).
 constexpr int EPI_COLS = 1, EPI_NFAC = 2, EPI_SZ = 4;
 
 // Per-column coefficients of one column tile, resolved through ep.cmap once per
@@ -341,14 +341,14 @@ __device__ __forceinline__ void epilogue(int64_t r, int ld, int b, int col, int 
   for (int i = 0; i < VW; ++i) y[i] = a * acc.v[i];
   Frag<T, VW> z;
   zero(z);
-  if (ep.Z && (cb0 != 0.0 || cb1 != 0.0 || csz != 0.0)) {
+  if constexpr ((E & EPI_SZ) != 0) {  // (before Y is written: it may be the same buffer)
+    if (ep.Sx) z = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Sx + off, true) : ldf<T, VW>(ep.Sx + off);
+  } else if (ep.Z && (cb0 != 0.0 || cb1 != 0.0 || csz != 0.0)) {
     const T coef = (T)(cb0 + cb1 * (double)deg);
     z = ldf_m<T, VW, MASK>(ep.Z + off, true);
 #pragma unroll
     for (int i = 0; i < VW; ++i) y[i] += coef * z.v[i];
   }
-  if constexpr ((E & EPI_SZ) != 0)  // (before Y is written: it may be the same buffer)
-    z = (MASK && VW == 1) ? ldf_m<T, VW, MASK>(ep.Sx + off, true) : ldf_nt<T, VW>(ep.Sx + off);
   if constexpr ((E & EPI_NFAC) != 0 && VW > 1) right_factor<T, VW>(y, cl, TILE, sN);
   if (ep.C) c_term<T, VW>(r, ld, b, col, cl, TILE, ep, sC, y);
   if (Y) {
@@ -554,8 +554,8 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
     }
     n_long = lo;
   }
-  const bool own_z = ep.Sx && !ep.gid && !ep.ctab;
-  WL_CHECK(!own_z || (!ep.Nm && !ep.Z), WL_EINTERNAL, "spmm: a sum with its own Z goes with no other variant");
+  WL_CHECK(!ep.own_z || (!ep.Nm && !ep.Z && !ep.gid && !ep.ctab), WL_EINTERNAL,
+           "spmm: a sum with its own Z goes with no other variant");
   WL_CHECK(!ep.Nm || (VW == 4 && !(ep.cmap && ep.Sout)), WL_EINTERNAL,
            "spmm: the deferred-normalisation factor needs FP32 16-byte vectors and takes no running sum");
   constexpr int RPB = 256 / G;
@@ -589,7 +589,7 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
       hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, EPI_COLS>), grid, dim3(256), lds, ctx->stream, g->rowptr,
                          g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
   }
-  if (own_z)
+  if (ep.own_z)
     hipLaunchKernelGGL((k_spmm<T, VW, LPN, G, MASK, EPI_SZ>), grid, dim3(256), lds, ctx->stream, g->rowptr,
                        g->colidx, g->n, b, b, X, Y, epx, lr, n_long, long_thr);
   else if (!ep.Nm && !ep.cmap)
@@ -599,7 +599,7 @@ wl_status run(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, int lo
   if (ks) {
     // algorithmic bytes: CSR once, the gathered block once (compulsory), every row stream once
     const double s = sizeof(T), nb = (double)g->n * b;
-    const double streams = 1 + (Y ? 1 : 0) + (ep.Z || own_z ? 1 : 0) + (ep.C ? 1 : 0) +
+    const double streams = 1 + (Y ? 1 : 0) + (ep.Z || (ep.own_z && ep.Sx) ? 1 : 0) + (ep.C ? 1 : 0) +
                            ep.s_share * ((ep.Sin ? 1 : 0) + (ep.Sout ? 1 : 0)) + (ep.Xw ? 1 : 0) + (ep.jx ? 1 : 0);
     WL_TRY(kstats_end(ctx, ks, 4.0 * g->nnz + 4.0 * (g->n + 1) + s * nb * streams + (ep.wv ? s * g->n : 0.0) +
                                    (ep.jw ? s * g->n : 0.0)));

@@ -259,12 +259,11 @@ struct EpiArgs {
   const T* Z2 = nullptr;
   const double* C = nullptr;
   int transC = 0;
+  int own_z = 0;  // without tables: the running sum's Z is Sx (may be null) and Z is null
   const T* Sin = nullptr;
   T* Sout = nullptr;
   double s0 = 0.0, sc = 0.0, sz = 0.0;
-  // Without tables: Z of the running sum alone, where y has no use for it (Z is null then; 0 x
-  // infinity would be NaN).
-  const T* Sx = nullptr;  // With gtab or ctab: the SS_X source of the running sum
+  const T* Sx = nullptr;  // with gtab or ctab: the SS_X source of the running sum
   double s_share = 1.0;   // share of the block whose running sum this launch reads (byte counts)
   const T* wv = nullptr;
   const T* Xw = nullptr;
