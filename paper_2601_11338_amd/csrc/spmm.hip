@@ -430,9 +430,10 @@ constexpr int gather_unroll() {
 // EPI_COLS, 5 operators and their walk degrees 21.6 / 23.2.  The last kind spills 4
 // registers in its epilogue all the same; forms that do not were slower (21.9 with one source vector
 // for both sources of the running sum, 24.9 with Z read again).  FP64 blocks need twice the
-// registers.
+// registers, but for one and two columns (left at four waves these took 86 and 122: 1M-node
+// lattice, one column 24 us and two columns 30 us, 19 and 20 so).
 template <typename T, int VW, int LPN, int G, bool MASK, int E>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void k_spmm(const int32_t* __restrict__ rowptr,
+__global__ __launch_bounds__(256, sizeof(T) == 4 || LPN == 1 ? 8 : 4) void k_spmm(const int32_t* __restrict__ rowptr,
                                               const int32_t* __restrict__ colidx, int64_t n, int ld, int b,
                                               const T* __restrict__ X, T* Y, EpiArgs<T> ep,
                                               const int32_t* __restrict__ long_rows, int n_long,

@@ -30,7 +30,7 @@ def code_objects(data):
 
 
 def kernels(tmp_path):
-    """{kernel name: spilled vector registers}"""
+    """{kernel name: (vector registers, spilled ones)}"""
     out = {}
     path = tmp_path / "code"
     for obj in code_objects(open(LIB, "rb").read()):
@@ -38,7 +38,7 @@ def kernels(tmp_path):
         notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
         for k in notes.split("- .agpr_count:")[1:]:
             name = re.search(r"\.name:\s+(\S+)", k).group(1)
-            out[name] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", k).group(1))
+            out[name] = tuple(int(re.search(r"\.%s:\s+(\d+)" % f, k).group(1)) for f in ("vgpr_count", "vgpr_spill_count"))
     return out
 
 
@@ -48,7 +48,10 @@ def test_products_do_not_spill(tmp_path):
     found = kernels(tmp_path)
     # k_spmm<T, VW, LPN, G, MASK, E>: E = 1 (per-column coefficients with a running sum) is
     # faster with its four spilled registers than in any form without
-    spmm = {n: s for n, s in found.items() if "k_spmmI" in n}
+    spmm = {n: s for n, (_, s) in found.items() if "k_spmmI" in n}
     assert len(spmm) > 100
     spilled = {n: s for n, s in spmm.items() if s > (4 if "ELi1EEEv" in n else 0)}
     assert not spilled
+    # one and two FP64 columns: eight waves per SIMD
+    narrow = {n: v for n, (v, _) in found.items() if re.search(r"k_spmmIdLi[12]ELi1ELi", n)}
+    assert len(narrow) > 8 and max(narrow.values()) <= 64
