@@ -157,20 +157,31 @@ static int segment_lanes(int prec, int b) {
 // 1.78 ms with one slot, 1.56 with eight).
 // Rows over the threshold go to whole workgroups: 16 rounds of a row's slots (R-MAT 2^19, 64
 // wide: 415 us at 512 to 2048, 447 at 256; flat for the graphs without heavy tails), 4 rounds
-// in a small graph.
+// in a small graph.  A round takes about 1.1 us, so on dense graphs (from 16 neighbours on, R-MAT
+// among them) it is as many as fit a quarter of the product's own time, from 4 on (8 from four
+// lanes on), and single lanes take slots up to 2^20 lanes.  R-MAT 2^17, 2 columns: 28.7 us with 4
+// slots and 512, 21.3 at 128, 19.5 with 8 slots and 256; R-MAT 2^15, 16 columns: 16.1 us with 4
+// slots and 512, 12.5 at 128.
 SpmmShape shape_for(wl_graph* g, int prec, int b) {
   auto it = g->tuned.find(prec * 1000 + std::min(b, 999));
   if (it != g->tuned.end()) return it->second;
   SpmmShape s;
-  const int lpn = std::min(segment_lanes(prec, b), spmm_max_lanes(g->n));
+  const int lpn = std::min(segment_lanes(prec, b), spmm_max_lanes(g, b * (prec == WL_FP32 ? 4 : 8)));
   int ns = 1;
   while (ns < 64 && 8.0 * ns * std::sqrt(2.0) < g->mean_deg) ns <<= 1;  // nearest power of two
   if (lpn == 4 && g->mean_deg >= 6.0) ns = std::max(ns, 2);
-  int thr = 128 * ns;
-  if (g->n * lpn * ns < (1 << 19)) {
-    while (g->n * lpn * ns < (1 << 19) && 2.0 * ns < g->mean_deg) ns <<= 1;
-    thr = 32 * ns;
+  const bool dense = g->mean_deg >= 16.0;
+  const int64_t few = dense && lpn == 1 ? 1 << 20 : 1 << 19;
+  int rounds = 16;
+  if (g->n * lpn * ns < few) {
+    while (g->n * lpn * ns < few && 2.0 * ns < g->mean_deg) ns <<= 1;
+    rounds = 4;
   }
+  if (dense && rounds == 16) {
+    const double us = 1e-6 * (double)g->nnz * (4.0 + 0.11 * b * (prec == WL_FP32 ? 4 : 8));  // the product's time
+    rounds = (int)std::max(lpn >= 4 ? 8.0 : 4.0, std::min(16.0, us / 4.4));
+  }
+  const int thr = 8 * rounds * ns;
   s.G = std::max(4, std::min(64, lpn * ns));
   s.long_thr = std::max(g->long_min_thr, thr);
   return s;

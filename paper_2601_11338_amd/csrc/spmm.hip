@@ -499,7 +499,26 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 || LPN == 1 ? 8 : 4) void k_spm
     const int s = rowptr[r], e = rowptr[r + 1];
     Frag<T, VW> acc;
     zero(acc);
-    gather_sum<T, VW, MASK, gather_unroll<T, VW>()>(colidx, s + slot, e, NSLOT, X, ld, col, colok, acc);
+    int k = s + slot;
+    if constexpr (VW == 1 && sizeof(T) == 4 && MASK) {
+      // whole batches without a branch at each load, where the loads would wait for one another
+      // (us a product, with / without: 100k nodes joined to 20 hubs, 13 columns 40 / 20; R-MAT 2^16,
+      // degree 28, 13 columns 80 / 39)
+      constexpr int U = gather_unroll<T, VW>();
+      const int cu = colok ? col : 0;
+      for (; k + (U - 1) * NSLOT < e; k += U * NSLOT) {
+        int32_t j[U];
+        T x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) j[u] = colidx[k + u * NSLOT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = X[(int64_t)j[u] * ld + cu];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc.v[0] += x[u];
+      }
+      if (!colok) zero(acc);
+    }
+    gather_sum<T, VW, MASK, gather_unroll<T, VW>()>(colidx, k, e, NSLOT, X, ld, col, colok, acc);
 #pragma unroll
     for (int off = LPN; off < 64; off <<= 1) add_shfl_xor(acc, off);
     const int wave = threadIdx.x >> 6;
@@ -645,6 +664,8 @@ template <typename T>
 wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep, const SpmmShape& sh) {
   if (g->n == 0) return WL_OK;
   constexpr int VW = vec_width<T>();
+  // narrower column tiles, in each branch below, where a launch or a hub's row asks for them
+  const int row_bytes = b * (int)sizeof(T), most = spmm_max_lanes(g, row_bytes);
   const bool vec_ok = (b % VW == 0) && (!ep.ctab || ep.cgw % VW == 0) && aligned_to<T>(ep, X, Y, 16);
   if (vec_ok) {
     const int lanes = b / VW;  // lanes needed for the whole row segment
@@ -655,7 +676,8 @@ wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep
     // 17..31 vectors (e.g. 96 FP32 values): with 32 or more lanes per row one 32-lane
     // segment covers the whole row (idle lanes masked), each neighbour's row gathered by
     // one group in one go; with fewer the row is cut into column tiles (below)
-    if (lanes > 16 && lanes < 32 && sh.G >= 32) return run_g<T, VW, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+    if (lanes > 16 && lanes < 32 && sh.G >= 32 && most >= 32)
+      return run_g<T, VW, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
     // 12 vectors (48 FP32 values): one 16-lane segment with the last four lanes idle
     // gathers each neighbour row once, where three 4-lane tiles would gather it thrice
     if (lanes == 12) return run_g<T, VW, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
@@ -669,25 +691,26 @@ wl_status launch_spmm(wl_graph* g, const T* X, T* Y, int b, const EpiArgs<T>& ep
     if (lanes < 16) return run_g<T, VW, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   }
   // even widths of FP32 blocks that are no multiple of 4 (or only 8-byte aligned): 8-byte
-  // vectors, a row in one segment up to 64 columns (in tiles of 32 where spmm_max_lanes allows
-  // 16 lanes only).  (30 columns, 100k nodes of degree 10,
+  // vectors, a row in one segment up to 64 columns.  (30 columns, 100k nodes of degree 10,
   // Lanczos epilogue: the scalar path's two 16-column tiles took 316 us, this 56 us.)
   if constexpr (sizeof(T) == 4) {
     if (b % 2 == 0 && !ep.cmap && (!ep.ctab || ep.cgw % 2 == 0) && aligned_to<T>(ep, X, Y, 8)) {
       const int lanes = b / 2;
       if (lanes == 1) return run_g<T, 2, 1, false>(g, X, Y, b, ep, sh.G, sh.long_thr);
       if (lanes <= 4) return run_g<T, 2, 4, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-      if (lanes <= 8) return run_g<T, 2, 8, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-      if (lanes <= 16 || spmm_max_lanes(g->n) < 32) return run_g<T, 2, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+      if (lanes <= 8 || spmm_hub_bound(g, 16, row_bytes))
+        return run_g<T, 2, 8, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+      if (lanes <= 16 || most < 32) return run_g<T, 2, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
       return run_g<T, 2, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
     }
   }
   // scalar path with column masking for any b
   if (b == 1) return run_g<T, 1, 1, false>(g, X, Y, b, ep, sh.G, sh.long_thr);
   if (b <= 2) return run_g<T, 1, 2, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-  if (b <= 4) return run_g<T, 1, 4, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+  if (b <= 4 || (b <= 8 && spmm_hub_bound(g, 8, row_bytes)))
+    return run_g<T, 1, 4, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   if (b <= 8) return run_g<T, 1, 8, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
-  if (b <= 16 || spmm_max_lanes(g->n) < 32) return run_g<T, 1, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
+  if (b <= 16 || most < 32) return run_g<T, 1, 16, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
   return run_g<T, 1, 32, true>(g, X, Y, b, ep, sh.G, sh.long_thr);
 }
 

@@ -112,10 +112,6 @@ struct SpmmShape {
   int long_thr = 512;  // rows with more neighbours go to whole workgroups
 };
 
-// Lanes that a row segment of the 8-byte and scalar products may take: 32 lanes a row reach the
-// 2^32 threads of a launch at 2^27 rows.
-inline int spmm_max_lanes(int64_t n) { return n < ((int64_t)1 << 27) ? 32 : 16; }
-
 // Live timing of kernel classes (opt-in): HIP events recorded around each launch
 // on the context stream, algorithmic bytes counted per launch.
 // Timing classes of sparse products: single-operator series steps (b >= 4), Lanczos
@@ -203,6 +199,20 @@ struct wl_op {
 };
 // Frees the operator's return-probability work buffers (with the stream drained).
 void rk_cache_destroy(wl_op* op);
+
+// Does the longest row set the time of a product with `lanes` lanes a neighbour?  Its workgroup's
+// 256 / lanes slots have eight gathers each in flight for about 1.1 us, against 5 TB/s for the
+// lines of all gathers.
+inline bool spmm_hub_bound(const wl_graph* g, int lanes, int row_bytes) {
+  return 1.1 * g->max_deg * lanes / 2048.0 > (double)g->nnz * ((row_bytes + 127) / 128) * 128.0 / 5e6;
+}
+// Lanes that a row segment may take: 32 a row reach the 2^32 threads of a launch at 2^27 rows, and
+// narrower column tiles shorten the chain of a hub's row (100k nodes joined to 20 hubs, us a product
+// with 32 lanes and with 16 or fewer: FP64, 17 columns 107 and 66, 48 columns 93 and 43; FP32, 30
+// columns 57 and 38, 96 columns 104 and 37).
+inline int spmm_max_lanes(const wl_graph* g, int row_bytes) {
+  return g->n < ((int64_t)1 << 27) && !spmm_hub_bound(g, 32, row_bytes) ? 32 : 16;
+}
 
 // ------------------------------------------------------------------ launch interfaces
 // Running sum of a truncated series S = sum_k omega_k P_k, k = 0..K, P_0 = X.  A step
