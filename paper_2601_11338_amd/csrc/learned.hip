@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 #include <vector>
 
 #include "wl_internal.h"
@@ -73,9 +74,10 @@ __device__ __forceinline__ double wave_add(double v) {
 // Sums over the neighbours of row i: s1 = sum d_j, s2 = sum d_j^2, mx = max d_j, by a group
 // of G lanes (every lane gets the result) or by a workgroup (G = 256, result in all threads).
 // The sums are integers below 2^53, so their order does not matter.  Rows of up to
-// ROWSUM_LONG neighbours take 16 lanes, the others (first in the decreasing-degree list) a
-// workgroup each: with one thread per row a hub row's chain of dependent loads set the time
-// (R-MAT of 2^19 nodes, features 6408 us and surrogate 6325 us; now 127 and 132 us).
+// ROWSUM_LONG neighbours take 16 lanes (of up to 64 one lane, in sparse graphs), the others (first
+// in the decreasing-degree list) a workgroup each: with one thread for every row a hub's chain of
+// dependent loads set the time (R-MAT of 2^19 nodes, degree 30: features 6235 us and surrogate
+// 5858 us; now 146 and 98 us).
 constexpr int ROWSUM_LONG = 512;
 struct RowSums {
   double s1, s2, mx;
@@ -114,49 +116,53 @@ __device__ __forceinline__ RowSums row_sums(const int32_t* __restrict__ rowptr, 
   return r;
 }
 
-// f(row, this thread's place in its group, neighbour sums) for every row: the first n_long
-// workgroups take one long row each, the others 16 short rows at a time (a launch is limited to
-// 2^32 threads, which one group per row would reach at 2^28 rows).
+// f(row, this thread's place in its group, lanes of the group, neighbour sums) for every row: the
+// first n_long workgroups take one row of more than long_deg neighbours each, the others 256 / W
+// rows at a time, W lanes each (a launch is limited to 2^32 threads, which 16 lanes per row would
+// reach at 2^28 rows).
 constexpr int64_t ROWSUM_WGS = 1 << 20;
-template <typename F>
+template <int W, typename F>
 __device__ __forceinline__ void for_rows(int64_t n, const int32_t* __restrict__ rowptr,
                                          const int32_t* __restrict__ colidx, const int32_t* __restrict__ long_rows,
-                                         int n_long, F f) {
+                                         int n_long, int long_deg, F f) {
   if ((int)blockIdx.x < n_long) {
     const int64_t row = long_rows[blockIdx.x];
-    f(row, (int)threadIdx.x, row_sums<256>(rowptr, colidx, rowptr[row], rowptr[row + 1], threadIdx.x));
+    f(row, (int)threadIdx.x, std::integral_constant<int, 256>(),
+      row_sums<256>(rowptr, colidx, rowptr[row], rowptr[row + 1], threadIdx.x));
     return;
   }
-  const int sub = threadIdx.x & 15;
-  const int64_t step = ((int64_t)gridDim.x - n_long) * 16;
-  for (int64_t row = ((int64_t)blockIdx.x - n_long) * 16 + (threadIdx.x >> 4); row < n; row += step) {
-    const int32_t a = rowptr[row], b = rowptr[row + 1];  // (the 16 lanes of a group stay together)
-    if (b - a <= ROWSUM_LONG) f(row, sub, row_sums<16>(rowptr, colidx, a, b, sub));
+  const int sub = threadIdx.x % W;
+  const int64_t step = ((int64_t)gridDim.x - n_long) * (256 / W);
+  for (int64_t row = ((int64_t)blockIdx.x - n_long) * (256 / W) + threadIdx.x / W; row < n; row += step) {
+    const int32_t a = rowptr[row], b = rowptr[row + 1];  // (the lanes of a group stay together)
+    if (b - a <= long_deg) f(row, sub, std::integral_constant<int, W>(), row_sums<W>(rowptr, colidx, a, b, sub));
   }
 }
 
+template <int W>
 __global__ __launch_bounds__(256) void k_features(int64_t n, const int32_t* __restrict__ rowptr,
                                                   const int32_t* __restrict__ colidx,
                                                   const unsigned long long* __restrict__ tri2, double s,
                                                   float* __restrict__ feat, const int32_t* __restrict__ long_rows,
-                                                  int n_long) {
-  for_rows(n, rowptr, colidx, long_rows, n_long, [&](int64_t i, int f, const RowSums& rs) {
-    if (f >= NIN) return;
+                                                  int n_long, int long_deg) {
+  for_rows<W>(n, rowptr, colidx, long_rows, n_long, long_deg, [&](int64_t i, int sub, auto lanes, const RowSums& rs) {
     const double d = rowptr[i + 1] - rowptr[i];
     const double t = tri2 ? 0.5 * (double)tri2[i] : 0.0;
-    // lane f of the group writes feature f
-    double x;
-    switch (f) {
-      case 0: x = s * d; break;
-      case 1: x = s * s * d; break;
-      case 2: x = s * s * s * 2.0 * t; break;
-      case 3: x = s * s * rs.s1; break;
-      case 4: x = s * (d > 0 ? rs.s1 / d : 0.0); break;
-      case 5: x = s * (d > 0 ? sqrt(rs.s2 / d) : 0.0); break;
-      case 6: x = s * rs.mx; break;
-      default: x = d >= 2 ? 2.0 * t / (d * (d - 1.0)) : 0.0; break;
+#pragma unroll
+    for (int f = sub; f < NIN; f += decltype(lanes)::value) {
+      double x;
+      switch (f) {
+        case 0: x = s * d; break;
+        case 1: x = s * s * d; break;
+        case 2: x = s * s * s * 2.0 * t; break;
+        case 3: x = s * s * rs.s1; break;
+        case 4: x = s * (d > 0 ? rs.s1 / d : 0.0); break;
+        case 5: x = s * (d > 0 ? sqrt(rs.s2 / d) : 0.0); break;
+        case 6: x = s * rs.mx; break;
+        default: x = d >= 2 ? 2.0 * t / (d * (d - 1.0)) : 0.0; break;
+      }
+      feat[i * NIN + f] = (float)(f < 7 ? log1p(x) : x);
     }
-    feat[i * NIN + f] = (float)(f < 7 ? log1p(x) : x);
   });
 }
 
@@ -533,14 +539,15 @@ __device__ inline void surrogate_terms(double d, double s2, double tri2, double 
   *scale = c4 * fmax(1.0, d * d + s2);
 }
 
-template <typename T>
+template <typename T, int W>
 __global__ __launch_bounds__(256) void k_surrogate_diag(int64_t n, const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ colidx,
                                                         const unsigned long long* __restrict__ tri2, double c2m,
                                                         double c3, double c4, T* __restrict__ base,
                                                         T* __restrict__ scale,
-                                                        const int32_t* __restrict__ long_rows, int n_long) {
-  for_rows(n, rowptr, colidx, long_rows, n_long, [&](int64_t r, int sub, const RowSums& rs) {
+                                                        const int32_t* __restrict__ long_rows, int n_long,
+                                                        int long_deg) {
+  for_rows<W>(n, rowptr, colidx, long_rows, n_long, long_deg, [&](int64_t r, int sub, auto, const RowSums& rs) {
     if (sub != 0) return;
     double bs, sc;
     surrogate_terms(rowptr[r + 1] - rowptr[r], rs.s1, (double)tri2[r], c2m, c3, c4, &bs, &sc);
@@ -575,13 +582,27 @@ __global__ void k_affine(int64_t n, const float* __restrict__ base, const float*
     y[i] = (base ? base[i] : 0.f) + (scale ? scale[i] : 1.f) * y[i];
 }
 
-// workgroups of the neighbour-sum kernels (nl: rows that take one of their own)
-dim3 rowsum_grid(int64_t n, int nl) { return dim3((unsigned)(nl + std::min((n + 15) / 16, ROWSUM_WGS))); }
-// rows that take a whole workgroup in the neighbour-sum kernels
-int rowsum_long(const wl_graph* g) {
+// Launch of the neighbour-sum kernels: lanes a short row, rows of a workgroup each, workgroups.
+// One lane a row where rows are short (below a mean degree of one_lane_deg) and many enough to
+// fill the chip; us with 1 / 16 lanes: features, lattice of 1M nodes 57 / 153, 500k nodes of degree 12
+// 83 / 90, of 16 107 / 94; surrogate, degree 6 23 / 31, 8 31 / 33, 12 52 / 40; features of 3000 nodes
+// of degree 8 22 / 18.
+constexpr double FEATURES_ONE_LANE = 14.0, SURROGATE_ONE_LANE = 8.0;
+constexpr int64_t ROWSUM_SMALL = 1 << 15;
+struct RowSumShape {
+  int lanes, long_deg, n_long;
+  dim3 grid;
+};
+RowSumShape rowsum_shape(const wl_graph* g, double one_lane_deg) {
+  RowSumShape s;
+  s.lanes = g->n >= ROWSUM_SMALL && g->mean_deg < one_lane_deg ? 1 : 16;
+  s.long_deg = s.lanes == 1 ? g->long_min_thr : ROWSUM_LONG;
   const auto& dd = g->h_long_deg;  // decreasing
-  return (int)(std::lower_bound(dd.begin(), dd.end(), ROWSUM_LONG, [](int32_t d, int t) { return d > t; }) -
-               dd.begin());
+  s.n_long = (int)(std::lower_bound(dd.begin(), dd.end(), s.long_deg, [](int32_t d, int t) { return d > t; }) -
+                   dd.begin());
+  const int rows = 256 / s.lanes;
+  s.grid = dim3((unsigned)(s.n_long + std::min((g->n + rows - 1) / rows, ROWSUM_WGS)));
+  return s;
 }
 
 // c_2 (1 - mu), c_3, c_4 of the operator's weights
@@ -633,9 +654,9 @@ wl_status wl_features(wl_graph* g, double scale, void* d_feat) {
   hipStream_t st = g->ctx->stream;
   const unsigned long long* tri = nullptr;
   WL_TRY(graph_tri2(g, &tri));
-  const int nl = rowsum_long(g);
-  hipLaunchKernelGGL(k_features, rowsum_grid(g->n, nl), dim3(256), 0, st, g->n, g->rowptr,
-                     g->colidx, tri, scale, (float*)d_feat, g->long_rows.as<int32_t>(), nl);
+  const RowSumShape sh = rowsum_shape(g, FEATURES_ONE_LANE);
+  hipLaunchKernelGGL((sh.lanes == 1 ? k_features<1> : k_features<16>), sh.grid, dim3(256), 0, st, g->n, g->rowptr,
+                     g->colidx, tri, scale, (float*)d_feat, g->long_rows.as<int32_t>(), sh.n_long, sh.long_deg);
   WL_HIP(hipGetLastError());
   WL_HIP(hipStreamSynchronize(st));
   return WL_OK;
@@ -687,14 +708,15 @@ wl_status wl_surrogate_diag(wl_op* op, void* d_base, void* d_scale) {
   WL_TRY(graph_tri2(g, &tri));
   double c2m, c3, c4;
   surrogate_coeffs(op, &c2m, &c3, &c4);
-  const int nl = rowsum_long(g);
-  const dim3 grid = rowsum_grid(g->n, nl);
+  const RowSumShape sh = rowsum_shape(g, SURROGATE_ONE_LANE);
   if (op->d.prec == WL_FP32)
-    hipLaunchKernelGGL(k_surrogate_diag<float>, grid, dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri,
-                       c2m, c3, c4, (float*)d_base, (float*)d_scale, g->long_rows.as<int32_t>(), nl);
+    hipLaunchKernelGGL((sh.lanes == 1 ? k_surrogate_diag<float, 1> : k_surrogate_diag<float, 16>), sh.grid, dim3(256),
+                       0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri, c2m, c3, c4, (float*)d_base,
+                       (float*)d_scale, g->long_rows.as<int32_t>(), sh.n_long, sh.long_deg);
   else
-    hipLaunchKernelGGL(k_surrogate_diag<double>, grid, dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri,
-                       c2m, c3, c4, (double*)d_base, (double*)d_scale, g->long_rows.as<int32_t>(), nl);
+    hipLaunchKernelGGL((sh.lanes == 1 ? k_surrogate_diag<double, 1> : k_surrogate_diag<double, 16>), sh.grid,
+                       dim3(256), 0, g->ctx->stream, g->n, g->rowptr, g->colidx, tri, c2m, c3, c4, (double*)d_base,
+                       (double*)d_scale, g->long_rows.as<int32_t>(), sh.n_long, sh.long_deg);
   WL_HIP(hipGetLastError());
   return WL_OK;
 }
