@@ -209,9 +209,10 @@ __global__ __launch_bounds__(256) void k_update_seg(int64_t N, const float* X, i
   }
 }
 
-__global__ void k_dcopy_batched(int count, const double* __restrict__ x, double* __restrict__ y, int64_t gs) {
-  const int64_t go = (int64_t)blockIdx.x * gs;
-  for (int e = threadIdx.x; e < count; e += blockDim.x) y[go + e] = x[go + e];
+__global__ void k_dcopy_batched(int count, const double* __restrict__ x, double* __restrict__ y, int64_t gx,
+                                int64_t gy) {
+  const int64_t g = blockIdx.x;
+  for (int e = threadIdx.x; e < count; e += blockDim.x) y[g * gy + e] = x[g * gx + e];
 }
 
 // Graphs whose Krylov space is exhausted at step j (kcap[g] == j + 1 blocks span their
@@ -579,7 +580,7 @@ wl_status expv_prepare(wl_batch* bt, BatchWork& wk, int b, int K) {
   const int nunits = (int)bt->us.size() - 1;
   WL_TRY(wk.basis.ensure((size_t)(K + 1) * blk * 4));
   WL_TRY(wk.S.ensure((size_t)ng * gs * 8));
-  WL_TRY(wk.F.ensure((size_t)ng * K * b * b * 8));
+  WL_TRY(wk.F.ensure((size_t)ng * (K + 1) * b * b * 8));  // F of every graph, then R0 of every graph
   WL_TRY(wk.tvals.ensure((size_t)ng * 8));
   WL_TRY(wk.kcap.ensure((size_t)ng * 4));
   WL_TRY(wk.partials.ensure((size_t)3 * nunits * 256 * sizeof(double)));
@@ -653,7 +654,8 @@ wl_status expv_enqueue(wl_batch* bt, BatchWork& wk, const float* U0, int b, int 
     WL_TRY(launch_chol(ctx, b, S + Ly.G(), tol, nullptr, nullptr, nullptr, S + Ly.Ri1(), nullptr, S + Ly.R1(), ng, gs,
                        nullptr, S + Ly.Ref(), ptol));
     if (j + 1 == K) {  // residual coupling B_{K-1} = R1 of every graph
-      hipLaunchKernelGGL(k_dcopy_batched, dim3(ng), dim3(64), 0, ctx->stream, b * b, S + Ly.R1(), S + Ly.B(j), gs);
+      hipLaunchKernelGGL(k_dcopy_batched, dim3(ng), dim3(64), 0, ctx->stream, b * b, S + Ly.R1(), S + Ly.B(j), gs,
+                         gs);
       WL_HIP(hipGetLastError());
       break;
     }
@@ -686,10 +688,13 @@ wl_status return_probabilities(wl_batch* bt, BatchWork& wk, int b, int K, double
   const int64_t gs = Ly.total();
   if (p_hat || p_err) {
     // Nystrom trace per graph from F_g and R0_g alone (Omega = V_0 R0, Y = V F).
-    std::vector<double> hF((size_t)ng * K * b * b), hR((size_t)ng * b * b);
+    // (one copy to the host: a strided one takes 5 us a graph)
+    std::vector<double> hF((size_t)ng * (K + 1) * b * b);
+    const double* hR = hF.data() + (size_t)ng * K * b * b;
+    hipLaunchKernelGGL(k_dcopy_batched, dim3(ng), dim3(64), 0, ctx->stream, b * b, wk.S.as<double>() + Ly.R0(),
+                       wk.F.as<double>() + (size_t)ng * K * b * b, gs, (int64_t)b * b);
+    WL_HIP(hipGetLastError());
     WL_HIP(hipMemcpyAsync(hF.data(), wk.F.p, hF.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-    WL_HIP(hipMemcpy2DAsync(hR.data(), (size_t)b * b * 8, wk.S.as<double>() + Ly.R0(), (size_t)gs * 8,
-                            (size_t)b * b * 8, ng, hipMemcpyDeviceToHost, ctx->stream));
     WL_HIP(hipStreamSynchronize(ctx->stream));
     for (int g = 0; g < ng; ++g) {
       const double* Fg = &hF[(size_t)g * K * b * b];
