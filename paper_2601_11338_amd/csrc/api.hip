@@ -453,6 +453,7 @@ wl_status wl_graph_create(wl_ctx* ctx, int64_t n, int64_t nnz, const int32_t* d_
       return fail(WL_EINVAL);
     }
     maxd = std::max(maxd, d);
+    g->small_long += d > SMALL_LONG;
     if (d > g->long_min_thr) longs.emplace_back(d, (int32_t)r);
   }
   g->max_deg = maxd;

@@ -30,7 +30,6 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int SMALL_T = 1024;         // threads
 constexpr int SMALL_W = SMALL_T / 64;  // waves
 constexpr int SMALL_B = 4;            // columns of a block
-constexpr int SMALL_LONG = 32;        // neighbours up to which a row is one thread's
 constexpr int SMALL_K = 256;          // steps k_vec_lanczos keeps scalars for
 constexpr int64_t SMALL_BLOCK_VALUES = 5000;  // rows times columns of a block
 typedef uint16_t idx_t;               // columns and row pointers in LDS
@@ -866,11 +865,16 @@ void small_rows(int64_t n, F f) {
 // FP64, Erdos-Renyi 300 / 1000 / 4000 nodes 115 / 159 / 366 us against 1.4 to 1.6 ms of launches).  Two
 // to four columns keep their blocks in memory and stop at 5000 values (2 columns of 2000 nodes
 // 0.98 ms against 1.4 to 1.7; 4 of 1000 0.80).  Kernel statistics count products per launch, so
-// profiling keeps the general path.
+// profiling keeps the general path.  A row of more than SMALL_LONG neighbours is a wave's task of
+// 0.7 us (one column), which 16 waves share; they may take about 20 us of a step for one column and
+// 12 for blocks, whose rows take 0.45 (FP32) or 0.7 us (FP64) a column (30 steps, ms, small / general:
+// 1000 nodes of degree 40, one column FP32 1.44 / 1.19; 500 of degree 50, one 0.83 / 1.21, four
+// FP64 2.79 / 1.31).
 bool small_lanczos_ok(const wl_graph* g, int prec, int b, int K, int reorth) {
   const size_t es = prec == WL_FP32 ? 4 : 8;
   if (g->ctx->h_flag == nullptr || reorth > 1) return false;
-  if (b == 1) return K <= SMALL_K && small_graph(g, es, 2, 148 * 1024);
+  if (b == 1) return K <= SMALL_K && g->small_long <= (es == 4 ? 500 : 400) && small_graph(g, es, 2, 148 * 1024);
+  if (g->small_long * b * es > 1600) return false;
   return b <= SMALL_B && g->n * b <= SMALL_BLOCK_VALUES && small_graph(g, es, 2 * b, 120 * 1024);
 }
 
@@ -954,9 +958,13 @@ wl_status launch_small_orth(wl_graph* g, int K, int j, int lo, T* basis, const T
 // One workgroup per column, graph and three vectors in LDS; a step costs about 0.15 ns per entry
 // against 3.4 us for a launch of the general kernel (40 steps, FP64: Erdos-Renyi 1000 nodes of degree
 // 8, 74 us against 136; 2000 nodes, 130 against 136; Barabasi-Albert 1000 nodes of degree 10, 133 against
-// 162; 2500 nodes, 290 against 185).
+// 162; 2500 nodes, 290 against 185).  Rows of more than SMALL_LONG neighbours cost more: up to 80 of them
+// in FP32, 40 in FP64 (30 steps, us: 100 nodes, 94 such rows, FP64 178 against 151; 300 nodes of degree
+// 40 403 against 139; 500 nodes, 29 such rows, 130 against 137).
 bool small_series_ok(const wl_graph* g, int prec, int K) {
-  return K >= 2 && g->n <= 2 * SMALL_T && g->nnz <= 12000 && small_graph(g, prec == WL_FP32 ? 4 : 8, 3, 150 * 1024);
+  const size_t es = prec == WL_FP32 ? 4 : 8;
+  return K >= 2 && g->n <= 2 * SMALL_T && g->nnz <= 12000 && g->small_long * es <= 320 &&
+         small_graph(g, es, 3, 150 * 1024);
 }
 
 template <typename T>

@@ -152,6 +152,8 @@ struct wl_ctx {
 };
 void ctx_release(wl_ctx* ctx);
 
+constexpr int SMALL_LONG = 32;  // neighbours up to which a row of a one-workgroup kernel is one thread's
+
 struct wl_graph {
   wl_ctx* ctx = nullptr;
   int64_t n = 0, nnz = 0;
@@ -160,6 +162,7 @@ struct wl_graph {
   DevBuf own_rowptr, own_colidx;
   int32_t max_deg = 0;
   double mean_deg = 0.0;
+  int64_t small_long = 0;  // rows of more than SMALL_LONG neighbours
   std::vector<int32_t> h_degree_hist;   // not used by kernels
   // rows sorted by decreasing degree whose degree exceeds the smallest threshold
   // any launch may use; per launch only the prefix above its threshold is taken.
