@@ -212,9 +212,10 @@ inline bool spmm_hub_bound(const wl_graph* g, int lanes, int row_bytes) {
 // Lanes that a row segment may take: 32 a row reach the 2^32 threads of a launch at 2^27 rows, and
 // narrower column tiles shorten the chain of a hub's row (100k nodes joined to 20 hubs, us a product
 // with 32 lanes and with 16 or fewer: FP64, 17 columns 107 and 66, 48 columns 93 and 43; FP32, 30
-// columns 57 and 38, 96 columns 104 and 37).
+// columns 57 and 38, 96 columns 104 and 37).  Below 1024 rows, 64 lanes each, two tiles also leave fewer
+// CUs idle (500 nodes of degree 100, exponential of 50 columns, 30 terms, 296 us with one and 228 with two).
 inline int spmm_max_lanes(const wl_graph* g, int row_bytes) {
-  return g->n < ((int64_t)1 << 27) && !spmm_hub_bound(g, 32, row_bytes) ? 32 : 16;
+  return g->n >= 1024 && g->n < ((int64_t)1 << 27) && !spmm_hub_bound(g, 32, row_bytes) ? 32 : 16;
 }
 
 // ------------------------------------------------------------------ launch interfaces

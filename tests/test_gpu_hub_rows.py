@@ -26,9 +26,12 @@ def graph(filler):
     return synth.csr_from_edges(n, hubs[keep], leaves[keep])
 
 
-@pytest.fixture(scope="module", params=[False, True], ids=["hubs", "filled"])
+@pytest.fixture(scope="module", params=["hubs", "filled", 1023, 1024])
 def case(request, lib):
-    rp, ci = graph(request.param)
+    if isinstance(request.param, int):
+        rp, ci = synth.erdos_renyi_gnm(request.param, 20 * request.param, 3)
+    else:
+        rp, ci = graph(request.param == "filled")
     return lib.Graph(lib.Context(0), rp, ci), torch.tensor(rp).cuda(), torch.tensor(ci).long().cuda()
 
 
