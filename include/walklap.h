@@ -146,7 +146,10 @@ wl_status wl_ctx_destroy(wl_ctx* ctx);
  * operator (degree >= 2, b >= 4), 1 block Lanczos operator product (b >= 4), 2 other
  * sparse products, 3 side-by-side series step (wl_multi_*, width >= 32), 4 side-by-side
  * Lanczos operator product (wl_multi_*, width >= 32), 5 finest-level products of the
- * multigrid-preconditioned CG (WL_M_AMG_CG).  Batched steps count as class 0.           */
+ * multigrid-preconditioned CG (WL_M_AMG_CG).  Batched steps count as class 0.
+ * A profiled context evaluates small graphs by the general kernels, launch by launch;
+ * without profiling one workgroup may run a whole evaluation (graphs of up to about 4096
+ * nodes), which counts no launches and takes less time.                                 */
 wl_status wl_ctx_set_profiling(wl_ctx* ctx, int32_t on);
 wl_status wl_ctx_kernel_stats(wl_ctx* ctx, int32_t kernel_class, int64_t* launches, double* total_ms,
                               double* alg_bytes);

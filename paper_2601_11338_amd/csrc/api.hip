@@ -1165,7 +1165,7 @@ template wl_status phi_apply_impl<double>(wl_op*, const double*, double*, int, c
 // eigendecomposition.  A term takes a launch, 3.2 us up to 8 columns, 4.6 at 16, 9.2 at 32, and a
 // series of degree 9.1 sqrt(z) + 24 (z = t ||T|| / 2) for every time; the eigendecomposition 65 m^2 ns
 // on 16 threads (0.65 ms at m = 100, 1.8 at 160, 6.7 at 320, 26 at 640, 115 at 1280).  Times 1, 10,
-// 100 on 20k nodes, ||T|| = 26, ms for the whole call, series / host: m = 128 7.2 / 6.3,
+// 100 on 20k nodes, walk degrees up to 26 (||T|| about 50), ms for the whole call, series / host: m = 128 7.2 / 6.3,
 // m = 160 5.7 / 5.1, m = 320 9.1 / 13.3, m = 640 12.4 / 31.9.
 constexpr int EXPV_CHEB_M = 100;     // rows of T below which the host takes less than the launches
 constexpr double EXPV_CHEB_Z = 4e4;  // z up to which the degree stays below 2000

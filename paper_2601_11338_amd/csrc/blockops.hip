@@ -1877,9 +1877,10 @@ wl_status gram_B(wl_ctx* ctx, int64_t n, const void* X, bool isf, int ldx, int64
   const int64_t parts = gram_parts(n, B, nblk);
   if constexpr (B >= 8) {
     WL_TRY(ctx->partials.ensure((size_t)parts * nblk * E * sizeof(double)));
-    if (isf)
-      gram_mx<float, B>(ctx, n, (const float*)X, ldx, sX, nblk, (const float*)Y, ldy, bx, by, (int)parts);
-    else
+    if constexpr (B < 16) {  // (wider FP32 blocks have returned above)
+      if (isf) gram_mx<float, B>(ctx, n, (const float*)X, ldx, sX, nblk, (const float*)Y, ldy, bx, by, (int)parts);
+    }
+    if (!isf)
       gram_mx<double, B>(ctx, n, (const double*)X, ldx, sX, nblk, (const double*)Y, ldy, bx, by, (int)parts);
     WL_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_gram_finalize, dim3(fin_grid(E), nblk), dim3(256), 0, ctx->stream,

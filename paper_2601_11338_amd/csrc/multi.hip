@@ -33,7 +33,8 @@ struct wl_multi {
   std::vector<wl_op_desc> desc;  // Lanczos groups: each operator's description
   std::vector<char> fin_at;  // fin_at[k]: some operator's series ends at step k
   std::vector<double> sum_at;  // sum_at[k]: share of the operators whose running sum takes terms at step k
-  DevBuf tab;      // [Kmax][nops][5] {a, b0, b1, omega, finish}
+  // [Kmax][nops][EPI_NC] {a, b0, b1, omega, finish, factor and source of the sum's second term}
+  DevBuf tab;
   DevBuf tab_phi;  // the same without the finish flags
   DevBuf W;        // walk degrees, n x nops
   bool w_valid = false;

@@ -163,7 +163,6 @@ struct wl_graph {
   int32_t max_deg = 0;
   double mean_deg = 0.0;
   int64_t small_long = 0;  // rows of more than SMALL_LONG neighbours
-  std::vector<int32_t> h_degree_hist;   // not used by kernels
   // rows sorted by decreasing degree whose degree exceeds the smallest threshold
   // any launch may use; per launch only the prefix above its threshold is taken.
   DevBuf long_rows;
